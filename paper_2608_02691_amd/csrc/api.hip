@@ -96,9 +96,11 @@ DecodePlan make_plan(int B, int Hq, int H, int max_ctx, int d_model, int groups)
   if (p.variant == 2 && chunk > 4096) chunk = 4096;  // the matrix-core scan stages <= 256 pages
   p.chunk_tokens = chunk;
   p.n_chunks = max_ctx > 0 ? (max_ctx + chunk - 1) / chunk : 1;
-  // matrix-core scan: persistent work-groups of min(H, 8) waves, enough to fill every CU
+  // matrix-core scan: persistent work-groups of min(H, 8) waves, enough to fill every CU, or fewer
+  // when the contexts cannot hold the pages for that many
   const int nw = H < 8 ? H : 8;
-  p.grid_g = num_cus() * (8 / nw);
+  const long long max_pages = ((long long)max_ctx + kBlock - 1) / kBlock;
+  p.grid_g = scan_groups(B * max_pages, B, num_cus() * (8 / nw));
   p.wo_ksplit = d_model > 0 ? wo_ksplit(Hq * kHeadDim, d_model, B) : 0;
   auto up = [](size_t x) { return (x + 255) & ~size_t(255); };
   size_t off = 0;
@@ -107,7 +109,7 @@ DecodePlan make_plan(int B, int Hq, int H, int max_ctx, int d_model, int groups)
   p.off_qop = off;
   off = up(off + qop_bytes(B, H, gq));
   p.off_prefix = off;
-  off = up(off + (size_t)(B + 1) * sizeof(int32_t));
+  off = up(off + (size_t)(B + 2) * sizeof(int32_t));
   p.off_wginfo = off;
   off = up(off + (size_t)(p.grid_g + 1) * 4 * sizeof(int32_t));
   p.off_seqwg = off;
@@ -120,7 +122,10 @@ DecodePlan make_plan(int B, int Hq, int H, int max_ctx, int d_model, int groups)
   const size_t part_rows = p.variant == 2 ? (size_t)(p.grid_g + B) : (size_t)B * p.n_chunks;
   off = up(off + part_rows * Hq * kPartStride * sizeof(float));
   // two-stage merge of the matrix-core scan for few, long sequences: folded slot ranges
-  p.s1 = p.variant == 2 && (long long)B * H < kMerge2MaxUnits ? kMerge2Ranges : 0;
+  const long long slots = max_pages / kScanMinPages + 2;  // scan groups a sequence can meet, or grid_g
+  p.s1 = p.variant == 2 && (long long)B * H < kMerge2MaxUnits && p.grid_g > kMerge2MinSlots && slots > kMerge2MinSlots
+             ? kMerge2Ranges
+             : 0;
   p.off_part2 = off;
   off = up(off + (size_t)B * p.s1 * Hq * kPartStride * sizeof(float));
   p.off_win = off;  // BF16-window partials, [kWinMaxSlices][B, Hq, kPartStride]

@@ -708,8 +708,11 @@ __device__ void page_prefix_block(const DecodeArgs& a, uint8_t* lds) {
     cnts[tid] += u;
     __syncthreads();
   }
-  const int P = sums[255], G = a.grid_g;
-  const long long W = (long long)P + (long long)kSegCost * cnts[255];
+  const int P = sums[255], nz = cnts[255], G = scan_groups(P, nz, a.grid_g);
+  // a lone sequence's start falls on every group alike; among groups of the smallest size the lead-in
+  // counts half, since a whole one would leave the first group of a sequence without pages
+  const int seg = nz <= 1 ? 0 : (long long)G * kScanMinPages >= P ? kSegCost / 2 : kSegCost;
+  const long long W = (long long)P + (long long)seg * nz;
   // few sequences: their group entries are filled by the whole block below (a long sequence spans
   // hundreds of groups, too many for one thread)
   const bool coop = a.B <= 8;
@@ -719,7 +722,7 @@ __device__ void page_prefix_block(const DecodeArgs& a, uint8_t* lds) {
     a.prefix[b] = run;
     int ga = 0, gb = -1;
     if (n > 0) {
-      const long long c0 = run + (long long)kSegCost * cnt, c1 = c0 + kSegCost + n;
+      const long long c0 = run + (long long)seg * cnt, c1 = c0 + seg + n;
       const int g1 = min(G - 1, (int)((c1 * G + W - 1) / W) - 1);
       // x(g) = floor(g W / G), stepped by quotient and remainder: one division for the whole loop
       // (a long sequence spans every group, and a 64-bit division per group costs microseconds)
@@ -727,7 +730,7 @@ __device__ void page_prefix_block(const DecodeArgs& a, uint8_t* lds) {
       const long long wq = W / G, wr = W % G;
       long long xq = (long long)g * wq + ((long long)g * wr) / G, xr = ((long long)g * wr) % G;
       for (; g <= g1; ++g) {
-        const int lo = run + (int)min((long long)n - 1, max(0LL, xq - c0 - kSegCost));
+        const int lo = run + (int)min((long long)n - 1, max(0LL, xq - c0 - seg));
         *reinterpret_cast<int4*>(a.wg_info + 4 * g) = make_int4(b, run, run + n, lo);
         xq += wq;
         xr += wr;
@@ -736,7 +739,7 @@ __device__ void page_prefix_block(const DecodeArgs& a, uint8_t* lds) {
           ++xq;
         }
       }
-      ga = min(G - 1, (int)(((c0 + kSegCost + 1) * G + W - 1) / W) - 1);
+      ga = min(G - 1, (int)(((c0 + seg + 1) * G + W - 1) / W) - 1);
       gb = g1;
       ++cnt;
     }
@@ -750,17 +753,18 @@ __device__ void page_prefix_block(const DecodeArgs& a, uint8_t* lds) {
       const int n = (seq_len_m(a, b) + kBlock - 1) >> 4;
       if (n == 0) continue;  // uniform
       const int rb = b > 0 ? sums[b - 1] : 0, cb = b > 0 ? cnts[b - 1] : 0;
-      const long long c0 = rb + (long long)kSegCost * cb, c1 = c0 + kSegCost + n;
+      const long long c0 = rb + (long long)seg * cb, c1 = c0 + seg + n;
       const int g1 = min(G - 1, (int)((c1 * G + W - 1) / W) - 1);
       for (int g = (int)((c0 * G + W - 1) / W) + tid; g <= g1; g += 256) {
         const long long x = (long long)g * W / G;
-        const int lo = rb + (int)min((long long)n - 1, max(0LL, x - c0 - kSegCost));
+        const int lo = rb + (int)min((long long)n - 1, max(0LL, x - c0 - seg));
         *reinterpret_cast<int4*>(a.wg_info + 4 * g) = make_int4(b, rb, rb + n, lo);
       }
     }
   }
   if (tid == 255) {
     a.prefix[a.B] = P;
+    a.prefix[a.B + 1] = G;
     a.wg_info[4 * G + 3] = P;  // range start of the group after the last
   }
 }
@@ -1140,18 +1144,17 @@ __global__ __launch_bounds__(512, 1) void decode_scan_flat_kernel(DecodeArgs a) 
   __shared__ __attribute__((aligned(16))) uint8_t cz_lds[kWavesPerWG][128 * NG + 16];
 
   // Work-groups are dispatched round-robin over the 8 XCDs (each with its own L2). Range g goes to
-  // the work-group dispatched as blockIdx.x with g = (x % 8) (G / 8) + x / 8, so that each XCD scans
+  // the work-group dispatched as blockIdx.x with g = (x % 8) (G / 8) + x / 8 (G groups in use), so that each XCD scans
   // one contiguous eighth of the pages: the few work-groups sharing a sequence then share that
   // sequence's query operands and page-list entries through one L2.
-  const int G = gridDim.x;
-  const int g = G % 8 == 0 ? (int)(blockIdx.x % 8) * (G / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
   const int h = blockIdx.y * kWavesPerWG + w;
   const bool all_waves = a.H < kWavesPerWG || (int)(blockIdx.y + 1) * kWavesPerWG <= a.H;
   if (h >= a.H) return;
   const cint_ptr prefix = (cint_ptr)(uintptr_t)(a.prefix);
-  const int P = prefix[a.B];
-  if (P == 0) return;
+  const int P = prefix[a.B], G = prefix[a.B + 1];
+  if (P == 0 || (int)blockIdx.x >= G) return;
+  const int g = G % 8 == 0 ? (int)(blockIdx.x % 8) * (G / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
   const cint_ptr info = (cint_ptr)(uintptr_t)(a.wg_info + 4 * g);
   const int s = info[3], e = info[7];  // lo(g), lo(g + 1)
   if (s >= e) return;
@@ -1184,15 +1187,16 @@ __global__ __launch_bounds__(512, 1) void decode_scan_flat_kernel(DecodeArgs a) 
 // pass over R_V (row c of R_V per thread) for all query heads.
 
 // First stage of the two-stage merge (few, long sequences): block (sequence b, KV head h, range z)
-// folds the work-group slots ga + z n .. ga + z n + n - 1 of the sequence (n = ceil(G / s1)) into
+// folds the work-group slots ga + z n .. ga + z n + n - 1 of the sequence (n = ceil(slots / s1)) into
 // one partial per query head, in slot order, and writes it to part2 (m = -inf for an empty range).
 // Thread (channel c, slot lane sl) takes every eighth slot; the lanes are combined in a fixed order.
-__global__ __launch_bounds__(1024) void merge_stage1_kernel(DecodeArgs a, int G) {
+__global__ __launch_bounds__(1024) void merge_stage1_kernel(DecodeArgs a) {
   __shared__ float ms[8][8], ls[8][8];
   __shared__ float os[8][8][kHeadDim];
   const int b = blockIdx.x, h = blockIdx.y, z = blockIdx.z, c = threadIdx.x & 127, sl = threadIdx.x >> 7;
-  const int gq = a.gq, per = (G + a.s1 - 1) / a.s1;
+  const int gq = a.gq;
   const int ga = a.seq_wg[2 * b], gb = a.seq_wg[2 * b + 1];
+  const int per = (gb - ga + a.s1) / a.s1;
   const int lo = ga + z * per, hi = min(gb, lo + per - 1);
   float M[8], lsum[8], osum[8];
 #pragma unroll
@@ -1254,7 +1258,7 @@ __global__ __launch_bounds__(1024) void merge_stage1_kernel(DecodeArgs a, int G)
 }
 
 template <int kMergeSlots>
-__global__ __launch_bounds__(128 * kMergeSlots) void merge_flat_kernel(DecodeArgs a, int G, int unrotate,
+__global__ __launch_bounds__(128 * kMergeSlots) void merge_flat_kernel(DecodeArgs a, int unrotate,
                                                                        float* __restrict__ out,
                                                                        uint16_t* __restrict__ ob, int fmt) {
   __shared__ float ms[kMergeSlots][8], ls[kMergeSlots][8];
@@ -1481,14 +1485,14 @@ hipError_t launch_merge_flat(const DecodeArgs& a, bool unrotate, float* out, uin
     // few, long sequences: every range of slots folded by its own block first, so that the
     // partials stream through B x H x s1 blocks instead of B x H
     DecodeArgs a1 = a;
-    hipLaunchKernelGGL(merge_stage1_kernel, dim3(a.B, a.H, a.s1), dim3(1024), 0, s, a1, a.grid_g);
-    hipLaunchKernelGGL(merge_flat_kernel<8>, dim3(a.B, a.H), dim3(128 * 8), 0, s, a, a.grid_g, unrotate ? 1 : 0, out,
+    hipLaunchKernelGGL(merge_stage1_kernel, dim3(a.B, a.H, a.s1), dim3(1024), 0, s, a1);
+    hipLaunchKernelGGL(merge_flat_kernel<8>, dim3(a.B, a.H), dim3(128 * 8), 0, s, a, unrotate ? 1 : 0, out,
                        ob, fmt);
   } else if (a.B >= 32)
-    hipLaunchKernelGGL(merge_flat_kernel<4>, dim3(a.B, a.H), dim3(128 * 4), 0, s, a, a.grid_g, unrotate ? 1 : 0, out,
+    hipLaunchKernelGGL(merge_flat_kernel<4>, dim3(a.B, a.H), dim3(128 * 4), 0, s, a, unrotate ? 1 : 0, out,
                        ob, fmt);
   else
-    hipLaunchKernelGGL(merge_flat_kernel<8>, dim3(a.B, a.H), dim3(128 * 8), 0, s, a, a.grid_g, unrotate ? 1 : 0, out,
+    hipLaunchKernelGGL(merge_flat_kernel<8>, dim3(a.B, a.H), dim3(128 * 8), 0, s, a, unrotate ? 1 : 0, out,
                        ob, fmt);
   return hipGetLastError();
 }

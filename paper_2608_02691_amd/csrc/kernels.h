@@ -64,7 +64,7 @@ struct DecodeArgs {
   uint8_t* qop;    // matrix-core query operands
   float* part;     // vector-ALU scan: [B, n_chunks, Hq, kPartStride]; matrix-core scan: [G + B, Hq, kPartStride]
   int chunk_tokens, n_chunks;
-  int32_t* prefix; // [B + 1] page prefix sums (matrix-core scan)
+  int32_t* prefix; // [B + 2] page prefix sums (matrix-core scan), then the scan groups in use
   int32_t* wg_info;  // [grid_g + 1][4]: first sequence of each scan work-group, its page range, lo(g)
   int32_t* seq_wg;   // [B][2]: first and last scan work-group whose range meets each sequence
   uint32_t* pages;   // page list of the matrix-core scan: [total pages + padding][4]
@@ -89,6 +89,7 @@ constexpr int kWinMaxCap = 512;
 constexpr int kWinSliceTokens = 96;                            // window tokens per partial
 constexpr int kMerge2Ranges = 16;      // slot ranges per sequence in the two-stage merge
 constexpr int kMerge2MaxUnits = 128;   // two-stage merge when batch x KV heads is below this
+constexpr int kMerge2MinSlots = 64;    // and a sequence can meet more scan groups than this
 // window partials per (sequence, query head)
 constexpr int kWinMaxSlices = (kWinMaxCap + kWinSliceTokens - 1) / kWinSliceTokens;
 hipError_t launch_window_write(const uint16_t* k, const uint16_t* v, const int32_t* rows, int n, int H, const float* mu,
@@ -119,6 +120,31 @@ enum OutFmt { kOutF32 = 0, kOutBf16x2 = 1, kOutF16 = 2 };
 hipError_t launch_merge(const DecodeArgs& a, bool unrotate, float* out, uint16_t* ob, int fmt, hipStream_t s);
 hipError_t launch_merge_flat(const DecodeArgs& a, bool unrotate, float* out, uint16_t* ob, int fmt, hipStream_t s);
 int num_cus();                        // compute units of the current device
+// Work-groups the matrix-core scan spreads `pages` pages of `seqs` non-empty sequences over, out of at most
+// G. A slot of partials costs the merge more than a few pages cost a group, so a group gets kScanMinPages
+// pages; half of that while a sequence still meets no more than kScanFreeSlots groups (one round of the
+// merge's loads); and never several whole sequences where a group each is left (each start is a pipeline
+// refill). One sequence is split over at most kScanMaxSlots groups. Us per call with a group per CU (or
+// more, below eight KV heads) -> this rule: one head, 256 tokens 54.8 -> 23.0; 32/8 heads, 1,011 tokens
+// 36.0 -> 30.5; 8 x 37..2,500 tokens at 32/4 heads 55.7 -> 46.5; one KV head, 4 x 4,096 tokens 70.3 ->
+// 27.7. Smallest groups of 2 pages: 23.8, 32.3, 52.5, 31.1; of 8: 23.7, 32.6, 44.8, 28.3; 64 sequences of
+// up to 200 tokens take 35.4 at 2 pages and 37.0 at 4, hence the half. Grows with both counts, so a plan
+// made for the largest pages and sequences bounds what the device computes.
+#ifndef INT2KV_SCAN_MIN_PAGES
+#define INT2KV_SCAN_MIN_PAGES 4
+#endif
+constexpr int kScanMinPages = INT2KV_SCAN_MIN_PAGES;
+constexpr int kScanFreeSlots = 4;
+constexpr int kScanMaxSlots = 512;
+__host__ __device__ inline int scan_groups(long long pages, long long seqs, int G) {
+  long long n = (pages + kScanMinPages - 1) / kScanMinPages, half = (pages + kScanMinPages / 2 - 1) / (kScanMinPages / 2);
+  if (half > kScanFreeSlots * seqs) half = kScanFreeSlots * seqs;
+  if (n < half) n = half;
+  if (n > kScanMaxSlots * seqs) n = kScanMaxSlots * seqs;
+  if (n < seqs) n = seqs;
+  if (n >= 8) n = (n + 7) & ~7LL;  // whole rounds over the 8 XCDs
+  return n < 1 ? 1 : n < G ? (int)n : G;
+}
 int wo_slice(int K, int N, int B);    // K per work-group of the output projection
 int wo_ksplit(int K, int N, int B);   // K slices of the output projection (partial products in the workspace)
 // prepared: W is int2kv_prepare_wo output and ob one fp16 term; else W is bf16 row-major, ob two bf16 terms
