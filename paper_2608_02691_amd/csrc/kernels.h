@@ -213,8 +213,7 @@ struct CalCfg {
   double* gram;           // [Hq, 128, 128]: W_{O,j}^T W_{O,j}
   double *R, *Rt;         // [H, 128, 128]: the current rotation and its transpose
   double* ex;             // [H, kCalScratch, 128, 128]
-  double* drp;            // [kCalSplit, H, 128, 128]
-  double* dr;             // [H, 128, 128]
+  double* drp;            // [kCalSplit, H, 128, 128]: dL/dR by token slice
 };
 size_t cal_set_bytes(int T, int nseq, int nrows, long long pelems, int H);
 size_t cal_shared_bytes(int H, int Hq);

@@ -15,8 +15,7 @@
 // G R masked, dL/dR = X^T (mask . G R) + G^T Zhat, dL/dE = R0^T dL/dR for E = exp(S), dL/dS as the
 // Frechet derivative of exp at S^T applied to dL/dE (the upper-right block of the exponential of
 // [[S^T, dL/dE], [0, S^T]]), and dL/dA = dL/dS - dL/dS^T.
-// exp: scaling by 2^-s until ||S||_1 <= 1/2, a Taylor polynomial of 14 terms (truncation below
-// 1e-17 relative), then s squarings; one work-group per KV head, products through LDS tiles.
+// exp: a Taylor polynomial of S 2^-j applied 2^j times, by column blocks (see the matrix functions below).
 #include <vector>
 
 #include "common.h"
@@ -28,8 +27,6 @@ namespace {
 
 constexpr int kD = kHeadDim;
 constexpr int kMat = kD * kD;
-constexpr int kExpTerms = 14;
-constexpr int kExpThreads = 1024;
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
@@ -57,18 +54,6 @@ __device__ double block_sum(double x, double* red) {
   __syncthreads();
   double t = 0.0;
   for (int i = 0; i < nw; ++i) t += red[i];  // fixed order: deterministic
-  return t;
-}
-
-__device__ double block_max(double x, double* red) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x = fmax(x, __shfl_xor(x, off));
-  const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[w] = x;
-  __syncthreads();
-  double t = red[0];
-  for (int i = 1; i < nw; ++i) t = fmax(t, red[i]);
   return t;
 }
 
@@ -940,258 +925,399 @@ __global__ __launch_bounds__(512) void cal_dr_kernel(CalSet S, CalCfg c, int val
     for (int v = 0; v < 4; ++v) out[(16 * w + lk + 4 * v) * kD + 16 * ct + li] = acc[ct][v];
 }
 
-__global__ __launch_bounds__(256) void cal_dr_reduce_kernel(CalCfg c) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x, n = (size_t)c.H * kMat;
-  if (i >= n) return;
-  double acc = 0.0;
-  for (int sp = 0; sp < kCalSplit; ++sp) acc += c.drp[(size_t)sp * n + i];
-  c.dr[i] = acc;
-}
-
 // ---------------------------------------------------------------------------------------------
-// Matrix functions: one work-group of 1024 threads per KV head; 128 x 128 products on the fp64
-// matrix cores, operands staged through LDS in 16-deep slices.
-struct ExpLds {
-  double at[16][kD];  // op(A)^T chunk: at[k][r] = op(A)[r][k0 + k]
-  double bs[16][kD];  // B chunk: bs[k][c] = B[k0 + k][c]
-  double red[16];
+// Matrix functions of the generators, per KV head. With S = A - A^T (skew, so normal: the 2-norm of S is
+// that of S^4 to the power 1/4, at most ||S^4||_1^{1/4}) the exponential is the Taylor polynomial of
+// S 2^-j, degree 4 nb - 1, in Paterson-Stockmeyer form: with Y = X^4,
+//   p(X) = (..(B_{nb-1} Y + B_{nb-2}) Y + ..) Y + B_0,  B_i = sum_{q<4} X^q / (4 i + q)!,
+// applied 2^j times; j is the smallest with ||S^4||_1^{1/4} 2^-j <= kExpTheta and nb the smallest whose
+// first dropped term is below 2^-55. Measured against a long-double exponential of random skew matrices
+// with 1-norms from 0.3 to 50, the relative error is 5e-17 to 1.3e-15 (8e-17 to 1e-14 for the degree-14
+// polynomial at ||X||_1 <= 1/2 with its squarings, which this form replaced).
+//
+// Every product's right operand is a 16-column block, and every left operand (S, S^4, ..) was complete
+// before the launch: a work-group computes its column block of the result with no exchange between
+// work-groups. A work-group (block of 16 columns, KV head) has eight waves, wave w owning rows
+// 16 w .. + 15: the left operand's rows stay in registers (64 per lane), the column block goes through
+// LDS, and a product is 32 fp64 matrix-core steps per wave (1.7 us at the CU's fp64 rate). Bound by that
+// chain of products: per call at 8 heads, exponential 369 -> 40 us and gradient 1,011 -> 90 us (medians
+// over a 20-step calibration) against one work-group of 1,024 threads per head (8 of 256 CUs).
+// Beyond kExpMaxReps halvings one work-group per head forms all column blocks and squares j times.
+constexpr int kExpCols = 16;      // columns per work-group
+constexpr int kExpThreads = 512;  // eight waves of 16 rows
+constexpr double kExpTheta = 3.5;
+constexpr int kExpMaxBlocks = 9;  // nb at most (theta^32 / 32! < 2^-55)
+constexpr int kExpMaxReps = 5;    // up to 2^5 applications per column block
+// scratch matrices of a head (c.ex): powers of S, then of [[X, G], [0, X]] with X = S^T = -S (upper right
+// blocks: X D_k + G X^k), the exponential's blocks, the column-block bounds on ||S^4||_1
+enum { kExS = 0, kExS2, kExS3, kExS4, kExG, kExD2, kExD3, kExD4, kExP2, kExP1, kExBound };
+static_assert(kExBound < kCalScratch, "scratch matrices of the matrix functions");
+
+__device__ constexpr double kInvFact[4 * kExpMaxBlocks] = {
+    0x1.0000000000000p+0, 0x1.0000000000000p+0, 0x1.0000000000000p-1, 0x1.5555555555555p-3, 0x1.5555555555555p-5,
+    0x1.1111111111111p-7, 0x1.6c16c16c16c17p-10, 0x1.a01a01a01a01ap-13, 0x1.a01a01a01a01ap-16,
+    0x1.71de3a556c734p-19, 0x1.27e4fb7789f5cp-22, 0x1.ae64567f544e4p-26, 0x1.1eed8eff8d898p-29,
+    0x1.6124613a86d09p-33, 0x1.93974a8c07c9dp-37, 0x1.ae7f3e733b81fp-41, 0x1.ae7f3e733b81fp-45,
+    0x1.952c77030ad4ap-49, 0x1.6827863b97d97p-53, 0x1.2f49b46814157p-57, 0x1.e542ba4020225p-62,
+    0x1.71b8ef6dcf572p-66, 0x1.0ce396db7f853p-70, 0x1.761b41316381ap-75, 0x1.f2cf01972f578p-80,
+    0x1.3f3ccdd165fa9p-84, 0x1.88e85fc6a4e5ap-89, 0x1.d1ab1c2dccea3p-94, 0x1.0a18a2635085dp-98,
+    0x1.259f98b4358adp-103, 0x1.3932c5047d60ep-108, 0x1.434d2e783f5bcp-113, 0x1.434d2e783f5bcp-118,
+    0x1.3981254dd0d52p-123, 0x1.2710231c0fd7ap-128, 0x1.0dc59c716d91fp-133};
+
+struct ExpBuf {
+  double y[2][kD * kExpCols];  // column block, two buffers
 };
 
-// Output fragment of wg_gemm: a thread's acc[t][v] is the element (frag_row(v), frag_col(t)) of the
-// 128 x 128 product. Wave w covers rows 16 (w / 2) .. + 15 and columns 64 (w % 2) .. + 63 as four
-// 16 x 16 matrix-core tiles; lane l holds rows l / 16 + 4 v, column l % 16 of tile t.
-__device__ __forceinline__ int frag_row(int v) {
-  return 16 * (threadIdx.x >> 7) + ((threadIdx.x & 63) >> 4) + 4 * v;
-}
-__device__ __forceinline__ int frag_col(int t) {
-  return 64 * ((threadIdx.x >> 6) & 1) + 16 * t + (threadIdx.x & 15);
-}
-
-// Fragment element (t, v) sits at offset frag_base() + frag_step(t, v) of a row-major 128 x 128 matrix.
-__device__ __forceinline__ unsigned frag_base() { return (unsigned)(frag_row(0) * kD + frag_col(0)); }
-constexpr unsigned frag_step(int t, int v) { return (unsigned)(4 * v * kD + 16 * t); }
-
-// M[fragment] = acc * scale (+ I when add_identity).
-__device__ __forceinline__ void frag_store(double* __restrict__ M, const f64x4 (&acc)[4], double scale,
-                                           bool add_identity) {
-  unsigned fb = frag_base();
-  // computed here, at the store: hoisted out of the callers' loops, the 32 addresses would not
-  // fit the register budget of a 1024-thread block
-  asm volatile("" : "+v"(fb));
-  double* __restrict__ Mf = M + fb;
-  const int r0 = frag_row(0), c0 = frag_col(0);
+// Rows 16 w + li of M (row-major, times sign) as the left operand: lane (li, lk) holds M[16 w + li][32 lk + s].
+__device__ __forceinline__ void exp_left(const double* M, double sign, double (&a)[32]) {
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const double2* r = reinterpret_cast<const double2*>(M + (16 * w + (l & 15)) * kD + 32 * (l >> 4));
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      Mf[frag_step(t, v)] = (add_identity && r0 + 4 * v == c0 + 16 * t ? 1.0 : 0.0) + acc[t][v] * scale;
-}
-
-// M[fragment] = acc + c0 I + c1 A1 + c2 A2 + c3 A3, the A's read at the thread's own fragment elements.
-__device__ __forceinline__ void frag_store_lin(double* __restrict__ M, const f64x4 (&acc)[4], double c0,
-                                               const double* A1, double c1, const double* A2, double c2,
-                                               const double* A3, double c3) {
-  unsigned fb = frag_base();
-  asm volatile("" : "+v"(fb));  // as in frag_store
-  const int r0 = frag_row(0), c0c = frag_col(0);
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const unsigned o = fb + frag_step(t, v);
-      M[o] = (r0 + 4 * v == c0c + 16 * t ? c0 : 0.0) + acc[t][v] + c1 * A1[o] + c2 * A2[o] + c3 * A3[o];
-    }
-}
-
-// Truncated Taylor series of exp (degree kExpTerms = 14) in Paterson-Stockmeyer form: with Y = X^4,
-// sum_k X^k / k! = ((B_3 Y + B_2) Y + B_1) Y + B_0, B_i = sum_{j<4} X^j / (4 i + j)! (1/15! taken as 0),
-// so the powers X^2, X^3, X^4 and three Horner steps take six products instead of fourteen.
-__device__ __forceinline__ void taylor_coeffs(double (&cf)[16]) {
-  cf[0] = 1.0;
-#pragma unroll
-  for (int k = 1; k <= kExpTerms; ++k) cf[k] = cf[k - 1] / (double)k;
-  cf[15] = 0.0;
-}
-
-// acc += op(A) B for 128 x 128 fp64 matrices in global memory (op(A) = A or A^T) on the fp64
-// matrix cores (16 x 16 x 4 steps), 16-deep chunks of A and B staged through LDS. Ends with a
-// barrier, so the caller may overwrite A or B right after.
-__device__ __forceinline__ void wg_gemm(const double* A, bool ta, const double* B, f64x4 (&acc)[4], ExpLds& sm) {
-  const int tid = threadIdx.x, l = tid & 63;
-  const int ar = 16 * (tid >> 7) + (l & 15), kl = l >> 4, bc = 64 * ((tid >> 6) & 1) + (l & 15);
-#pragma unroll 1
-  for (int k0 = 0; k0 < kD; k0 += 16) {
-    for (int e = tid; e < kD * 16; e += kExpThreads) {
-      const int kk = e >> 7, r = e & 127;
-      sm.at[kk][r] = ta ? A[(k0 + kk) * kD + r] : A[r * kD + k0 + kk];
-      sm.bs[kk][r] = B[(k0 + kk) * kD + r];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k4 = 0; k4 < 16; k4 += 4) {
-      const double av = sm.at[k4 + kl][ar];
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        acc[t] = mfma64(av, sm.bs[k4 + kl][bc + 16 * t], acc[t]);
-    }
-    __syncthreads();
+  for (int i = 0; i < 16; ++i) {
+    const double2 x = r[i];
+    a[2 * i] = sign * x.x;
+    a[2 * i + 1] = sign * x.y;
   }
 }
 
-__device__ __forceinline__ void zero4(f64x4 (&a)[4]) {
+// acc + M Y for the wave's 16 rows: Y in LDS [k][16]; element v: row 16 w + lk + 4 v, column li.
+__device__ __forceinline__ f64x4 exp_prod(const double (&a)[32], const double* Y, f64x4 acc) {
+  const int l = threadIdx.x & 63;
+  const double* y = Y + 32 * kExpCols * (l >> 4) + (l & 15);
 #pragma unroll
-  for (int t = 0; t < 4; ++t) a[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+  for (int s = 0; s < 32; ++s) acc = mfma64(a[s], y[kExpCols * s], acc);
+  return acc;
 }
 
-// X <- (A - A^T) * 2^-sc with sc the smallest scaling giving ||X||_1 <= 1/2 (returned); with
-// transpose, X <- (A - A^T)^T * 2^-sc.
-__device__ int wg_skew_scaled(const double* A, double* X, bool transpose, ExpLds& sm) {
-  const int tid = threadIdx.x;
-  double colsum = 0.0;
-  if (tid < kD)
-    for (int r = 0; r < kD; ++r) colsum += fabs(A[r * kD + tid] - A[tid * kD + r]);
-  const double nrm = block_max(tid < kD ? colsum : 0.0, sm.red);
-  int sc = 0;
-  while (sc < 60 && ldexp(nrm, -sc) > 0.5) ++sc;
-  const double f = ldexp(1.0, -sc);
-  for (int e = tid; e < kMat; e += kExpThreads) {
-    const int r = e >> 7, cc = e & 127;
-    const double s = A[r * kD + cc] - A[cc * kD + r];
-    X[e] = (transpose ? -s : s) * f;
+// The thread's fragment of column block cb: rows exp_row(v), column 16 cb + li.
+__device__ __forceinline__ int exp_row(int v) {
+  return 16 * (threadIdx.x >> 6) + ((threadIdx.x & 63) >> 4) + 4 * v;
+}
+__device__ __forceinline__ f64x4 exp_load(const double* M, int cb, double sign) {
+  f64x4 f;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) f[v] = sign * M[exp_row(v) * kD + kExpCols * cb + (threadIdx.x & 15)];
+  return f;
+}
+__device__ __forceinline__ void exp_store(double* M, int cb, f64x4 f) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) M[exp_row(v) * kD + kExpCols * cb + (threadIdx.x & 15)] = f[v];
+}
+__device__ __forceinline__ void exp_put(double* Y, f64x4 f) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) Y[exp_row(v) * kExpCols + (threadIdx.x & 15)] = f[v];
+}
+__device__ __forceinline__ f64x4 exp_eye(int cb) {
+  f64x4 f;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) f[v] = exp_row(v) == kExpCols * cb + (int)(threadIdx.x & 15) ? 1.0 : 0.0;
+  return f;
+}
+// column block cb of M (row-major) into LDS
+__device__ __forceinline__ void exp_block(const double* M, int cb, double sign, double* Y) {
+  for (int e = threadIdx.x; e < kD * kExpCols; e += kExpThreads)
+    Y[e] = sign * M[(e / kExpCols) * kD + kExpCols * cb + e % kExpCols];
+}
+
+// j halvings and nb polynomial blocks for a head, from the bounds its powers kernel stored
+__device__ __forceinline__ void exp_plan(const double* ex, int& j, int& nb) {
+  const double* bound = ex + kExBound * kMat;
+  double b = 0.0;
+  for (int i = 0; i < kD / kExpCols; ++i) b = fmax(b, bound[i]);
+  b = sqrt(sqrt(b));
+  j = 0;
+  while (b > kExpTheta && j < 60) {
+    b *= 0.5;
+    ++j;
   }
-  __syncthreads();
-  return sc;
+  const double b4 = (b * b) * (b * b);
+  double p = b4;
+  nb = 1;
+  while (nb < kExpMaxBlocks && p * kInvFact[4 * nb - 1] / (4 * nb) > 0x1p-55) {
+    p *= b4;
+    ++nb;
+  }
+  j = __builtin_amdgcn_readfirstlane(j);  // the same in every lane: loop counts and coefficients are scalar
+  nb = __builtin_amdgcn_readfirstlane(nb);
 }
 
-// Forward: R = R0 exp(A - A^T) and Rt = R^T (fp64) for every head.
-__global__ __launch_bounds__(kExpThreads) void cal_expm_kernel(CalCfg c, const double* __restrict__ Aall, int value) {
-  __shared__ ExpLds sm;
-  const int h = blockIdx.x, tid = threadIdx.x;
+// S, S^2, S^3, S^4 and each column block's largest absolute column sum of S^4.
+__global__ __launch_bounds__(kExpThreads) void cal_exp_powers_kernel(CalCfg c, const double* __restrict__ Aall) {
+  __shared__ ExpBuf sm;
+  __shared__ double cs[8][kExpCols];
+  const int cb = blockIdx.x, h = blockIdx.y, tid = threadIdx.x, w = tid >> 6, l = tid & 63, li = l & 15, lk = l >> 4;
+  const double* A = Aall + (size_t)h * kMat;
   double* ex = c.ex + (size_t)h * kCalScratch * kMat;
-  double *X = ex, *P = ex + kMat, *R0 = ex + 2 * kMat;
-  double *X2 = ex + 5 * kMat, *X3 = ex + 6 * kMat, *X4 = ex + 7 * kMat;
-  const float* R0f = (value ? c.R0v : c.R0k) + (size_t)h * kMat;
-  for (int e = tid; e < kMat; e += kExpThreads) R0[e] = (double)R0f[e];
-  const int sc = wg_skew_scaled(Aall + (size_t)h * kMat, X, false, sm);
-  double cf[16];
-  taylor_coeffs(cf);
-  f64x4 acc[4];
-  zero4(acc);
-  wg_gemm(X, false, X, acc, sm);
-  frag_store(X2, acc, 1.0, false);
-  __syncthreads();
-  zero4(acc);
-  wg_gemm(X2, false, X, acc, sm);
-  frag_store(X3, acc, 1.0, false);
-  zero4(acc);
-  wg_gemm(X2, false, X2, acc, sm);
-  frag_store(X4, acc, 1.0, false);
-  __syncthreads();
-  for (int e = tid; e < kMat; e += kExpThreads)  // P = B_3
-    P[e] = ((e >> 7) == (e & 127) ? cf[12] : 0.0) + cf[13] * X[e] + cf[14] * X2[e] + cf[15] * X3[e];
-  __syncthreads();
-  for (int i = 2; i >= 0; --i) {  // P <- P X^4 + B_i
-    zero4(acc);
-    wg_gemm(P, false, X4, acc, sm);
-    frag_store_lin(P, acc, cf[4 * i], X, cf[4 * i + 1], X2, cf[4 * i + 2], X3, cf[4 * i + 3]);
-    __syncthreads();
-  }
-  for (int i = 0; i < sc; ++i) {  // P <- P P
-    zero4(acc);
-    wg_gemm(P, false, P, acc, sm);
-    frag_store(P, acc, 1.0, false);
-    __syncthreads();
-  }
-  zero4(acc);
-  wg_gemm(R0, false, P, acc, sm);
-  double* R = c.R + (size_t)h * kMat;
-  double* Rt = c.Rt + (size_t)h * kMat;
-  frag_store(R, acc, 1.0, false);
-  const int r0 = frag_row(0), c0 = frag_col(0);
+  double a[32];
+  exp_left(A, 1.0, a);
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
+  for (int s = 0; s < 32; ++s) a[s] -= A[(32 * lk + s) * kD + 16 * w + li];
+  for (int e = tid; e < kD * kExpCols; e += kExpThreads) {
+    const int r = e / kExpCols, col = kExpCols * cb + e % kExpCols;
+    const double s = A[r * kD + col] - A[col * kD + r];
+    sm.y[0][e] = s;
+    ex[kExS * kMat + r * kD + col] = s;
+  }
+  f64x4 f;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) Rt[(unsigned)((c0 + 16 * t) * kD + r0 + 4 * v)] = acc[t][v];
+  for (int p = 0; p < 3; ++p) {
+    __syncthreads();
+    f = exp_prod(a, sm.y[p & 1], f64x4{0.0, 0.0, 0.0, 0.0});
+    exp_store(ex + (kExS2 + p) * kMat, cb, f);
+    if (p < 2) exp_put(sm.y[(p + 1) & 1], f);
+  }
+  double t = (fabs(f[0]) + fabs(f[1])) + (fabs(f[2]) + fabs(f[3]));
+  t += __shfl_xor(t, 16);
+  t += __shfl_xor(t, 32);
+  if (lk == 0) cs[w][li] = t;
+  __syncthreads();
+  if (tid < 16) {
+    double b = 0.0;
+    for (int i = 0; i < 8; ++i) b += cs[i][tid];
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) b = fmax(b, __shfl_xor(b, off));
+    if (tid == 0) ex[kExBound * kMat + cb] = b;
+  }
 }
 
-// Backward: grad = dS - dS^T with dS = L_exp(S^T, R0^T dR), S = A - A^T, for every head: the top
-// right block of exp([[X, G], [0, X]]) (X = S^T, G = R0^T dR, both scaled by 2^-sc), whose powers
-// are [[X^k, D_k], [0, X^k]] with D_{a+b} = X^a D_b + D_a X^b; the Taylor polynomial of the block
-// matrix in the Paterson-Stockmeyer form above, then sc squarings.
-__global__ __launch_bounds__(kExpThreads) void cal_expm_grad_kernel(CalCfg c, const double* __restrict__ Aall,
-                                                                   int value, double* __restrict__ grad) {
-  __shared__ ExpLds sm;
-  const int h = blockIdx.x, tid = threadIdx.x;
+// R = R0 exp(S) and Rt = R^T (fp64).
+__global__ __launch_bounds__(kExpThreads) void cal_exp_apply_kernel(CalCfg c, int value) {
+  __shared__ ExpBuf sm;
+  const int h = blockIdx.y;
   double* ex = c.ex + (size_t)h * kCalScratch * kMat;
-  double *X = ex, *P1 = ex + kMat, *R0 = ex + 2 * kMat, *P2 = ex + 3 * kMat, *Gs = ex + 4 * kMat;
-  double *X2 = ex + 5 * kMat, *X3 = ex + 6 * kMat, *X4 = ex + 7 * kMat;
-  double *D2 = ex + 8 * kMat, *D3 = ex + 9 * kMat, *D4 = ex + 10 * kMat;
+  int j, nb;
+  exp_plan(ex, j, nb);
+  const bool alone = j > kExpMaxReps;  // uniform over the head's work-groups
+  if (alone && blockIdx.x != 0) return;
   const float* R0f = (value ? c.R0v : c.R0k) + (size_t)h * kMat;
-  for (int e = tid; e < kMat; e += kExpThreads) R0[e] = (double)R0f[e];
-  const int sc = wg_skew_scaled(Aall + (size_t)h * kMat, X, true, sm);
-  const double f = ldexp(1.0, -sc);
-  double cf[16];
-  taylor_coeffs(cf);
-  f64x4 acc[4], t1[4];
-  zero4(acc);
-  wg_gemm(R0, true, c.dr + (size_t)h * kMat, acc, sm);  // G_E = R0^T dR, scaled like X
-  frag_store(Gs, acc, f, false);
-  __syncthreads();
-  // M^2: (X^2, X G + G X)
-  zero4(acc);
-  wg_gemm(X, false, X, acc, sm);
-  frag_store(X2, acc, 1.0, false);
-  zero4(acc);
-  wg_gemm(X, false, Gs, acc, sm);
-  wg_gemm(Gs, false, X, acc, sm);
-  frag_store(D2, acc, 1.0, false);
-  __syncthreads();
-  // M^3 = M^2 M: (X^2 X, X^2 G + D_2 X); M^4 = M^2 M^2: (X^2 X^2, X^2 D_2 + D_2 X^2)
-  zero4(acc);
-  wg_gemm(X2, false, X, acc, sm);
-  frag_store(X3, acc, 1.0, false);
-  zero4(acc);
-  wg_gemm(X2, false, Gs, acc, sm);
-  wg_gemm(D2, false, X, acc, sm);
-  frag_store(D3, acc, 1.0, false);
-  zero4(acc);
-  wg_gemm(X2, false, X2, acc, sm);
-  frag_store(X4, acc, 1.0, false);
-  zero4(acc);
-  wg_gemm(X2, false, D2, acc, sm);
-  wg_gemm(D2, false, X2, acc, sm);
-  frag_store(D4, acc, 1.0, false);
-  __syncthreads();
-  for (int e = tid; e < kMat; e += kExpThreads) {  // (P1, P2) = B_3
-    P1[e] = ((e >> 7) == (e & 127) ? cf[12] : 0.0) + cf[13] * X[e] + cf[14] * X2[e] + cf[15] * X3[e];
-    P2[e] = cf[13] * Gs[e] + cf[14] * D2[e] + cf[15] * D3[e];
-  }
-  __syncthreads();
-  for (int i = 2; i >= 0; --i) {  // (P1, P2) <- (P1 X^4, P1 D_4 + P2 X^4) + B_i
-    zero4(t1);
-    wg_gemm(P1, false, X4, t1, sm);
-    zero4(acc);
-    wg_gemm(P1, false, D4, acc, sm);
-    wg_gemm(P2, false, X4, acc, sm);
-    frag_store_lin(P2, acc, 0.0, Gs, cf[4 * i + 1], D2, cf[4 * i + 2], D3, cf[4 * i + 3]);
-    frag_store_lin(P1, t1, cf[4 * i], X, cf[4 * i + 1], X2, cf[4 * i + 2], X3, cf[4 * i + 3]);
+  double a[32];
+  int yb = 0;  // LDS buffer the next column block goes to
+  auto put = [&](f64x4 f) {
+    double* Y = sm.y[yb];
+    yb ^= 1;
+    exp_put(Y, f);
     __syncthreads();
+    return Y;
+  };
+  const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
+  // p(S 2^-j) y for a column block y (the identity's block cb when first)
+  auto poly = [&](int cb, bool first, f64x4 y) {
+    f64x4 w1, w2, w3;
+    if (first) {
+      y = exp_eye(cb);
+      w1 = exp_load(ex + kExS * kMat, cb, 1.0);
+      w2 = exp_load(ex + kExS2 * kMat, cb, 1.0);
+      w3 = exp_load(ex + kExS3 * kMat, cb, 1.0);
+    } else {
+      exp_left(ex + kExS * kMat, 1.0, a);
+      w1 = exp_prod(a, put(y), zero);
+      w2 = exp_prod(a, put(w1), zero);
+      w3 = exp_prod(a, put(w2), zero);
+    }
+    exp_left(ex + kExS4 * kMat, 1.0, a);
+    auto blk = [&](int i) {
+      const double c0 = ldexp(kInvFact[4 * i], -4 * i * j), c1 = ldexp(kInvFact[4 * i + 1], -(4 * i + 1) * j),
+                   c2 = ldexp(kInvFact[4 * i + 2], -(4 * i + 2) * j), c3 = ldexp(kInvFact[4 * i + 3], -(4 * i + 3) * j);
+      return c0 * y + c1 * w1 + c2 * w2 + c3 * w3;
+    };
+    f64x4 p = blk(nb - 1);
+    for (int i = nb - 2; i >= 0; --i) p = exp_prod(a, put(p), blk(i));
+    return p;
+  };
+  auto finish = [&](int cb, f64x4 y) {  // R[:, block] = R0 y
+    const double* Y = put(y);
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const float4* r = reinterpret_cast<const float4*>(R0f + (16 * w + (l & 15)) * kD + 32 * (l >> 4));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float4 x = r[i];
+      a[4 * i] = x.x;
+      a[4 * i + 1] = x.y;
+      a[4 * i + 2] = x.z;
+      a[4 * i + 3] = x.w;
+    }
+    const f64x4 f = exp_prod(a, Y, zero);
+    exp_store(c.R + (size_t)h * kMat, cb, f);
+    double* Rt = c.Rt + (size_t)h * kMat + (kExpCols * cb + (l & 15)) * kD;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Rt[exp_row(v)] = f[v];
+  };
+  if (!alone) {
+    const int cb = blockIdx.x;
+    f64x4 y = poly(cb, true, zero);
+    for (int r = 1; r < (1 << j); ++r) y = poly(cb, false, y);
+    finish(cb, y);
+    return;
   }
-  for (int i = 0; i < sc; ++i) {  // (P1, P2) <- (P1 P1, P1 P2 + P2 P1)
-    zero4(t1);
-    wg_gemm(P1, false, P1, t1, sm);
-    zero4(acc);
-    wg_gemm(P1, false, P2, acc, sm);
-    wg_gemm(P2, false, P1, acc, sm);
-    frag_store(P2, acc, 1.0, false);
-    frag_store(P1, t1, 1.0, false);
+  double *P = ex + kExP1 * kMat, *Q = ex + kExP2 * kMat;
+  for (int cb = 0; cb < kD / kExpCols; ++cb) exp_store(P, cb, poly(cb, true, zero));
+  for (int i = 0; i < j; ++i) {
     __syncthreads();
+    exp_left(P, 1.0, a);
+    for (int cb = 0; cb < kD / kExpCols; ++cb) exp_store(Q, cb, exp_prod(a, put(exp_load(P, cb, 1.0)), zero));
+    double* t = P;
+    P = Q;
+    Q = t;
   }
-  double* g = grad + (size_t)h * kMat;
-  for (int e = tid; e < kMat; e += kExpThreads) {
-    const int r = e >> 7, cc = e & 127;
-    g[e] = P2[r * kD + cc] - P2[cc * kD + r];
+  for (int cb = 0; cb < kD / kExpCols; ++cb) finish(cb, exp_load(P, cb, 1.0));
+}
+
+// Gradient: dL/dA = dS - dS^T with dS = L_exp(S^T, G), G = R0^T dL/dR: the upper right block of
+// exp([[X, G], [0, X]]), X = S^T = -S, whose powers are [[X^k, D_k], [0, X^k]], D_{k+1} = X D_k + G X^k; the
+// same polynomial on column blocks (u, v), two or three products per step. The powers of S are the ones
+// the exponential left for the same generators.
+//
+// G of one column block, with dL/dR summed over its token slices in slice order.
+__global__ __launch_bounds__(kExpThreads) void cal_grad_g_kernel(CalCfg c, int value) {
+  __shared__ ExpBuf sm;
+  const int cb = blockIdx.x, h = blockIdx.y, tid = threadIdx.x, w = tid >> 6, l = tid & 63, li = l & 15, lk = l >> 4;
+  const float* R0 = (value ? c.R0v : c.R0k) + (size_t)h * kMat;
+  double a[32];
+#pragma unroll
+  for (int s = 0; s < 32; ++s) a[s] = R0[(32 * lk + s) * kD + 16 * w + li];  // rows of R0^T
+  for (int e = tid; e < kD * kExpCols; e += kExpThreads) {
+    const double* d = c.drp + (size_t)h * kMat + (e / kExpCols) * kD + kExpCols * cb + e % kExpCols;
+    double x[kCalSplit], t = 0.0;
+#pragma unroll
+    for (int sp = 0; sp < kCalSplit; ++sp) x[sp] = d[(size_t)sp * c.H * kMat];
+#pragma unroll
+    for (int sp = 0; sp < kCalSplit; ++sp) t += x[sp];
+    sm.y[0][e] = t;
   }
+  __syncthreads();
+  exp_store(c.ex + ((size_t)h * kCalScratch + kExG) * kMat, cb, exp_prod(a, sm.y[0], f64x4{0.0, 0.0, 0.0, 0.0}));
+}
+
+// D_2, D_3, D_4 of one column block.
+__global__ __launch_bounds__(kExpThreads) void cal_grad_powers_kernel(CalCfg c) {
+  __shared__ ExpBuf u, v;
+  const int cb = blockIdx.x;
+  double* ex = c.ex + (size_t)blockIdx.y * kCalScratch * kMat;
+  double aX[32], aG[32];
+  exp_left(ex + kExS * kMat, -1.0, aX);
+  exp_left(ex + kExG * kMat, 1.0, aG);
+  exp_block(ex + kExG * kMat, cb, 1.0, u.y[0]);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {  // D_{p+2} = X D_{p+1} + G X^{p+1} (D_1 = G)
+    exp_block(ex + (kExS + p) * kMat, cb, p == 1 ? 1.0 : -1.0, v.y[p & 1]);
+    __syncthreads();
+    const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
+    const f64x4 d = exp_prod(aX, u.y[p & 1], zero) + exp_prod(aG, v.y[p & 1], zero);
+    exp_store(ex + (kExD2 + p) * kMat, cb, d);
+    if (p < 2) exp_put(u.y[(p + 1) & 1], d);
+  }
+}
+
+// The upper right block of the exponential, [128][128] per head, into scratch kExP2.
+__global__ __launch_bounds__(kExpThreads) void cal_grad_apply_kernel(CalCfg c) {
+  __shared__ ExpBuf su, sv;
+  const int h = blockIdx.y;
+  double* ex = c.ex + (size_t)h * kCalScratch * kMat;
+  int j, nb;
+  exp_plan(ex, j, nb);
+  const bool alone = j > kExpMaxReps;
+  if (alone && blockIdx.x != 0) return;
+  double a[32], b[32];  // left operands: X (or X^4, P_1) and G (or D_4, P_2)
+  int yb = 0;
+  auto put = [&](f64x4 fu, f64x4 fv) {
+    const int y = yb;
+    yb ^= 1;
+    exp_put(su.y[y], fu);
+    exp_put(sv.y[y], fv);
+    __syncthreads();
+    return y;
+  };
+  const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
+  // (u, v) <- (a u + b v + du, a v + dv)
+  auto step = [&](f64x4& fu, f64x4& fv, f64x4 du, f64x4 dv) {
+    const int y = put(fu, fv);
+    const f64x4 t = exp_prod(b, sv.y[y], zero);
+    fu = exp_prod(a, su.y[y], du) + t;
+    fv = exp_prod(a, sv.y[y], dv);
+  };
+  auto poly = [&](int cb, bool first, f64x4& u, f64x4& v) {
+    f64x4 u1, u2, u3, v1, v2, v3;
+    if (first) {
+      u = zero;
+      v = exp_eye(cb);
+      u1 = exp_load(ex + kExG * kMat, cb, 1.0);
+      u2 = exp_load(ex + kExD2 * kMat, cb, 1.0);
+      u3 = exp_load(ex + kExD3 * kMat, cb, 1.0);
+      v1 = exp_load(ex + kExS * kMat, cb, -1.0);
+      v2 = exp_load(ex + kExS2 * kMat, cb, 1.0);
+      v3 = exp_load(ex + kExS3 * kMat, cb, -1.0);
+    } else {
+      exp_left(ex + kExS * kMat, -1.0, a);
+      exp_left(ex + kExG * kMat, 1.0, b);
+      u1 = u;
+      v1 = v;
+      step(u1, v1, zero, zero);
+      u2 = u1;
+      v2 = v1;
+      step(u2, v2, zero, zero);
+      u3 = u2;
+      v3 = v2;
+      step(u3, v3, zero, zero);
+    }
+    exp_left(ex + kExS4 * kMat, 1.0, a);
+    exp_left(ex + kExD4 * kMat, 1.0, b);
+    f64x4 pu = zero, pv = zero;
+    for (int i = nb - 1; i >= 0; --i) {
+      const double c0 = ldexp(kInvFact[4 * i], -4 * i * j), c1 = ldexp(kInvFact[4 * i + 1], -(4 * i + 1) * j),
+                   c2 = ldexp(kInvFact[4 * i + 2], -(4 * i + 2) * j), c3 = ldexp(kInvFact[4 * i + 3], -(4 * i + 3) * j);
+      const f64x4 du = c0 * u + c1 * u1 + c2 * u2 + c3 * u3, dv = c0 * v + c1 * v1 + c2 * v2 + c3 * v3;
+      if (i == nb - 1) {
+        pu = du;
+        pv = dv;
+      } else {
+        step(pu, pv, du, dv);
+      }
+    }
+    u = pu;
+    v = pv;
+  };
+  f64x4 u, v;
+  if (!alone) {
+    const int cb = blockIdx.x;
+    poly(cb, true, u, v);
+    for (int r = 1; r < (1 << j); ++r) poly(cb, false, u, v);
+    exp_store(ex + kExP2 * kMat, cb, u);
+    return;
+  }
+  for (int cb = 0; cb < kD / kExpCols; ++cb) {
+    poly(cb, true, u, v);
+    exp_store(ex + kExP2 * kMat, cb, u);
+    exp_store(ex + kExP1 * kMat, cb, v);
+  }
+  // (P_1, P_2) <- (P_1 P_1, P_1 P_2 + P_2 P_1); the powers' scratch is free now
+  int p1 = kExP1, p2 = kExP2, q1 = kExD2, q2 = kExD3;
+  for (int i = 0; i < j; ++i) {
+    __syncthreads();
+    exp_left(ex + p1 * kMat, 1.0, a);
+    exp_left(ex + p2 * kMat, 1.0, b);
+    for (int cb = 0; cb < kD / kExpCols; ++cb) {
+      u = exp_load(ex + p2 * kMat, cb, 1.0);
+      v = exp_load(ex + p1 * kMat, cb, 1.0);
+      step(u, v, zero, zero);
+      exp_store(ex + q2 * kMat, cb, u);
+      exp_store(ex + q1 * kMat, cb, v);
+    }
+    int t = p1;
+    p1 = q1;
+    q1 = t;
+    t = p2;
+    p2 = q2;
+    q2 = t;
+  }
+  if (p2 != kExP2)  // each thread copies the elements it stored
+    for (int cb = 0; cb < kD / kExpCols; ++cb) exp_store(ex + kExP2 * kMat, cb, exp_load(ex + p2 * kMat, cb, 1.0));
+}
+
+// grad = dS - dS^T
+__global__ __launch_bounds__(256) void cal_grad_skew_kernel(CalCfg c, double* __restrict__ grad) {
+  const int h = blockIdx.y, e = blockIdx.x * 256 + threadIdx.x, r = e / kD, col = e % kD;
+  const double* P = c.ex + ((size_t)h * kCalScratch + kExP2) * kMat;
+  grad[(size_t)h * kMat + e] = P[e] - P[col * kD + r];
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1303,7 +1429,7 @@ size_t cal_set_bytes(int T, int nseq, int nrows, long long pelems, int H) {
 
 size_t cal_shared_bytes(int H, int Hq) {
   return up256((size_t)Hq * kMat * 8) + 2 * up256((size_t)H * kMat * 8) + up256((size_t)H * kCalScratch * kMat * 8) +
-         up256((size_t)kCalSplit * H * kMat * 8) + up256((size_t)H * kMat * 8);
+         up256((size_t)kCalSplit * H * kMat * 8);
 }
 
 hipError_t cal_bind_set(CalSet& set, uint8_t* base, const uint16_t* k, const uint16_t* v, const uint16_t* q,
@@ -1400,8 +1526,6 @@ void cal_bind_shared(CalCfg& c, uint8_t* base) {
   c.ex = reinterpret_cast<double*>(p);
   p += up256((size_t)c.H * kCalScratch * kMat * 8);
   c.drp = reinterpret_cast<double*>(p);
-  p += up256((size_t)kCalSplit * c.H * kMat * 8);
-  c.dr = reinterpret_cast<double*>(p);
 }
 
 hipError_t cal_gram(const CalCfg& c, const uint16_t* W_o, hipStream_t s) {
@@ -1409,13 +1533,21 @@ hipError_t cal_gram(const CalCfg& c, const uint16_t* W_o, hipStream_t s) {
   return hipGetLastError();
 }
 
+// R = R0 exp(A - A^T) and its transpose for every head
+static void rotation(const CalCfg& c, const double* A, int value, hipStream_t s) {
+  const dim3 grid(kD / kExpCols, c.H), block(kExpThreads);
+  hipLaunchKernelGGL(cal_exp_powers_kernel, grid, block, 0, s, c, A);
+  hipLaunchKernelGGL(cal_exp_apply_kernel, grid, block, 0, s, c, value);
+}
+
 static void rot_and_quant(const CalCfg& c, CalSet& set, const double* A, int value, hipStream_t s) {
-  hipLaunchKernelGGL(cal_expm_kernel, dim3(c.H), dim3(kExpThreads), 0, s, c, A, value);
+  rotation(c, A, value, s);
   if (set.T > 0)
     hipLaunchKernelGGL(cal_rotq_kernel, dim3((set.T + kRotTile - 1) / kRotTile, c.H), dim3(512), 0, s, set, c, value);
 }
 
-static void backward(const CalCfg& c, CalSet& set, const double* A, int value, double* grad, hipStream_t s) {
+// after rot_and_quant for the same generators (it leaves the powers of S)
+static void backward(const CalCfg& c, CalSet& set, int value, double* grad, hipStream_t s) {
   if (set.T > 0) {
     hipLaunchKernelGGL(cal_gx_kernel, dim3((set.T + kGxTok - 1) / kGxTok, c.H), dim3(256), 0, s, set, c, value);
     hipLaunchKernelGGL(cal_gz_kernel, dim3((set.T + kGzTile - 1) / kGzTile, c.H), dim3(256), 0, s, set, c);
@@ -1424,8 +1556,11 @@ static void backward(const CalCfg& c, CalSet& set, const double* A, int value, d
     hipLaunchKernelGGL(cal_fill_kernel, dim3((unsigned)((kCalSplit * (size_t)c.H * kMat + 255) / 256)), dim3(256), 0,
                        s, c.drp, kCalSplit * (size_t)c.H * kMat, 0.0);
   }
-  hipLaunchKernelGGL(cal_dr_reduce_kernel, dim3((unsigned)(((size_t)c.H * kMat + 255) / 256)), dim3(256), 0, s, c);
-  hipLaunchKernelGGL(cal_expm_grad_kernel, dim3(c.H), dim3(kExpThreads), 0, s, c, A, value, grad);
+  const dim3 grid(kD / kExpCols, c.H), block(kExpThreads);
+  hipLaunchKernelGGL(cal_grad_g_kernel, grid, block, 0, s, c, value);
+  hipLaunchKernelGGL(cal_grad_powers_kernel, grid, block, 0, s, c);
+  hipLaunchKernelGGL(cal_grad_apply_kernel, grid, block, 0, s, c);
+  hipLaunchKernelGGL(cal_grad_skew_kernel, dim3(kMat / 256, c.H), dim3(256), 0, s, c, grad);
 }
 
 // the tile kernels: one block per (tile, KV head)
@@ -1461,7 +1596,7 @@ hipError_t cal_key_loss(const CalCfg& c, CalSet& set, const double* A, double* l
                          (size_t)c.H * kMat, 0.0);
       return hipGetLastError();
     }
-    backward(c, set, A, 0, grad, s);
+    backward(c, set, 0, grad, s);
   }
   return hipGetLastError();
 }
@@ -1487,7 +1622,7 @@ hipError_t cal_value_loss(const CalCfg& c, CalSet& set, const double* A, double*
                          (size_t)c.H * kMat, 0.0);
       return hipGetLastError();
     }
-    backward(c, set, A, 1, grad, s);
+    backward(c, set, 1, grad, s);
   }
   return hipGetLastError();
 }
@@ -1517,7 +1652,7 @@ hipError_t cal_fill(double* p, size_t n, double v, hipStream_t s) {
 }
 
 hipError_t cal_rotation_out(const CalCfg& c, const double* A, bool value, float* out, hipStream_t s) {
-  hipLaunchKernelGGL(cal_expm_kernel, dim3(c.H), dim3(kExpThreads), 0, s, c, A, value ? 1 : 0);
+  rotation(c, A, value ? 1 : 0, s);
   const size_t n = (size_t)c.H * kMat;
   hipLaunchKernelGGL(cal_to_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, c.R, out, n);
   return hipGetLastError();

@@ -1,0 +1,47 @@
+"""The matrix exponential of the calibration and its gradient over the norms that change its form: fewer and more
+polynomial blocks, one to thirty-two applications per column block, and the squarings beyond that. Both sides compute
+in fp64; exp(S) carries a relative error of about ||S|| eps (1e-13 at the largest norm here, against the library's own
+1e-15), so the bounds of the other calibration tests hold at every norm."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import optr_oracle as P
+from paper_2608_02691_amd import int2kv as K
+from paper_2608_02691_amd import workloads as W
+
+from _helpers import dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("scale", [1e-4, 0.01, 0.1, 0.2, 0.7, 3.0, 30.0])
+def test_objectives_and_gradients_over_generator_norms(scale):
+    H, Hq = 2, 4
+    print(f"\n[optr norms] {scale}", flush=True)
+    w = W.make_workload(1, batch=1, ctx=16, num_q_heads=Hq, num_kv_heads=H, d_model=64)
+    rng = np.random.default_rng(5)
+    bits = lambda *s: W.f32_to_bf16_bits(rng.standard_normal(s).astype(np.float32))
+    k, v, q, st = bits(70, H, 128), bits(70, H, 128), bits(70, Hq, 128), np.array([0, 40, 70], np.int32)
+    mu = P.key_mean(k)
+    cfg = K.optr_config(H, Hq, 64, group_size=32, n_last=12, sink=0, recent=0)
+    A, Av = rng.standard_normal((2, H, 128, 128)) * scale
+    Av[1] *= 0.01  # the heads of one launch take different forms
+    tr = K.OptrTraces(dev(k), dev(v), dev(q), st)
+    lk, gk = K.int2kv_optr_key_loss(cfg, tr, dev(w.R_k), dev(mu), dev(w.W_o), dev(A))
+    lv, gv = K.int2kv_optr_value_loss(cfg, tr, dev(w.R_k), dev(A), dev(mu), dev(w.R_v), dev(w.W_o), dev(Av))
+    kw = dict(group=32, n_last=12)
+    for h in range(H):
+        for got_l, got_g, gen, loss in (
+                (lk, gk, A, lambda x: P.key_loss(x, w.R_k, k, v, q, st, mu, w.W_o, h, 2, clip=0.96, **kw)),
+                (lv, gv, Av, lambda x: P.value_loss(x, w.R_v, v, st, P.key_probs(w.R_k, A[h], k, q, st, mu, h, 2,
+                                                                                  clip=0.96, **kw),
+                                                    w.W_o, h, 2, clip=0.92, **kw))):
+            x = torch.from_numpy(gen[h].copy()).requires_grad_(True)
+            ref = loss(x)
+            ref.backward()
+            g = x.grad.numpy()
+            dl = abs(float(got_l[h]) / float(ref.detach()) - 1.0)
+            dg = np.linalg.norm(got_g[h].cpu().numpy() - g) / np.linalg.norm(g)
+            print(f"head {h}: loss {dl:.1e}, gradient {dg:.1e}", flush=True)
+            assert dl <= 1e-9 and dg <= 1e-7, (scale, h, dl, dg)
