@@ -743,7 +743,7 @@ static int optr_setup(const int2kv_optr_config* cfg, const int2kv_optr_traces* t
   g = make_cal_cfg(cfg, mu, R0_k, R0_v);
   cal_bind_shared(g, base);
   hipError_t e = cal_bind_set(set, base + L.shared, tr->k, tr->v, tr->q, tr->seq_starts, tr->num_seqs, g.H, g.gq,
-                              g.n_last, stream);
+                              g.n_last, g.sink, g.recent, stream);
   if (e == hipSuccess) e = cal_gram(g, W_o, stream);
   if (e == hipSuccess) e = cal_prepare_set(g, set, stream);
   state = base + L.shared + L.set_c;
@@ -792,10 +792,10 @@ int int2kv_optr_calibrate(const int2kv_optr_config* cfg, const int2kv_optr_trace
   cal_bind_shared(g, base);
   CalSet sc, sh;
   hipError_t e = cal_bind_set(sc, base + L.shared, calib->k, calib->v, calib->q, calib->seq_starts, calib->num_seqs,
-                              g.H, g.gq, g.n_last, stream);
+                              g.H, g.gq, g.n_last, g.sink, g.recent, stream);
   if (e == hipSuccess)
     e = cal_bind_set(sh, base + L.shared + L.set_c, heldout->k, heldout->v, heldout->q, heldout->seq_starts,
-                     heldout->num_seqs, g.H, g.gq, g.n_last, stream);
+                     heldout->num_seqs, g.H, g.gq, g.n_last, g.sink, g.recent, stream);
   if (e == hipSuccess) e = cal_gram(g, W_o, stream);
   if (e == hipSuccess) e = cal_prepare_set(g, sc, stream);
   if (e == hipSuccess) e = cal_prepare_set(g, sh, stream);

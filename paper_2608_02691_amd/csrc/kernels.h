@@ -187,7 +187,8 @@ struct CalSet {
   int4* tiles;                     // [ntiles]: (sequence, first row, rows, position of the first row)
   long long pelems;                // per KV head: sum over sequences of rows * len
   CalSeq* seqs;                    // [nseq]
-  int* row_seq;                    // [nrows]: sequence of each row
+  int nunits;                      // units of up to 16 consecutive tokens that some query reads from INT2
+  int4* units;                     // [nunits]: (first token, tokens, sequence, first token in its sequence)
   double *zhat, *xeff, *gx, *gz;   // [H, T, 128]: dequantized rotated rows, effective rows, gradients
   uint8_t* mask;                   // [H, T, 128]: straight-through mask
   double* pd;                      // [H, pelems]: key probabilities, then logit gradients, on the tokens
@@ -219,7 +220,8 @@ size_t cal_set_bytes(int T, int nseq, int nrows, long long pelems, int H);
 size_t cal_shared_bytes(int H, int Hq);
 // carves a set's buffers from base and uploads its sequence and row tables (host starts [nseq + 1])
 hipError_t cal_bind_set(CalSet& set, uint8_t* base, const uint16_t* k, const uint16_t* v, const uint16_t* q,
-                        const int32_t* starts_host, int nseq, int H, int gq, int n_last, hipStream_t s);
+                        const int32_t* starts_host, int nseq, int H, int gq, int n_last, int sink, int recent,
+                        hipStream_t s);
 void cal_bind_shared(CalCfg& c, uint8_t* base);
 hipError_t cal_gram(const CalCfg& c, const uint16_t* W_o, hipStream_t s);
 // loss[h] (device) of every KV head at generators A [H, 128, 128]; grad (may be null) receives dL/dA

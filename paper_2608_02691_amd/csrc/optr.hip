@@ -29,6 +29,7 @@ constexpr int kD = kHeadDim;
 constexpr int kMat = kD * kD;
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 // fp64 matrix-core step D += A B for 16 x 4 by 4 x 16 operands: lane l holds A[l % 16][l / 16] and
 // B[l / 16][l % 16]; D[l / 16 + 4 v][l % 16] is element v of its accumulator.
@@ -79,27 +80,42 @@ __device__ __forceinline__ void bf16x8_to_f64(uint4 u, double (&d)[8]) {
 // channels (eight 16-row tiles), N = the wave's 16 rows y (lane l holds row l % 16), K = the 128
 // input channels. The lane's B operand at step s is ya[s] = y[row][k(s)], k(4 q + d) = 32 (l / 16) +
 // 4 q + d (KMAP 0: each lane reads 32 contiguous channels of its row) or 16 q + 4 d + l / 16 (KMAP 1:
-// the channels this layout leaves in a lane, see below); Bm goes through Bs (LDS, 16 rows x
-// kBsStride) 16 rows at a time. Result element v of acc[ct]: channel 16 ct + l / 16 + 4 v of row
+// the channels this layout leaves in a lane, see below); Bm goes through Bs (LDS, kBsRows rows x
+// kBsStride) kBsRows rows at a time. Result element v of acc[ct]: channel 16 ct + l / 16 + 4 v of row
 // l % 16. Contains block barriers: every thread of the block calls it.
-constexpr int kBsStride = 132;  // doubles per staged row (lane groups l / 16 two banks apart)
+// The next kBsRows rows of Bm are fetched into registers while the matrix cores run on the staged ones.
+constexpr int kBsStride = 132;  // doubles per staged row
+constexpr int kBsRows = 32;     // rows staged at a time: 64 matrix-core steps per wave hide the next fetch
+constexpr int kMatThreads = 256;
 template <int KMAP>
 __device__ __forceinline__ void mat_t_rows(const double (&ya)[32], const double* __restrict__ Bm, double* Bs,
                                            f64x4 (&acc)[8]) {
   const int tid = threadIdx.x, l = tid & 63, li = l & 15, lk = l >> 4;
+  constexpr int kPer = kBsRows * kD / (2 * kMatThreads);  // 16-byte pieces per thread
+  f64x2 next[kPer];
+  auto fetch = [&](int q) {
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {  // unrolled: ya is indexed by q
+    for (int u = 0; u < kPer; ++u) {
+      const int e = tid + kMatThreads * u, rr = e / (kD / 2), col = 2 * (e % (kD / 2));
+      const int krow = KMAP == 0 ? 32 * (rr >> 3) + 8 * q + (rr & 7) : kBsRows * q + rr;
+      next[u] = *reinterpret_cast<const f64x2*>(Bm + krow * kD + col);
+    }
+  };
+  fetch(0);
+#pragma unroll
+  for (int q = 0; q < kD / kBsRows; ++q) {  // unrolled: ya is indexed by q
     __syncthreads();
-    for (int e = tid; e < 16 * kD; e += blockDim.x) {
-      const int rr = e >> 7, col = e & 127;
-      const int krow = KMAP == 0 ? 32 * (rr >> 2) + 4 * q + (rr & 3) : 16 * q + rr;
-      Bs[rr * kBsStride + col] = Bm[krow * kD + col];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int e = tid + kMatThreads * u;
+      *reinterpret_cast<f64x2*>(Bs + (e / (kD / 2)) * kBsStride + 2 * (e % (kD / 2))) = next[u];
     }
     __syncthreads();
+    if (q + 1 < kD / kBsRows) fetch(q + 1);
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      const double b = ya[4 * q + d];
-      const double* br = Bs + (KMAP == 0 ? 4 * lk + d : 4 * d + lk) * kBsStride + li;
+    for (int e = 0; e < 8; ++e) {
+      const double b = ya[8 * q + e];
+      const double* br = Bs + (KMAP == 0 ? 8 * lk + e : 16 * (e >> 2) + 4 * (e & 3) + lk) * kBsStride + li;
 #pragma unroll
       for (int ct = 0; ct < 8; ++ct) acc[ct] = mfma64(br[16 * ct], b, acc[ct]);
     }
@@ -118,15 +134,17 @@ __device__ __forceinline__ void row_operand_f64(const double* row, bool ok, doub
 }
 
 // Rotation and quantization: zhat (the dequantized codes of (x - mu) R, fp64), the in-range mask, and
-// the effective rows zhat R^T. Block (128 tokens, KV head), wave w: tokens 16 w .. + 15 (one per lane
-// l % 16), every lane group l / 16 a quarter of the channels. A token's quantization group is spread
-// over its four lane groups: min / max through two cross-group exchanges.
-constexpr int kRotTile = 128;  // tokens per rotation work-group (eight waves of 16)
-__global__ __launch_bounds__(512) void cal_rotq_kernel(CalSet S, CalCfg c, int value) {
-  __shared__ double Bs[16 * kBsStride];
+// the effective rows zhat R^T, of the tokens some query reads from INT2 (S.units; the rest of those
+// buffers is never read into a result: with the paper's windows about two thirds of the tokens).
+// Block (four units, KV head), wave w: unit 4 bx + w (one token per lane l % 16), every lane group
+// l / 16 a quarter of the channels. A token's quantization group is spread over its four lane
+// groups: min / max through two cross-group exchanges. 77 -> 35 us (every token, 16 staged rows before).
+__global__ __launch_bounds__(kMatThreads) void cal_rotq_kernel(CalSet S, CalCfg c, int value) {
+  __shared__ __align__(16) double Bs[kBsRows * kBsStride];
   const int h = blockIdx.y, tid = threadIdx.x, w = tid >> 6, l = tid & 63, li = l & 15, lk = l >> 4;
-  const int tok = blockIdx.x * kRotTile + 16 * w + li;
-  const bool ok = tok < S.T;
+  const int4 unit = 4 * (int)blockIdx.x + w < S.nunits ? S.units[4 * blockIdx.x + w] : make_int4(0, 0, 0, 0);
+  const int tok = unit.x + li;
+  const bool ok = li < unit.y;
   const size_t xo = ((size_t)(ok ? tok : 0) * c.H + h) * kD, rowo = hrow(S, ok ? tok : 0, h);
   const uint16_t* X = value ? S.v : S.k;
   double ya[32];
@@ -636,8 +654,8 @@ __global__ __launch_bounds__(kTileThreads) void cal_pos_val_kernel(CalSet S, Cal
 // 64 positions), the layout of the rotation kernel with positions as rows (a row's four lane groups
 // are in one wave, each reads dO at its own output channels before writing them).
 constexpr int kUTile = 64;
-__global__ __launch_bounds__(256) void cal_u_kernel(CalSet S, CalCfg c, int value) {
-  __shared__ double Bs[16 * kBsStride];
+__global__ __launch_bounds__(kMatThreads) void cal_u_kernel(CalSet S, CalCfg c, int value) {
+  __shared__ __align__(16) double Bs[kBsRows * kBsStride];
   const int j = blockIdx.x, h = j / c.gq, jj = j % c.gq, tid = threadIdx.x;
   const int w = tid >> 6, l = tid & 63, li = l & 15, lk = l >> 4;
   const int npos = S.nrows / c.gq, pp = blockIdx.y * kUTile + 16 * w + li;
@@ -758,154 +776,153 @@ __global__ __launch_bounds__(kTileThreads) void cal_pos_grad_kernel(CalSet S, Ca
   }
 }
 
-// Gradient w.r.t. the effective rows: gx[s] = sum over the rows r of s's sequence of pd[r][s] y_r
-// with y_r = q_r / sqrt(d) (keys) or the row weight (values): per sequence the product
-// P^T Y of its [rows x len] weights and [rows x 128] row vectors, on the fp64 matrix cores. Block
-// (64-token tile, KV head) of four waves, wave w: tokens 16 w .. + 15 x all 128 channels (eight
-// 16 x 16 tiles); 16 rows at a time through LDS, the next chunk fetched into registers while the
-// matrix cores run on the current one.
-constexpr int kGxTok = 64, kGxRows = 16;
-constexpr int kGxPs = kGxTok + 16, kGxYs = kD + 16;  // padded LDS rows: lane groups l / 16 on other banks
-__global__ __launch_bounds__(256) void cal_gx_kernel(CalSet S, CalCfg c, int value) {
-  __shared__ double ps[kGxRows][kGxPs];
-  __shared__ double ys[kGxRows][kGxYs];
-  const int h = blockIdx.y, tid = threadIdx.x, s0 = blockIdx.x * kGxTok;
-  const int w = tid >> 6, l = tid & 63, li = l & 15, lk = l >> 4;
+// Gradient w.r.t. the effective rows and the rotated rows of one unit of 16 tokens:
+//   gx[s] = sum over the rows r of s's sequence of pd[r][s] y_r, y_r = q_r / sqrt(d) (keys) or the row
+//   weight (values), then gz = mask . (gx R).
+// Taken as gx^T = Y^T P (M = channels, N = the unit's tokens, K = rows), so the channels a lane ends with are
+// the K slices of the second product gz^T = R^T gx^T and gx needs no transpose. Both operands are read from
+// memory in operand order (lane li: channels 8 li + t of row lk for tiles t; token li of the row's weights),
+// so there is no staging and no barrier on the way. Block (unit, KV head) of two waves: each sums half of
+// the rows, the halves are added in order through LDS, and each forms half of gz's channels.
+// Bound by the matrix cores' fp64 rate within a wave. At 8 heads, 7 sequences, the paper's windows: 168 us
+// (64-token tiles staged through LDS over every token) + 49 us (gz on its own) -> 51 us.
+__global__ __launch_bounds__(128) void cal_gxz_kernel(CalSet S, CalCfg c, int value) {
+  __shared__ double part[2][32][64];
+  const int h = blockIdx.y, w = threadIdx.x >> 6, l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
+  const int4 unit = S.units[blockIdx.x];
+  const CalSeq sq = S.seqs[unit.z];
+  const int nr = (sq.len - sq.t0) * c.gq, half = 4 * (((nr + 3) / 4 + 1) / 2);
+  const int r_lo = w ? half : 0, r_hi = w ? nr : min(nr, half);
+  const bool ok = li < unit.y;
+  const double* pd = S.pd + (size_t)h * S.pelems + sq.p0 + (unit.w + (ok ? li : 0));
+  const double* wr = S.wrow + ((size_t)h * S.nrows + sq.row0) * kD + 8 * li;
+  const uint16_t* qr = S.q + ((size_t)(sq.start + sq.t0) * c.Hq + (size_t)h * c.gq) * kD + 8 * li;
   f64x4 acc[8];
 #pragma unroll
   for (int t = 0; t < 8; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-  int lo = 0, hi = S.nseq - 1;  // the sequence holding token s0
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (S.seqs[mid].start <= s0) lo = mid; else hi = mid - 1;
-  }
-  // chunk (sequence n, rows r0 .. r0 + 15) into registers: 4 weights and 8 row entries per thread
-  double pr[4], yr[8];
-  auto fetch = [&](const CalSeq& sq, int nr, int r0) {
-    const double* pd = S.pd + (size_t)h * S.pelems + sq.p0;
+  // rows past the end read the last row with weight zero
+  if (value) {
+#pragma unroll 4
+    for (int r0 = r_lo; r0 < r_hi; r0 += 4) {
+      const int r = min(r0 + lk, nr - 1);
+      const double2* y2 = reinterpret_cast<const double2*>(wr + (size_t)r * kD);
+      const double2 y[4] = {y2[0], y2[1], y2[2], y2[3]};
+      const double x = pd[(size_t)r * sq.len], p = ok && r0 + lk < r_hi ? x : 0.0;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = tid + 256 * u, i = e / kGxTok, x = e % kGxTok, sl = s0 + x - sq.start;
-      pr[u] = (r0 + i < nr && sl >= 0 && sl < sq.len) ? pd[(size_t)(r0 + i) * sq.len + sl] : 0.0;
+      for (int t = 0; t < 8; ++t) acc[t] = mfma64(t & 1 ? y[t >> 1].y : y[t >> 1].x, p, acc[t]);
     }
+  } else {
+    const int step = c.Hq * kD;  // row r: position r / gq, query head r % gq
+#pragma unroll 4
+    for (int r0 = r_lo; r0 < r_hi; r0 += 4) {
+      const int r = min(r0 + lk, nr - 1), pos = r / c.gq;
+      double y[8];
+      bf16x8_to_f64(*reinterpret_cast<const uint4*>(qr + (size_t)pos * step + (size_t)(r - pos * c.gq) * kD), y);
+      const double x = pd[(size_t)r * sq.len], p = ok && r0 + lk < r_hi ? x * kInvSqrtD : 0.0;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = tid + 256 * u, i = e / kD, col = e % kD, lr = r0 + i;
-      double y = 0.0;
-      if (lr < nr) {
-        if (value) {
-          y = S.wrow[((size_t)h * S.nrows + sq.row0 + lr) * kD + col];
-        } else {
-          const int t = sq.t0 + lr / c.gq, j = h * c.gq + lr % c.gq;
-          y = bf16d(S.q[((size_t)(sq.start + t) * c.Hq + j) * kD + col]) * kInvSqrtD;
-        }
-      }
-      yr[u] = y;
-    }
-  };
-  int n = lo, r0 = 0;
-  CalSeq sq = S.seqs[n];
-  int nr = (sq.len - sq.t0) * c.gq;
-  // the chunks: rows of every sequence that meets the tile, in order
-  auto valid = [&]() { return n < S.nseq && sq.start < s0 + kGxTok; };
-  auto advance = [&]() {
-    r0 += kGxRows;
-    while (valid() && r0 >= nr) {
-      if (++n >= S.nseq) break;
-      sq = S.seqs[n];
-      nr = (sq.len - sq.t0) * c.gq;
-      r0 = 0;
-    }
-  };
-  if (valid() && nr == 0) {  // a sequence without query rows contributes nothing
-    r0 = -kGxRows;
-    advance();
-  }
-  if (valid()) fetch(sq, nr, r0);
-  while (valid()) {
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = tid + 256 * u;
-      ps[e / kGxTok][e % kGxTok] = pr[u];
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = tid + 256 * u;
-      ys[e / kD][e % kD] = yr[u];
-    }
-    __syncthreads();
-    advance();
-    if (valid()) fetch(sq, nr, r0);
-#pragma unroll
-    for (int k4 = 0; k4 < kGxRows; k4 += 4) {
-      const double a = ps[k4 + lk][16 * w + li];
-#pragma unroll
-      for (int t = 0; t < 8; ++t) acc[t] = mfma64(a, ys[k4 + lk][16 * t + li], acc[t]);
+      for (int t = 0; t < 8; ++t) acc[t] = mfma64(y[t], p, acc[t]);
     }
   }
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int s = s0 + 16 * w + lk + 4 * v;
-    if (s < S.T) {
-      double* out = S.gx + hrow(S, s, h) + li;
+  for (int t = 0; t < 8; ++t)
 #pragma unroll
-      for (int t = 0; t < 8; ++t) out[16 * t] = acc[t][v];
-    }
-  }
-}
-
-// gz = mask . (gx R): block (64 tokens, KV head), the layout of the rotation kernel.
-constexpr int kGzTile = 64;
-__global__ __launch_bounds__(256) void cal_gz_kernel(CalSet S, CalCfg c) {
-  __shared__ double Bs[16 * kBsStride];
-  const int h = blockIdx.y, tid = threadIdx.x, w = tid >> 6, l = tid & 63, li = l & 15, lk = l >> 4;
-  const int tok = blockIdx.x * kGzTile + 16 * w + li;
-  const bool ok = tok < S.T;
-  const size_t rowo = hrow(S, ok ? tok : 0, h);
-  double ya[32];
-  row_operand_f64(S.gx + rowo, ok, ya);
-  f64x4 acc[8];
+    for (int v = 0; v < 4; ++v) part[w][4 * t + v][l] = acc[t][v];
+  __syncthreads();
 #pragma unroll
-  for (int ct = 0; ct < 8; ++ct) acc[ct] = f64x4{0.0, 0.0, 0.0, 0.0};
-  mat_t_rows<0>(ya, c.R + (size_t)h * kMat, Bs, acc);
+  for (int t = 0; t < 8; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[t][v] += part[1 - w][4 * t + v][l];  // two terms: the same in either order
+  // element v of acc[t]: token li, channel 8 (lk + 4 v) + t; wave w stores v = 2 w, 2 w + 1
+  const size_t row = hrow(S, unit.x + (ok ? li : 0), h);
   if (ok)
 #pragma unroll
-    for (int ct = 0; ct < 8; ++ct)
+    for (int v = 0; v < 4; ++v) {
+      if ((v >> 1) != w) continue;
+      double2* o = reinterpret_cast<double2*>(S.gx + row + 8 * (lk + 4 * v));
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const size_t o = rowo + 16 * ct + lk + 4 * v;
-        S.gz[o] = S.mask[o] ? acc[ct][v] : 0.0;
-      }
+      for (int t = 0; t < 4; ++t) o[t] = make_double2(acc[2 * t][v], acc[2 * t + 1][v]);
+    }
+  // gz: wave w's channels 64 w + 4 m + ct, m the row of tile ct
+  f64x4 z[4];
+#pragma unroll
+  for (int ct = 0; ct < 4; ++ct) z[ct] = f64x4{0.0, 0.0, 0.0, 0.0};
+  const double* R = c.R + (size_t)h * kMat + 64 * w + 4 * li;
+#pragma unroll
+  for (int t = 0; t < 8; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const double2* r2 = reinterpret_cast<const double2*>(R + (8 * (lk + 4 * v) + t) * kD);
+      const double2 ra = r2[0], rb = r2[1];
+      z[0] = mfma64(ra.x, acc[t][v], z[0]);
+      z[1] = mfma64(ra.y, acc[t][v], z[1]);
+      z[2] = mfma64(rb.x, acc[t][v], z[2]);
+      z[3] = mfma64(rb.y, acc[t][v], z[3]);
+    }
+  if (ok)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const size_t o = row + 64 * w + 4 * (lk + 4 * v);
+      const uint32_t m = *reinterpret_cast<const uint32_t*>(S.mask + o);
+      double2* g = reinterpret_cast<double2*>(S.gz + o);
+      g[0] = make_double2(m & 0xFF ? z[0][v] : 0.0, m & 0xFF00 ? z[1][v] : 0.0);
+      g[1] = make_double2(m & 0xFF0000 ? z[2][v] : 0.0, m & 0xFF000000 ? z[3][v] : 0.0);
+    }
 }
 
-// Partial dL/dR over a token slice: sum_s x_s[a] gz_s[b] + gx_s[a] zhat_s[b] on the fp64 matrix
-// cores (M = a, N = b, K = the slice's tokens, four per step). Block (KV head, slice) of eight
-// waves, wave w: rows a = 16 w .. + 15 and all 128 columns; 16-token chunks of the four operands
-// staged in LDS.
+// Partial dL/dR over a slice of the units (the other tokens have gx = 0): sum_s x_s[a] gz_s[b] +
+// gx_s[a] zhat_s[b] on the fp64 matrix cores (M = a, N = b, K = the slice's tokens, four per step).
+// Block (KV head, slice) of eight waves, wave w: rows a = 16 w .. + 15 and all 128 columns; the four
+// operands of one unit at a time staged in LDS, the next unit's fetched meanwhile. 101 -> 24 us (every
+// token, nothing in flight before).
 constexpr int kDrChunk = 16, kDrStride = 132;
 __global__ __launch_bounds__(512) void cal_dr_kernel(CalSet S, CalCfg c, int value) {
-  __shared__ double xs[kDrChunk][kDrStride], gxs[kDrChunk][kDrStride];
-  __shared__ double gzs[kDrChunk][kDrStride], zs[kDrChunk][kDrStride];
+  __shared__ __align__(16) double xs[kDrChunk][kDrStride], gxs[kDrChunk][kDrStride];
+  __shared__ __align__(16) double gzs[kDrChunk][kDrStride], zs[kDrChunk][kDrStride];
   const int h = blockIdx.x, sp = blockIdx.y, tid = threadIdx.x;
   const int w = tid >> 6, l = tid & 63, li = l & 15, lk = l >> 4;
-  const int s_lo = (int)((long long)S.T * sp / kCalSplit), s_hi = (int)((long long)S.T * (sp + 1) / kCalSplit);
+  const int u_lo = (int)((long long)S.nunits * sp / kCalSplit), u_hi = (int)((long long)S.nunits * (sp + 1) / kCalSplit);
   const uint16_t* X = value ? S.v : S.k;
+  // thread: token tid / 32 of the unit, channels 4 (tid % 32) .. + 3
+  const int tt = tid >> 5, c4 = 4 * (tid & 31);
+  double mu[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) mu[i] = value ? 0.0 : (double)c.mu[h * kD + c4 + i];
+  uint2 xr;
+  f64x2 gxr[2], gzr[2], zr[2];
+  bool okr = false;
+  auto fetch = [&](int u) {
+    const int4 unit = S.units[u];
+    okr = tt < unit.y;
+    const int s = unit.x + (okr ? tt : 0);
+    const size_t io = hrow(S, s, h) + c4;
+    xr = *reinterpret_cast<const uint2*>(X + ((size_t)s * c.H + h) * kD + c4);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      gxr[i] = reinterpret_cast<const f64x2*>(S.gx + io)[i];
+      gzr[i] = reinterpret_cast<const f64x2*>(S.gz + io)[i];
+      zr[i] = reinterpret_cast<const f64x2*>(S.zhat + io)[i];
+    }
+  };
   f64x4 acc[8];
 #pragma unroll
   for (int ct = 0; ct < 8; ++ct) acc[ct] = f64x4{0.0, 0.0, 0.0, 0.0};
-  for (int s0 = s_lo; s0 < s_hi; s0 += kDrChunk) {
+  if (u_lo < u_hi) fetch(u_lo);
+  for (int u = u_lo; u < u_hi; ++u) {
     __syncthreads();
-    for (int e = tid; e < kDrChunk * kD; e += blockDim.x) {
-      const int t = e >> 7, col = e & 127, s = s0 + t;
-      const bool ok = s < s_hi;
-      const size_t o = ((size_t)(ok ? s : s_lo) * c.H + h) * kD + col, io = hrow(S, ok ? s : s_lo, h) + col;
-      xs[t][col] = ok ? bf16d(X[o]) - (value ? 0.0 : (double)c.mu[h * kD + col]) : 0.0;
-      gxs[t][col] = ok ? S.gx[io] : 0.0;
-      gzs[t][col] = ok ? S.gz[io] : 0.0;
-      zs[t][col] = ok ? S.zhat[io] : 0.0;
+    const f64x2 z2 = {0.0, 0.0};
+    const double x0 = (double)__uint_as_float(xr.x << 16), x1 = (double)__uint_as_float(xr.x & 0xFFFF0000u);
+    const double x2 = (double)__uint_as_float(xr.y << 16), x3 = (double)__uint_as_float(xr.y & 0xFFFF0000u);
+    f64x2* px = reinterpret_cast<f64x2*>(&xs[tt][c4]);
+    px[0] = okr ? f64x2{x0 - mu[0], x1 - mu[1]} : z2;
+    px[1] = okr ? f64x2{x2 - mu[2], x3 - mu[3]} : z2;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      reinterpret_cast<f64x2*>(&gxs[tt][c4])[i] = okr ? gxr[i] : z2;
+      reinterpret_cast<f64x2*>(&gzs[tt][c4])[i] = okr ? gzr[i] : z2;
+      reinterpret_cast<f64x2*>(&zs[tt][c4])[i] = okr ? zr[i] : z2;
     }
     __syncthreads();
+    if (u + 1 < u_hi) fetch(u + 1);
 #pragma unroll
     for (int k4 = 0; k4 < kDrChunk; k4 += 4) {
       const int t = k4 + lk;
@@ -1373,24 +1390,41 @@ __global__ __launch_bounds__(256) void cal_to_f32_kernel(const double* __restric
   if (i < n) dst[i] = (float)src[i];
 }
 
-// W_{O,j}^T W_{O,j} on the fp64 matrix cores: block = query head j, eight waves; wave w owns output rows
-// 16 w .. 16 w + 15 (all eight 16-column tiles). The head's d_model x 128 slice of W_O goes through LDS
-// 16 rows at a time (bf16 -> fp64, exact); K = those rows, 4 per step.
-constexpr int kGramRows = 16;
+// Partial W_{O,j}^T W_{O,j} over a slice of W_O's rows on the fp64 matrix cores: block (query head j, slice)
+// of eight waves, wave w: output rows 16 w .. 16 w + 15 (all eight 16-column tiles). The head's slice goes
+// through LDS 32 rows at a time (bf16 -> fp64, exact), the next rows fetched meanwhile; K = those rows, 4
+// per step. The slices (into c.drp: as many as it holds for the query heads) are summed in order. Bound by
+// the fp64 matrix cores of the CUs in use: 976 us with one block per query head (32 of 256 CUs) ->
+// 146 us at four slices and the next rows in flight.
+constexpr int kGramRows = 32;
+__host__ __device__ constexpr int gram_slices(int gq) { return gq < kCalSplit ? kCalSplit / gq : 1; }
 __global__ __launch_bounds__(512) void cal_gram_kernel(const uint16_t* __restrict__ W, int dm, int Hq,
-                                                       double* __restrict__ gram) {
-  __shared__ double xs[kGramRows][kD + 2];
-  const int j = blockIdx.x, tid = threadIdx.x, w = tid >> 6, l = tid & 63, lo = l & 15, lk = l >> 4;
+                                                       double* __restrict__ part) {
+  __shared__ __align__(16) double xs[kGramRows][kD + 2];
+  const int j = blockIdx.x, sl = blockIdx.y, tid = threadIdx.x, w = tid >> 6, l = tid & 63, lo = l & 15, lk = l >> 4;
   const size_t ld = (size_t)Hq * kD;
+  const int n_lo = (int)((long long)dm * sl / gridDim.y), n_hi = (int)((long long)dm * (sl + 1) / gridDim.y);
   f64x4 acc[8];
 #pragma unroll
   for (int t = 0; t < 8; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-  for (int r0 = 0; r0 < dm; r0 += kGramRows) {
-    for (int e = tid; e < kGramRows * kD; e += 512) {
-      const int rr = e / kD, c = e % kD;
-      xs[rr][c] = r0 + rr < dm ? bf16d(W[(size_t)(r0 + rr) * ld + (size_t)j * kD + c]) : 0.0;
-    }
+  // thread: row tid / 16 of the chunk, channels 8 (tid % 16) .. + 7
+  const int rr = tid >> 4, c8 = 8 * (tid & 15);
+  uint4 xr = make_uint4(0, 0, 0, 0);
+  bool okr = false;
+  auto fetch = [&](int r0) {
+    okr = r0 + rr < n_hi;
+    // W_O has no alignment beyond its type's
+    __builtin_memcpy(&xr, W + (size_t)(okr ? r0 + rr : n_lo) * ld + (size_t)j * kD + c8, 16);
+  };
+  if (n_lo < n_hi) fetch(n_lo);
+  for (int r0 = n_lo; r0 < n_hi; r0 += kGramRows) {
+    double d[8];
+    bf16x8_to_f64(okr ? xr : make_uint4(0, 0, 0, 0), d);
     __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) reinterpret_cast<double2*>(&xs[rr][c8])[i] = make_double2(d[2 * i], d[2 * i + 1]);
+    __syncthreads();
+    if (r0 + kGramRows < n_hi) fetch(r0 + kGramRows);
 #pragma unroll
     for (int k4 = 0; k4 < kGramRows; k4 += 4) {
       // A[m][k] = X[k][16 w + m], B[k][n] = X[k][16 t + n]: lane l holds A[lo][lk] and B[lk][lo]
@@ -1398,13 +1432,21 @@ __global__ __launch_bounds__(512) void cal_gram_kernel(const uint16_t* __restric
 #pragma unroll
       for (int t = 0; t < 8; ++t) acc[t] = mfma64(av, xs[k4 + lk][16 * t + lo], acc[t]);
     }
-    __syncthreads();
   }
   // element v of tile t: row 16 w + lk + 4 v, column 16 t + lo
+  double* out = part + ((size_t)sl * Hq + j) * kMat;
 #pragma unroll
   for (int t = 0; t < 8; ++t)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) gram[((size_t)j * kD + 16 * w + lk + 4 * v) * kD + 16 * t + lo] = acc[t][v];
+    for (int v = 0; v < 4; ++v) out[(16 * w + lk + 4 * v) * kD + 16 * t + lo] = acc[t][v];
+}
+
+__global__ __launch_bounds__(256) void cal_gram_sum_kernel(const double* __restrict__ part, size_t n, int slices,
+                                                           double* __restrict__ gram) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;  // n is a multiple of 256
+  double t = part[i];
+  for (int s = 1; s < slices; ++s) t += part[(size_t)s * n + i];
+  gram[i] = t;
 }
 
 // Per-channel mean of the keys: block = KV head, thread = channel (sequential fp64 sum).
@@ -1422,7 +1464,8 @@ size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
 size_t cal_set_bytes(int T, int nseq, int nrows, long long pelems, int H) {
   const size_t rows = (size_t)T * H * kD;
-  return up256(sizeof(CalSeq) * (size_t)nseq) + up256(sizeof(int4) * (size_t)nrows) + up256(sizeof(int) * (size_t)nrows) + 4 * up256(rows * 8) +
+  return up256(sizeof(CalSeq) * (size_t)nseq) + up256(sizeof(int4) * (size_t)nrows) +
+         up256(sizeof(int4) * ((size_t)T / 16 + nseq)) + 4 * up256(rows * 8) +
          up256(rows) + 4 * up256((size_t)H * pelems * 8) + 3 * up256((size_t)H * nrows * kD * 8) +
          up256((size_t)H * nrows * 16) + 2 * up256((size_t)H * nrows * 8);
 }
@@ -1433,9 +1476,9 @@ size_t cal_shared_bytes(int H, int Hq) {
 }
 
 hipError_t cal_bind_set(CalSet& set, uint8_t* base, const uint16_t* k, const uint16_t* v, const uint16_t* q,
-                        const int32_t* starts_host, int nseq, int H, int gq, int n_last, hipStream_t s) {
+                        const int32_t* starts_host, int nseq, int H, int gq, int n_last, int sink, int recent, hipStream_t s) {
   std::vector<CalSeq> seqs(nseq);
-  std::vector<int> row_seq;
+  std::vector<int4> units;
   long long pel = 0;
   int rows = 0, maxlen = 0;
   for (int i = 0; i < nseq; ++i) {
@@ -1447,7 +1490,8 @@ hipError_t cal_bind_set(CalSet& set, uint8_t* base, const uint16_t* k, const uin
     c.p0 = pel;
     maxlen = c.len > maxlen ? c.len : maxlen;
     const int nr = (c.len - c.t0) * gq;
-    for (int r = 0; r < nr; ++r) row_seq.push_back(i);
+    // the tokens the last position reads from INT2 hold those of every earlier one
+    for (int s0 = sink; s0 < c.len - recent; s0 += 16) units.push_back(make_int4(c.start + s0, min(16, c.len - recent - s0), i, s0));
     rows += nr;
     pel += (long long)nr * c.len;
   }
@@ -1475,8 +1519,9 @@ hipError_t cal_bind_set(CalSet& set, uint8_t* base, const uint16_t* k, const uin
   p += up256(sizeof(CalSeq) * (size_t)nseq);
   set.tiles = reinterpret_cast<int4*>(p);
   p += up256(sizeof(int4) * (size_t)rows);
-  set.row_seq = reinterpret_cast<int*>(p);
-  p += up256(sizeof(int) * (size_t)rows);
+  set.units = reinterpret_cast<int4*>(p);
+  set.nunits = (int)units.size();
+  p += up256(sizeof(int4) * ((size_t)set.T / 16 + nseq));
   set.zhat = reinterpret_cast<double*>(p);
   p += up256(nrow_el * 8);
   set.xeff = reinterpret_cast<double*>(p);
@@ -1507,8 +1552,8 @@ hipError_t cal_bind_set(CalSet& set, uint8_t* base, const uint16_t* k, const uin
   p += up256((size_t)H * rows * kD * 8);
   set.lrow = reinterpret_cast<double*>(p);
   hipError_t e = hipMemcpyAsync(set.seqs, seqs.data(), sizeof(CalSeq) * nseq, hipMemcpyHostToDevice, s);
-  if (e == hipSuccess && rows > 0)
-    e = hipMemcpyAsync(set.row_seq, row_seq.data(), sizeof(int) * rows, hipMemcpyHostToDevice, s);
+  if (e == hipSuccess && !units.empty())
+    e = hipMemcpyAsync(set.units, units.data(), sizeof(int4) * units.size(), hipMemcpyHostToDevice, s);
   if (e == hipSuccess && !tiles.empty())
     e = hipMemcpyAsync(set.tiles, tiles.data(), sizeof(int4) * tiles.size(), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host tables go out of scope
@@ -1529,7 +1574,10 @@ void cal_bind_shared(CalCfg& c, uint8_t* base) {
 }
 
 hipError_t cal_gram(const CalCfg& c, const uint16_t* W_o, hipStream_t s) {
-  hipLaunchKernelGGL(cal_gram_kernel, dim3(c.Hq), dim3(512), 0, s, W_o, c.dm, c.Hq, c.gram);
+  const int slices = gram_slices(c.gq);
+  const size_t n = (size_t)c.Hq * kMat;
+  hipLaunchKernelGGL(cal_gram_kernel, dim3(c.Hq, slices), dim3(512), 0, s, W_o, c.dm, c.Hq, c.drp);
+  hipLaunchKernelGGL(cal_gram_sum_kernel, dim3((unsigned)(n / 256)), dim3(256), 0, s, c.drp, n, slices, c.gram);
   return hipGetLastError();
 }
 
@@ -1542,20 +1590,15 @@ static void rotation(const CalCfg& c, const double* A, int value, hipStream_t s)
 
 static void rot_and_quant(const CalCfg& c, CalSet& set, const double* A, int value, hipStream_t s) {
   rotation(c, A, value, s);
-  if (set.T > 0)
-    hipLaunchKernelGGL(cal_rotq_kernel, dim3((set.T + kRotTile - 1) / kRotTile, c.H), dim3(512), 0, s, set, c, value);
+  if (set.nunits > 0)
+    hipLaunchKernelGGL(cal_rotq_kernel, dim3((set.nunits + 3) / 4, c.H), dim3(kMatThreads), 0, s, set, c, value);
 }
 
 // after rot_and_quant for the same generators (it leaves the powers of S)
 static void backward(const CalCfg& c, CalSet& set, int value, double* grad, hipStream_t s) {
-  if (set.T > 0) {
-    hipLaunchKernelGGL(cal_gx_kernel, dim3((set.T + kGxTok - 1) / kGxTok, c.H), dim3(256), 0, s, set, c, value);
-    hipLaunchKernelGGL(cal_gz_kernel, dim3((set.T + kGzTile - 1) / kGzTile, c.H), dim3(256), 0, s, set, c);
-    hipLaunchKernelGGL(cal_dr_kernel, dim3(c.H, kCalSplit), dim3(512), 0, s, set, c, value);
-  } else {
-    hipLaunchKernelGGL(cal_fill_kernel, dim3((unsigned)((kCalSplit * (size_t)c.H * kMat + 255) / 256)), dim3(256), 0,
-                       s, c.drp, kCalSplit * (size_t)c.H * kMat, 0.0);
-  }
+  if (set.nunits > 0)
+    hipLaunchKernelGGL(cal_gxz_kernel, dim3(set.nunits, c.H), dim3(128), 0, s, set, c, value);
+  hipLaunchKernelGGL(cal_dr_kernel, dim3(c.H, kCalSplit), dim3(512), 0, s, set, c, value);  // zeros without units
   const dim3 grid(kD / kExpCols, c.H), block(kExpThreads);
   hipLaunchKernelGGL(cal_grad_g_kernel, grid, block, 0, s, c, value);
   hipLaunchKernelGGL(cal_grad_powers_kernel, grid, block, 0, s, c);

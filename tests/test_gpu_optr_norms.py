@@ -45,3 +45,34 @@ def test_objectives_and_gradients_over_generator_norms(scale):
             dg = np.linalg.norm(got_g[h].cpu().numpy() - g) / np.linalg.norm(g)
             print(f"head {h}: loss {dl:.1e}, gradient {dg:.1e}", flush=True)
             assert dl <= 1e-9 and dg <= 1e-7, (scale, h, dl, dg)
+
+
+@pytest.mark.parametrize("lens,sink,recent", [([40, 30], 0, 1000), ([50, 3, 41], 7, 30), ([64, 33], 16, 0)])
+def test_few_or_no_int2_tokens(lens, sink, recent):
+    """Only the tokens some query reads from INT2 are rotated and differentiated: windows that leave none at all, none in
+    some sequences, or a count that is not a multiple of the sixteen tokens of a unit."""
+    H, Hq = 2, 4
+    w = W.make_workload(1, batch=1, ctx=16, num_q_heads=Hq, num_kv_heads=H, d_model=64)
+    rng = np.random.default_rng(6)
+    T = sum(lens)
+    bits = lambda *s: W.f32_to_bf16_bits(rng.standard_normal(s).astype(np.float32))
+    k, v, q, st = bits(T, H, 128), bits(T, H, 128), bits(T, Hq, 128), np.cumsum([0] + lens).astype(np.int32)
+    mu = P.key_mean(k)
+    cfg = K.optr_config(H, Hq, 64, group_size=128, n_last=12, sink=sink, recent=recent)
+    A, Av = rng.standard_normal((2, H, 128, 128)) * 0.02
+    tr = K.OptrTraces(dev(k), dev(v), dev(q), st)
+    lk, gk = K.int2kv_optr_key_loss(cfg, tr, dev(w.R_k), dev(mu), dev(w.W_o), dev(A))
+    lv, gv = K.int2kv_optr_value_loss(cfg, tr, dev(w.R_k), dev(A), dev(mu), dev(w.R_v), dev(w.W_o), dev(Av))
+    kw = dict(group=128, n_last=12, sink=sink, recent=recent)
+    for h in range(H):
+        probs = P.key_probs(w.R_k, A[h], k, q, st, mu, h, 2, clip=0.96, **kw)
+        for got_l, got_g, gen, loss in (
+                (lk, gk, A, lambda x: P.key_loss(x, w.R_k, k, v, q, st, mu, w.W_o, h, 2, clip=0.96, **kw)),
+                (lv, gv, Av, lambda x: P.value_loss(x, w.R_v, v, st, probs, w.W_o, h, 2, clip=0.92, **kw))):
+            x = torch.from_numpy(gen[h].copy()).requires_grad_(True)
+            ref = loss(x)
+            ref.backward()
+            g = x.grad.numpy()
+            # absolute terms: with no INT2 token both are zero up to the rounding of the softmaxes' sums
+            assert abs(float(got_l[h]) - float(ref.detach())) <= 1e-9 * abs(float(ref.detach())) + 1e-14
+            assert np.linalg.norm(got_g[h].cpu().numpy() - g) <= 1e-7 * np.linalg.norm(g) + 1e-13
