@@ -7,27 +7,63 @@
 
 namespace int2kv {
 
-// Append on the matrix cores: x R (x bf16 [n, H, 128], R fp32 [128, 128]) as bf16 MFMA with R split
-// into three bf16 terms (R = R_1 + R_2 + R_3 + O(2^-27 |R|): every product is exact and the sum is
-// an fp32 accumulation, like an fp32 GEMM), starting from - mu R_K for keys; then the group
-// quantizer and the packed stores. Work-group (KV head h, K or V, a stride of 16-token
-// tiles); R^T of the work-group's (h, K|V) is converted once into LDS as the B operand.
-// Tile layout: the product is formed transposed, D^T = R^T x^T, with R^T fragments as the A operand
-// and token rows as the B operand. D^T[channel][token] of m-tile p (channels 16p .. 16p + 15) sits
-// in lane token + 16 ((channel % 16) / 4), register channel % 4: lane (token, hi) holds channels
-// 16 p + 4 hi + j, so register j of tiles p = 0..7 gives the eight 2-bit codes of half 4 hi + j of
-// the packed layout, and the 32 channels of group g (tiles 2g, 2g + 1) sit in the four lanes of
-// one token, eight in each. The group parameters are then computed once per (token, group).
+// The cache write of one (KV head, K or V): x R (x bf16 [n, H, 128], R fp32 [128, 128]) as bf16 MFMA with R
+// split into three bf16 terms by truncation (R = t0 + t1 + t2 exactly: t0 and t1 take the leading 8 significant
+// bits of R and of R - t0, the remainder has at most 8 left; every product is exact in fp32), an fp32
+// accumulation starting from - mu R_K for keys, smallest term first; then the group quantizer and the packed
+// stores.
+//
+// A work-group has four waves and takes 32-token tiles. Wave g owns the 32 output channels of group g: its
+// share of R^T, 32 channels x 128 x 3 terms, stays in registers (96 per lane) as the A operand of
+// 32 x 32 x 16 products, so a work-group starts in a few microseconds (no R^T to stage) and the LDS traffic of a
+// tile is its 8 KiB of tokens, read once by each wave. D^T[row][token]: lane (token t = l % 32, hf = l / 32)
+// holds rows 8 a + 4 hf + b in register 4 a + b. R^T's rows are permuted so that row 8 a + 4 hf + b is
+// channel 16 (a / 2) + 8 hf + 4 (a % 2) + b of the group: a lane's 16 values are then both 2-bit codes
+// (positions 2 g, 2 g + 1) of the packed halves 8 hf .. 8 hf + 7, one 32-bit word of nibbles, and a group's
+// extremes need one exchange with lane l ^ 32. The four waves' nibble words meet in LDS and a later step
+// interleaves and stores them (32 contiguous bytes of key codes per token).
+//
+// Step i: packed stores of tile i - 2, loads of a later tile, products of tile i beside the quantizer of
+// tile i - 1, one barrier. Tiles come by LDS-DMA, kApStages - 1 ahead; with RoPE through registers, since thread
+// (token, channels 8 j .. 8 j + 7 and 64 + 8 j ..) holds whole rotate-half pairs and contiguous pieces of the row, of
+// the table and of the post-RoPE output. Matrix cores and vector ALU (about 220 instructions per tile and
+// wave, 80 of them the quantizer's) add up rather than overlap, also when alternated in one wave; long dense
+// prompts therefore use the arrangement of append_wide.h.
+//
+// Us a call at 8 KV heads, against sixteen 16-token tiles per eight-wave work-group with R^T in LDS: RoPE,
+// 32,768 tokens 91 -> 75; RoPE and Hadamard, 16,384 tokens 44.5 -> 31.8; RoPE, G = 128, 2,011 tokens 11.3 ->
+// 10.6; one decode step (32/8 heads, 1,011 tokens), whose first launch carries the write, 30.5 -> 28.8.
 typedef __bf16 ap_bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float ap_f4_t __attribute__((ext_vector_type(4)));
+typedef float ap_f16_t __attribute__((ext_vector_type(16)));
+typedef uint32_t ap_u4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kApWaves = 8;
-constexpr int kApDepth = 6;   // R^T fragments in flight
-constexpr int kApRow = 144;   // bf16 per LDS row of R^T (128 + 16 pad: conflict-free 16-byte reads)
+constexpr int kApTok = 32;       // tokens per tile
+constexpr int kApThreads = 256;  // four waves, one per 32-channel group
+#ifndef INT2KV_AP_DEPTH
+#define INT2KV_AP_DEPTH 2
+#endif
+constexpr int kApDepth = INT2KV_AP_DEPTH;  // tiles in flight in registers
+
+// LDS of one append work-group
+#ifndef INT2KV_AP_STAGES
+#define INT2KV_AP_STAGES 4
+#endif
+constexpr int kApStages = INT2KV_AP_STAGES;  // tiles staged by LDS-DMA
+struct ApLds {
+  __attribute__((aligned(16))) uint8_t x[kApStages][kApTok * 256];  // tile rows, 16-byte piece q at q ^ (token % 16)
+  __attribute__((aligned(16))) int slot[kApStages][kApThreads];     // each thread's slot (token tid / 8)
+  __attribute__((aligned(16))) uint32_t words[2][kApTok][2][4];  // nibble words [token][hf][group]
+  __attribute__((aligned(16))) uint32_t meta[2][kApTok][4];      // scale | zero << 16 per group
+  float err[2][kApTok][4];                                       // squared reconstruction errors
+  float ext[kApTok][4][2];                                       // extremes per 32 channels (one group per token)
+  __attribute__((aligned(16))) float sub[kHeadDim];              // - mu R_K (keys), 0 (values)
+  float recip[1024];                                             // RN(1 / (1 + m / 1024))
+};
+constexpr int kAppendLdsBytes = sizeof(ApLds);
 
 // x / 3 correctly rounded, as a product with RN(1/3) and one FMA correction: checked against the
 // correctly rounded quotient for every fp32 significand (so for every x whose intermediate values
-// stay normal: x == 0 or x >= 2^-100; the caller routes other x to a division).
+// stay normal: x == 0 or x >= 2^-100).
 __device__ __forceinline__ float div3_rn(float x) {
 #pragma clang fp contract(off)
   const float c = 0x1.555556p-2f;  // RN(1/3)
@@ -36,35 +72,25 @@ __device__ __forceinline__ float div3_rn(float x) {
   return __builtin_fmaf(r, c, q0);
 }
 
-// The quantizer's group parameters (bit-identical to int2_group_params): s = fp16((mx - mn) / 3)
-// with the division above, and 1/s from a table of the correctly rounded reciprocals of the 1024
-// normal fp16 significands (exact after the power-of-two scaling); zero, fp16-subnormal and
-// infinite scales and tiny ranges take the division.
+// The quantizer's group parameters (bit-identical to int2_group_params), without branches: s = fp16((mx - mn) / 3)
+// with the division above (below 2^-100 its value does not matter: fp16 rounds it to zero), and 1/s from a
+// table of the correctly rounded reciprocals of 1 + m / 1024: s has at most 11 significant bits, so its fp32
+// form (normalized, also for subnormal s) is (1 + m / 1024) 2^e and the scaling by 2^-e is exact. Zero,
+// infinite and NaN scales have no reciprocal (0: 1/inf, and by definition for s = 0).
 __device__ __forceinline__ void int2_group_params_fast(float mn, float mx, float clip, const float* recip_tab,
                                                        uint32_t& s_bits, uint32_t& z_bits, float& zf, float& inv) {
 #pragma clang fp contract(off)
-  if (clip != 1.0f) {
-    mn = clip * mn;
-    mx = clip * mx;
-  }
-  const float range = mx - mn;
-  float s32;
-  if (range != 0.0f && range < 0x1p-100f)
-    s32 = range / 3.0f;
-  else
-    s32 = div3_rn(range);
-  const __half s = __float2half_rn(s32);
+  mn = clip != 1.0f ? clip * mn : mn;
+  mx = clip != 1.0f ? clip * mx : mx;
+  const __half s = __float2half_rn(div3_rn(mx - mn));
   const __half z = __float2half_rn(mn);
   s_bits = __half_as_ushort(s);
   z_bits = __half_as_ushort(z);
   zf = __half2float(z);
-  const uint32_t e16 = (s_bits >> 10) & 31u;
-  if (e16 == 0u || e16 == 31u) {  // zero, fp16-subnormal or infinite scale
-    const float sf = __half2float(s);
-    inv = sf > 0.0f ? 1.0f / sf : 0.0f;
-  } else {
-    inv = __builtin_ldexpf(recip_tab[s_bits & 1023u], 15 - (int)e16);
-  }
+  const float sf = __half2float(s);
+  const uint32_t u = __float_as_uint(sf);
+  const float r = __builtin_ldexpf(recip_tab[(u >> 13) & 1023u], 127 - (int)(u >> 23));
+  inv = sf > 0.0f && sf < INFINITY ? r : 0.0f;
 }
 
 // Cross-lane exchanges of the group reductions on the vector ALU (no LDS round trip).
@@ -79,165 +105,55 @@ __device__ __forceinline__ LanePair lane_swap32(float a, float b) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
   return LanePair{__uint_as_float(r[0]), __uint_as_float(r[1])};
 }
-__device__ __forceinline__ LanePair lane_swap16(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  return LanePair{__uint_as_float(r[0]), __uint_as_float(r[1])};
-}
-
-// Packed output of one lane for one 16-token tile: halves 4 hi .. 4 hi + 3 of its token (two per
-// word) and the scale / zero of group hi.
+// Quantizer parameters and codes of one tile: v[4 a + b] as above; returns the nibble word and the packed
+// (scale, zero) of the lane's group, e = the token's squared error over the group (both lanes).
 struct ApOut {
-  uint32_t w01, w23, meta;
-  float err;  // with ERR: squared reconstruction error of the token's 128 channels (every lane of it)
+  uint32_t word, meta;
+  float err;
 };
-
-// Group quantizer of one 16-token tile held in the transposed layout above.
-// With ERR, also the token's squared reconstruction error sum_c (x_c - (code_c s + z))^2 in fp32
-// (the rotated basis, where it equals the model basis' ||k - k~||^2: R is orthogonal).
-template <int NG, bool ERR = false>
-__device__ __forceinline__ ApOut quantize_tile(const ap_f4_t (&acc)[8], float clip, const float* recip_tab, int lo,
-                                               int hi) {
-  if constexpr (NG == 1) {
-    // one group of 128 channels: the lane's 32 values, then the token's four lanes (xor 16, 32)
-    float mn = acc[0][0], mx = acc[0][0];
-#pragma unroll
-    for (int p = 0; p < 8; ++p)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        mn = __builtin_elementwise_minimum(mn, acc[p][j]);
-        mx = __builtin_elementwise_maximum(mx, acc[p][j]);
-      }
-    {
-      const auto n16 = lane_swap16(mn, mn), x16 = lane_swap16(mx, mx);
-      mn = __builtin_elementwise_minimum(n16.a, n16.b);
-      mx = __builtin_elementwise_maximum(x16.a, x16.b);
-      const auto n32 = lane_swap32(mn, mn), x32 = lane_swap32(mx, mx);
-      mn = __builtin_elementwise_minimum(n32.a, n32.b);
-      mx = __builtin_elementwise_maximum(x32.a, x32.b);
-    }
-    uint32_t s_bits, z_bits;
-    float zf, inv;
-    int2_group_params_fast(mn, mx, clip, recip_tab, s_bits, z_bits, zf, inv);
-    float hf[4] = {0.f, 0.f, 0.f, 0.f};
-    float e = 0.0f;
-    const float sf = __half2float(__ushort_as_half((unsigned short)s_bits));
-#pragma unroll
-    for (int p = 0; p < 8; ++p)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-#pragma clang fp contract(off)
-        const float t = (acc[p][j] - zf) * inv;
-        const float c = __builtin_rintf(__builtin_amdgcn_fmed3f(t, 0.0f, 3.0f));
-        hf[j] = __builtin_fmaf(c, (float)(1 << (2 * p)), hf[j]);
-        if constexpr (ERR) {
-          const float d = acc[p][j] - __builtin_fmaf(c, sf, zf);
-          e = __builtin_fmaf(d, d, e);
-        }
-      }
-    if constexpr (ERR) {
-      e += __shfl_xor(e, 16);
-      e += __shfl_xor(e, 32);
-    }
-    const uint32_t q0 = (uint32_t)hf[0], q1 = (uint32_t)hf[1], q2 = (uint32_t)hf[2], q3 = (uint32_t)hf[3];
-    return ApOut{q0 | (q1 << 16), q2 | (q3 << 16), s_bits | (z_bits << 16), e};
-  }
-  // group g = tiles 2g, 2g + 1: lane-local min/max of its eight values, then a reduce-scatter
-  // over the four lanes of the token (xor 32, then xor 16) leaves group hi's extremes in lane hi
-  float pmn[4], pmx[4];
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    float a = __builtin_elementwise_minimum(acc[2 * g][0], acc[2 * g][1]), b = __builtin_elementwise_maximum(acc[2 * g][0], acc[2 * g][1]);
-    a = __builtin_elementwise_minimum(a, __builtin_elementwise_minimum(acc[2 * g][2], acc[2 * g][3]));
-    b = __builtin_elementwise_maximum(b, __builtin_elementwise_maximum(acc[2 * g][2], acc[2 * g][3]));
-    a = __builtin_elementwise_minimum(a, __builtin_elementwise_minimum(acc[2 * g + 1][0], acc[2 * g + 1][1]));
-    b = __builtin_elementwise_maximum(b, __builtin_elementwise_maximum(acc[2 * g + 1][0], acc[2 * g + 1][1]));
-    pmn[g] = __builtin_elementwise_minimum(a, __builtin_elementwise_minimum(acc[2 * g + 1][2], acc[2 * g + 1][3]));
-    pmx[g] = __builtin_elementwise_maximum(b, __builtin_elementwise_maximum(acc[2 * g + 1][2], acc[2 * g + 1][3]));
-  }
-  float mn, mx;
-  {
-    // lanes 0-31 keep groups 0 and 1, lanes 32-63 groups 2 and 3: one swap of (group g, group
-    // g + 2) leaves both lanes' halves of the kept group in the swap's two results
-    const auto n0 = lane_swap32(pmn[0], pmn[2]), n1 = lane_swap32(pmn[1], pmn[3]);
-    const auto x0 = lane_swap32(pmx[0], pmx[2]), x1 = lane_swap32(pmx[1], pmx[3]);
-    const float kn0 = __builtin_elementwise_minimum(n0.a, n0.b), kn1 = __builtin_elementwise_minimum(n1.a, n1.b);
-    const float kx0 = __builtin_elementwise_maximum(x0.a, x0.b), kx1 = __builtin_elementwise_maximum(x1.a, x1.b);
-    // even rows (hi 0, 2) keep the first of the two, odd rows the second: the same with rows of 16
-    const auto n = lane_swap16(kn0, kn1), x = lane_swap16(kx0, kx1);
-    mn = __builtin_elementwise_minimum(n.a, n.b);
-    mx = __builtin_elementwise_maximum(x.a, x.b);
-  }
+template <bool ERR>
+__device__ __forceinline__ ApOut quantize_group(const ap_f16_t& v, float mn, float mx, float clip,
+                                                const float* recip_tab) {
   uint32_t s_bits, z_bits;
   float zf, inv;
   int2_group_params_fast(mn, mx, clip, recip_tab, s_bits, z_bits, zf, inv);
-  // every lane of the token gathers the four groups' zero and reciprocal scale: a swap of rows of
-  // 16 gives each lane (group 2 h1, group 2 h1 + 1), swaps of halves of 32 then give (group 0,
-  // group 2) and (group 1, group 3) in every lane
-  float zg[4], ig[4], sg[4];
-  const float sfo = __half2float(__ushort_as_half((unsigned short)s_bits));
-  auto gather4 = [](float v, float(&out)[4]) {
-    const LanePair r = lane_swap16(v, v);
-    const LanePair e = lane_swap32(r.a, r.a), o = lane_swap32(r.b, r.b);
-    out[0] = e.a;
-    out[1] = o.a;
-    out[2] = e.b;
-    out[3] = o.b;
-  };
-  gather4(zf, zg);
-  gather4(inv, ig);
-  if constexpr (ERR) gather4(sfo, sg);
-  // codes: half 4 hi + j of the token collects tiles p = 0..7 of register j at bits 2p, summed as
-  // exact small integers in fp32
-  float hf[4] = {0.f, 0.f, 0.f, 0.f};
+  const float sf = __half2float(__ushort_as_half((unsigned short)s_bits));
+  // v_cvt_pk_u8_f32 rounds to nearest even into a byte: value (a, b), bits 8 (2 (a % 2) + b / 2) + 4 (b % 2) +
+  // 2 (a / 2) of the word, goes to that byte of d[2 (b % 2) + a / 2], and the four words are shifted together
+  uint32_t d[4] = {0u, 0u, 0u, 0u};
   float e = 0.0f;
 #pragma unroll
-  for (int p = 0; p < 8; ++p)
+  for (int a = 0; a < 4; ++a)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int b = 0; b < 4; ++b) {
 #pragma clang fp contract(off)
-      const float t = (acc[p][j] - zg[p >> 1]) * ig[p >> 1];
-      const float c = __builtin_rintf(__builtin_amdgcn_fmed3f(t, 0.0f, 3.0f));
-      hf[j] = __builtin_fmaf(c, (float)(1 << (2 * p)), hf[j]);
+      const float x = v[4 * a + b];
+      const float t = __builtin_amdgcn_fmed3f((x - zf) * inv, 0.0f, 3.0f);
+      uint32_t& w = d[2 * (b & 1) + (a >> 1)];
+      w = __builtin_amdgcn_cvt_pk_u8_f32(t, 2 * (a & 1) + (b >> 1), w);
       if constexpr (ERR) {
-        const float d = acc[p][j] - __builtin_fmaf(c, sg[p >> 1], zg[p >> 1]);
-        e = __builtin_fmaf(d, d, e);
+        const float r = x - __builtin_fmaf(__builtin_rintf(t), sf, zf);
+        e = __builtin_fmaf(r, r, e);
       }
     }
   if constexpr (ERR) {
-    e += __shfl_xor(e, 16);
-    e += __shfl_xor(e, 32);
+    const LanePair p = lane_swap32(e, e);
+    e = p.a + p.b;
   }
-  const uint32_t q0 = (uint32_t)hf[0], q1 = (uint32_t)hf[1], q2 = (uint32_t)hf[2], q3 = (uint32_t)hf[3];
-  return ApOut{q0 | (q1 << 16), q2 | (q3 << 16), s_bits | (z_bits << 16), e};
+  return ApOut{(d[0] | (d[1] << 2)) | ((d[2] | (d[3] << 2)) << 4), s_bits | (z_bits << 16), e};
 }
 
-// Stores of one lane's ApOut into the record of its token's slot (skipped for slots out of range).
-// With one group per token (NG = 1) the four lanes of a token hold the same metadata; lane hi = 0
-// stores it.
-template <int NG>
-__device__ __forceinline__ void store_tile(const ApOut& o, int slot, const CacheView& cv, int h, int kv, int nslots,
-                                           int hi) {
-  using L = Rec<NG>;
-  if (slot >= 0 && slot < nslots) {
-    const int blk = slot >> 4, t = slot & 15;
-    uint8_t* rec = cv.pool + ((size_t)blk * cv.num_kv_heads + h) * L::kBytes;
-    const bool meta = NG == 4 || hi == 0;
-    const int g = NG == 4 ? hi : 0;
-    if (kv == 0) {
-      *reinterpret_cast<uint2*>(rec + kOffKCodes + 32 * t + 8 * hi) = make_uint2(o.w01, o.w23);
-      if (meta) *reinterpret_cast<uint32_t*>(rec + L::kOffKMeta + 4 * NG * t + 4 * g) = o.meta;
-    } else {
-      uint8_t* vc = rec + kOffVCodes + 32 * 4 * hi + 2 * t;
-      *reinterpret_cast<uint16_t*>(vc) = (uint16_t)o.w01;
-      *reinterpret_cast<uint16_t*>(vc + 32) = (uint16_t)(o.w01 >> 16);
-      *reinterpret_cast<uint16_t*>(vc + 64) = (uint16_t)o.w23;
-      *reinterpret_cast<uint16_t*>(vc + 96) = (uint16_t)(o.w23 >> 16);
-      if (meta) {
-        *reinterpret_cast<uint16_t*>(rec + L::kOffVScale + 32 * g + 2 * t) = (uint16_t)o.meta;
-        *reinterpret_cast<uint16_t*>(rec + L::kOffVZero + 32 * g + 2 * t) = (uint16_t)(o.meta >> 16);
-      }
-    }
+// extremes of a lane's 16 values and its partner's (lane ^ 32), NaN-propagating as the oracle's
+__device__ __forceinline__ void ap_extremes(const ap_f16_t& v, float& mn, float& mx) {
+  mn = mx = v[0];
+#pragma unroll
+  for (int r = 1; r < 16; ++r) {
+    mn = __builtin_elementwise_minimum(mn, v[r]);
+    mx = __builtin_elementwise_maximum(mx, v[r]);
   }
+  const LanePair n = lane_swap32(mn, mn), x = lane_swap32(mx, mx);
+  mn = __builtin_elementwise_minimum(n.a, n.b);
+  mx = __builtin_elementwise_maximum(x.a, x.b);
 }
 
 // Optional stages of the cache write. RoPE (with ROPE): the keys arrive pre-RoPE and each token is
@@ -269,254 +185,397 @@ __device__ __forceinline__ uint32_t f64_to_bf16_rne(double d) {
   return f32_to_bf16_rne(r);
 }
 
-// RoPE of one lane's slice of a token row in place: X[ks] holds channels 32 ks + 8 hi + e
-// (e = 0..7), so pairs (i, i + 64) are (X[ks][e], X[ks + 2][e]) for ks = 0, 1; cs points at the
-// token's table row.
-__device__ __forceinline__ void rope_lane(ap_bf16x8_t (&X)[4], const float* __restrict__ cs, int hi) {
+// Two RoPE pairs in fp32 with proof of their rounding: words a, b hold x_i, x_{i+1} and x_{i+64}, x_{i+65}. With
+// p = RN(x2 s) and y = RN(x1 c - p) (an FMA), |y - (x1 c - x2 s)| <= 2^-24 (|y| + |p|) for normal values, so with
+// E a little above that bound (and above 2^-120, which covers underflow) the exact value lies in [y - E, y + E];
+// when both ends round to the same bf16 value, so does the exact value (and its fp64 rounding, which lies between
+// them too). Otherwise, and for infinities and NaN (E is not below 2^100 then), `unsure` is set and the caller
+// takes fp64. About one word in twenty of a wave is unsure on N(0, 1) keys. Per pair 20 vector instructions
+// instead of about 50, with fp64 at half rate; the write is bound by the rows and the table it moves (without the
+// output rows 44 -> 30 us), so this shows only once those move well.
+struct RopeWord {
+  uint32_t a, b;
+  bool unsure;
+};
+__device__ __forceinline__ RopeWord rope_word(uint32_t a, uint32_t b, float c0, float c1, float s0, float s1) {
 #pragma clang fp contract(off)
-  float c[2][8], sn[2][8];
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+  constexpr float k = 0x1.2p-24f;
+  const float x1[2] = {__uint_as_float(a << 16), __uint_as_float(a & 0xFFFF0000u)};
+  const float x2[2] = {__uint_as_float(b << 16), __uint_as_float(b & 0xFFFF0000u)};
+  const float cc[2] = {c0, c1}, ss[2] = {s0, s1};
+  f2 lo1, hi1, lo2, hi2;
+  float emax = 0.0f;
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    const float4* cp = reinterpret_cast<const float4*>(cs + 32 * ks + 8 * hi);
-    const float4* sp = reinterpret_cast<const float4*>(cs + 64 + 32 * ks + 8 * hi);
-    const float4 c0 = cp[0], c1 = cp[1], s0 = sp[0], s1 = sp[1];
-    c[ks][0] = c0.x; c[ks][1] = c0.y; c[ks][2] = c0.z; c[ks][3] = c0.w;
-    c[ks][4] = c1.x; c[ks][5] = c1.y; c[ks][6] = c1.z; c[ks][7] = c1.w;
-    sn[ks][0] = s0.x; sn[ks][1] = s0.y; sn[ks][2] = s0.z; sn[ks][3] = s0.w;
-    sn[ks][4] = s1.x; sn[ks][5] = s1.y; sn[ks][6] = s1.z; sn[ks][7] = s1.w;
+  for (int i = 0; i < 2; ++i) {
+    const float p1 = x2[i] * ss[i], y1 = __builtin_fmaf(x1[i], cc[i], -p1);
+    const float p2 = x1[i] * ss[i], y2 = __builtin_fmaf(x2[i], cc[i], p2);
+    const float e1 = __builtin_fmaf(fabsf(p1), k, __builtin_fmaf(fabsf(y1), k, 0x1p-120f));
+    const float e2 = __builtin_fmaf(fabsf(p2), k, __builtin_fmaf(fabsf(y2), k, 0x1p-120f));
+    lo1[i] = y1 - e1;
+    hi1[i] = y1 + e1;
+    lo2[i] = y2 - e2;
+    hi2[i] = y2 + e2;
+    emax += e1 + e2;
   }
+  const uint32_t l1 = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo1, b2));
+  const uint32_t h1 = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi1, b2));
+  const uint32_t l2 = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo2, b2));
+  const uint32_t h2 = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi2, b2));
+  return RopeWord{l1, l2, ((l1 ^ h1) | (l2 ^ h2)) != 0u || !(emax < 0x1p100f)};
+}
+
+// RoPE of eight pairs in place: x0 holds channels 8 j .. 8 j + 7 of a token, x1 channels 64 + 8 j .., cs the eight
+// cosines then the eight sines.
+__device__ __forceinline__ void rope_pairs(ap_u4_t& x0, ap_u4_t& x1, const float (&cs)[16]) {
+#pragma clang fp contract(off)
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    uint4 a = __builtin_bit_cast(uint4, X[ks]), b = __builtin_bit_cast(uint4, X[ks + 2]);
-    uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t a = x0[q], b = x1[q];
+    const RopeWord r = rope_word(a, b, cs[2 * q], cs[2 * q + 1], cs[8 + 2 * q], cs[9 + 2 * q]);
+    uint32_t oa = r.a, ob = r.b;
+    if (__any(r.unsure)) {
+      // a wave whose bounds did not settle a rounding takes the word in fp64
+      oa = ob = 0u;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      uint32_t oa = 0u, ob = 0u;
-#pragma unroll
-      for (int hlf = 0; hlf < 2; ++hlf) {
-        const int e = 2 * q + hlf;
-        const double x1 = (double)__uint_as_float((aw[q] >> (16 * hlf)) << 16);
-        const double x2 = (double)__uint_as_float((bw[q] >> (16 * hlf)) << 16);
-        const double cc = (double)c[ks][e], ss = (double)sn[ks][e];
-        const double y1 = x1 * cc - x2 * ss;  // exact products, one rounding
-        const double y2 = x2 * cc + x1 * ss;
-        oa |= f64_to_bf16_rne(y1) << (16 * hlf);
-        ob |= f64_to_bf16_rne(y2) << (16 * hlf);
+      for (int i = 0; i < 2; ++i) {
+        const double u1 = (double)__uint_as_float((a >> (16 * i)) << 16), u2 = (double)__uint_as_float((b >> (16 * i)) << 16);
+        const double cc = (double)cs[2 * q + i], ss = (double)cs[8 + 2 * q + i];
+        const double y1 = u1 * cc - u2 * ss;  // exact products, one rounding
+        const double y2 = u2 * cc + u1 * ss;
+        oa |= f64_to_bf16_rne(y1) << (16 * i);
+        ob |= f64_to_bf16_rne(y2) << (16 * i);
       }
-      aw[q] = oa;
-      bw[q] = ob;
     }
-    X[ks] = __builtin_bit_cast(ap_bf16x8_t, make_uint4(aw[0], aw[1], aw[2], aw[3]));
-    X[ks + 2] = __builtin_bit_cast(ap_bf16x8_t, make_uint4(bw[0], bw[1], bw[2], bw[3]));
+    x0[q] = oa;
+    x1[q] = ob;
   }
 }
 
-// Each wave takes kApTiles consecutive 16-token tiles per step, so every R^T fragment read from
-// LDS feeds kApTiles products (two for long appends; one for short ones, which spreads the few
-// tiles over more waves).
-// LDS of one append work-group: R^T as three bf16 terms, then the reciprocal table.
-constexpr int kAppendLdsBytes = 3 * kHeadDim * kApRow * 2 + 1024 * 4;
+// LDS-DMA: lane i's bytes land at lds + 16 i (4 i). Issued through inline asm, so that the compiler's waits do
+// not count them (it would wait for all of them before any LDS read); vmcnt counts the wave's memory
+// operations in issue order.
+__device__ __forceinline__ void ap_dma16(const void* p, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(p) : "memory", "m0");
+}
+__device__ __forceinline__ void ap_dma4(const void* p, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(p) : "memory", "m0");
+}
 
-// One append work-group of kWaves waves: KV head h, K (kv = 0) or V (kv = 1), block bx of nbx
-// striding over the 16-token tiles; lds holds kAppendLdsBytes (16-byte aligned). Every thread of
-// the block must call it (it synchronizes once).
-// With ERR, err[(token * H + h) * 2 + kv] receives each token's squared reconstruction error.
-// With ROPE, opt carries the positions and table (keys only); opt.had selects the Hadamard rotation.
-template <int kApTiles, int kWaves, int NG, bool ERR = false, bool ROPE = false>
+// One append work-group (kApThreads threads): KV head h, K (kv = 0) or V (kv = 1), block bx of nbx striding over
+// the 32-token tiles. Every thread of the block must call it (it synchronizes). TERMS: 3 (dense R) or 1
+// (Hadamard). With ERR, err[(token * H + h) * 2 + kv] receives each token's squared reconstruction error. With
+// ROPE (keys only), opt carries the positions and table.
+template <int NG, bool ERR, bool ROPE, int TERMS>
+__device__ __forceinline__ void append_tiles(const CacheView& cv, const uint16_t* __restrict__ X,
+                                             const int32_t* __restrict__ slots, int n, const float* __restrict__ R,
+                                             const float* __restrict__ mu_rk, float clip, int bx, int nbx, int h, int kv,
+                                             ApLds& L, float* __restrict__ err, const ApOpts& opt) {
+  using Lay = Rec<NG>;
+  const int H = cv.num_kv_heads, tid = threadIdx.x, l = tid & 63;
+  const int g = __builtin_amdgcn_readfirstlane(tid >> 6);  // the wave's group
+  const int tl = l & 31, hf = l >> 5;                      // its token and half in the products
+  const int tt = tid >> 3, j = tid & 7;                    // the thread's token and piece in loads and stores
+  const int tiles = (n + kApTok - 1) / kApTok, cnt = (tiles - bx + nbx - 1) / nbx;
+
+  // ---- loads of tile i (of this block) into register set p; past the end: the last token, slot -1
+  struct Pre {
+    ap_u4_t x0, x1;
+    int slot;
+    float cs[16];
+    bool pos_ok;
+  };
+  Pre pre[kApDepth];
+  int pos_next = 0;
+  auto token = [&](int i) { return (bx + i * nbx) * kApTok + tt; };
+  // pointers of the next tile to load; past the end they stay on a row already read
+  const int hop = nbx * kApTok;
+  int tok_ld = token(0);
+  const uint16_t* row_ld = X + ((size_t)min(tok_ld, n - 1) * H + h) * kHeadDim + 8 * j;
+  const int32_t* slot_ld = slots + min(tok_ld, n - 1);
+  const int32_t* pos_ld = ROPE ? opt.pos + min(tok_ld, n - 1) : nullptr;
+  auto load = [&](Pre& p) {
+    const bool more = tok_ld + hop < n;
+    if constexpr (ROPE) {
+      // the position was fetched a step ago; the next one goes first, so that it is the oldest of this step's loads
+      const int pos = pos_next;
+      pos_ld += more ? hop : 0;
+      pos_next = *pos_ld;
+      p.pos_ok = pos >= 0 && pos < opt.max_pos;
+      const float4* c = reinterpret_cast<const float4*>(opt.cos_sin + (size_t)(p.pos_ok ? pos : 0) * kHeadDim + 8 * j);
+      const float4 c0 = c[0], c1 = c[1], s0 = c[16], s1 = c[17];
+      p.cs[0] = c0.x, p.cs[1] = c0.y, p.cs[2] = c0.z, p.cs[3] = c0.w;
+      p.cs[4] = c1.x, p.cs[5] = c1.y, p.cs[6] = c1.z, p.cs[7] = c1.w;
+      p.cs[8] = s0.x, p.cs[9] = s0.y, p.cs[10] = s0.z, p.cs[11] = s0.w;
+      p.cs[12] = s1.x, p.cs[13] = s1.y, p.cs[14] = s1.z, p.cs[15] = s1.w;
+    }
+    p.x0 = *reinterpret_cast<const ap_u4_t*>(row_ld);
+    p.x1 = *reinterpret_cast<const ap_u4_t*>(row_ld + 64);
+    p.slot = *slot_ld;
+    row_ld += more ? (size_t)hop * H * kHeadDim : 0;
+    slot_ld += more ? hop : 0;
+    tok_ld += hop;
+  };
+  // register set p (tile i) into LDS buffer i % 2; returns the thread's slot (-1: not stored)
+  auto consume = [&](int i, Pre& p) {
+    const int tok = token(i);
+    int slot = tok < n ? p.slot : -1;
+    if constexpr (ROPE) {
+      rope_pairs(p.x0, p.x1, p.cs);
+      if (!p.pos_ok) slot = -1;
+      if (opt.k_out && p.pos_ok && tok < n) {
+        uint16_t* o = opt.k_out + ((size_t)tok * H + h) * kHeadDim + 8 * j;
+        *reinterpret_cast<ap_u4_t*>(o) = p.x0;
+        *reinterpret_cast<ap_u4_t*>(o + 64) = p.x1;
+      }
+    }
+    uint8_t* x = L.x[i & 1] + 256 * tt;
+    *reinterpret_cast<ap_u4_t*>(x + 16 * (j ^ (tt & 15))) = p.x0;
+    *reinterpret_cast<ap_u4_t*>(x + 16 * ((j + 8) ^ (tt & 15))) = p.x1;
+    return slot;
+  };
+  const int nslots = cv.num_blocks * kBlock;
+  // packed stores of the tile in exchange buffer i % 2: thread (token tt, halves 2 j and 2 j + 1)
+  auto finish = [&](int i, int slot) {
+    const int s_hf = j >> 2, q = j & 3, buf = i & 1;
+    const uint4 w = *reinterpret_cast<const uint4*>(&L.words[buf][tt][s_hf][0]);
+    const uint32_t m = L.meta[buf][tt][NG == 4 ? q : 0];
+    // byte q of the four groups' words, group g in byte g
+    const uint32_t sel = 0x0C0C0400u + 0x0101u * q;
+    const uint32_t lo = __builtin_amdgcn_perm(w.y, w.x, sel), hi = __builtin_amdgcn_perm(w.w, w.z, sel);
+    const uint32_t b4 = lo | (hi << 16);
+    uint32_t e = b4 & 0x0F0F0F0Fu, o = (b4 >> 4) & 0x0F0F0F0Fu;  // halves 2 j, 2 j + 1: nibble g in byte g
+    e = (e | (e >> 4)) & 0x00FF00FFu;
+    o = (o | (o >> 4)) & 0x00FF00FFu;
+    e = (e | (e >> 8)) & 0xFFFFu;
+    o = (o | (o >> 8)) & 0xFFFFu;
+    float es = 0.0f;
+    if constexpr (ERR) es = (L.err[buf][tt][0] + L.err[buf][tt][1]) + (L.err[buf][tt][2] + L.err[buf][tt][3]);
+    if (slot >= 0 && slot < nslots) {
+      const int t = slot & 15;
+      uint8_t* rec = cv.pool + ((size_t)(slot >> 4) * H + h) * Lay::kBytes;
+      if (kv == 0) {
+        *reinterpret_cast<uint32_t*>(rec + kOffKCodes + 32 * t + 4 * j) = e | (o << 16);
+        if (j < NG) *reinterpret_cast<uint32_t*>(rec + Lay::kOffKMeta + 4 * NG * t + 4 * j) = m;
+      } else {
+        uint8_t* vc = rec + kOffVCodes + 64 * j + 2 * t;
+        *reinterpret_cast<uint16_t*>(vc) = (uint16_t)e;
+        *reinterpret_cast<uint16_t*>(vc + 32) = (uint16_t)o;
+        if (q < NG)
+          *reinterpret_cast<uint16_t*>(rec + (s_hf ? Lay::kOffVZero : Lay::kOffVScale) + 32 * q + 2 * t) =
+              (uint16_t)(s_hf ? m >> 16 : m);
+      }
+    }
+    if constexpr (ERR) {
+      const int tok = token(i);
+      if (j == 0 && tok < n) err[((size_t)tok * H + h) * 2 + kv] = es;
+    }
+  };
+
+  // without RoPE the tiles go straight to LDS: wave g fetches tokens 8 g .. + 7 (two operations) and its threads' slots
+  const int t_dma = 8 * g + (l >> 4);
+  const uint16_t* row_dma[2];
+  int tok_dma[2];
+  if constexpr (!ROPE) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int t = t_dma + 4 * u;
+      tok_dma[u] = bx * kApTok + t;
+      row_dma[u] = X + ((size_t)min(tok_dma[u], n - 1) * H + h) * kHeadDim + 8 * ((l & 15) ^ (t & 15));
+    }
+  }
+  const uint32_t x_lds = (uint32_t)(uintptr_t)&L.x[0][0] + 2048 * g, slot_lds = (uint32_t)(uintptr_t)&L.slot[0][0] + 256 * g;
+  constexpr int kDma = 3;  // operations per tile and wave
+  auto dma = [&](int stage) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      ap_dma16(row_dma[u], x_lds + (uint32_t)(stage * kApTok * 256 + 1024 * u));
+      row_dma[u] += tok_dma[u] + hop < n ? (size_t)hop * H * kHeadDim : 0;
+      tok_dma[u] += hop;
+    }
+    ap_dma4(slot_ld, slot_lds + (uint32_t)(stage * kApThreads * 4));
+    slot_ld += tok_ld + hop < n ? hop : 0;
+    tok_ld += hop;
+  };
+  if constexpr (ROPE) {
+    pos_next = *pos_ld;
+#pragma unroll
+    for (int d = 0; d < kApDepth; ++d) load(pre[d]);
+  } else {
+#pragma unroll
+    for (int s = 0; s < kApStages - 1; ++s) dma(s);
+  }
+
+  // ---- the wave's rows of R^T: lane (row l % 32, 8 hf ..) of k step ks holds R[16 ks + 8 hf + e][channel]
+  ap_bf16x8_t A[TERMS][8];
+  {
+    const int a = tl >> 3, ch = 32 * g + 16 * (a >> 1) + 8 * ((tl >> 2) & 1) + 4 * (a & 1) + (tl & 3);
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      uint32_t t16[TERMS][8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int k = 16 * ks + 8 * hf + e;
+        if constexpr (TERMS == 1) {
+          t16[0][e] = (__builtin_popcount(k & ch) & 1) ? 0xBF80u : 0x3F80u;
+        } else {
+          const float r = R[k * kHeadDim + ch];
+          const uint32_t b0 = __float_as_uint(r) & 0xFFFF0000u;
+          const float r1 = r - __uint_as_float(b0);
+          const uint32_t b1 = __float_as_uint(r1) & 0xFFFF0000u;
+          t16[0][e] = b0 >> 16;
+          t16[1][e] = b1 >> 16;
+          t16[2][e] = __float_as_uint(r1 - __uint_as_float(b1)) >> 16;
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < TERMS; ++t)
+        A[t][ks] = __builtin_bit_cast(ap_bf16x8_t, ap_u4_t{t16[t][0] | (t16[t][1] << 16), t16[t][2] | (t16[t][3] << 16),
+                                                           t16[t][4] | (t16[t][5] << 16), t16[t][6] | (t16[t][7] << 16)});
+    }
+  }
+  for (int m = tid; m < 1024; m += kApThreads) L.recip[m] = 1.0f / (1.0f + (float)m * 0x1p-10f);
+  if (tid < kHeadDim) L.sub[tid] = kv == 0 ? -mu_rk[(size_t)h * kHeadDim + tid] : 0.0f;
+  auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+  int slot = -1, slot_prev = -1, slot_done = -1;  // of tiles i, i - 1 and i - 2
+  if constexpr (ROPE) slot = consume(0, pre[0]);
+  barrier();
+
+  // ---- step i with its registers pre[i % kApDepth]: the products of tile i beside the quantizer of tile i - 1
+  // (prev: its rotated values), which depend on nothing in common; both in one block without branches, so that
+  // the schedule below can alternate them
+  ap_f16_t acc[2];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[1][r] = 0.0f;
+  auto quantize = [&](int i, const ap_f16_t& prev) {
+    float mn, mx;
+    ap_extremes(prev, mn, mx);
+    if constexpr (NG == 1) {
+      if (hf == 0) *reinterpret_cast<float2*>(L.ext[tl][g]) = make_float2(mn, mx);
+      barrier();
+      const float4 e0 = *reinterpret_cast<const float4*>(L.ext[tl][0]), e1 = *reinterpret_cast<const float4*>(L.ext[tl][2]);
+      mn = __builtin_elementwise_minimum(__builtin_elementwise_minimum(e0.x, e0.z), __builtin_elementwise_minimum(e1.x, e1.z));
+      mx = __builtin_elementwise_maximum(__builtin_elementwise_maximum(e0.y, e0.w), __builtin_elementwise_maximum(e1.y, e1.w));
+    }
+    const ApOut o = quantize_group<ERR>(prev, mn, mx, clip, L.recip);
+    L.words[i & 1][tl][hf][g] = o.word;
+    L.meta[i & 1][tl][g] = o.meta;  // both halves hold the same
+    if constexpr (ERR) L.err[i & 1][tl][g] = o.err;
+  };
+  auto product = [&](const uint8_t* tile, ap_f16_t& acc) {
+    const uint8_t* x = tile + 256 * tl;
+    auto sub = [&](int r4) {  // the lane's channels: 16 (a / 2) + 8 hf + 4 (a % 2) + b of group g
+      return *reinterpret_cast<const float4*>(&L.sub[32 * g + 16 * (r4 >> 1) + 8 * hf + 4 * (r4 & 1)]);
+    };
+    ap_bf16x8_t B[8];
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks)
+      B[ks] = *reinterpret_cast<const ap_bf16x8_t*>(x + 16 * ((2 * ks + hf) ^ (tl & 15)));
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const float4 s = TERMS == 1 ? make_float4(0.f, 0.f, 0.f, 0.f) : sub(a);
+      acc[4 * a] = s.x, acc[4 * a + 1] = s.y, acc[4 * a + 2] = s.z, acc[4 * a + 3] = s.w;
+    }
+#pragma unroll
+    for (int t = TERMS - 1; t >= 0; --t)  // smallest term first
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[t][ks], B[ks], acc, 0, 0, 0);
+    if constexpr (TERMS == 1) {
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const float4 s = sub(a);
+        acc[4 * a] = __builtin_fmaf(acc[4 * a], kHadScale, s.x);
+        acc[4 * a + 1] = __builtin_fmaf(acc[4 * a + 1], kHadScale, s.y);
+        acc[4 * a + 2] = __builtin_fmaf(acc[4 * a + 2], kHadScale, s.z);
+        acc[4 * a + 3] = __builtin_fmaf(acc[4 * a + 3], kHadScale, s.w);
+      }
+    }
+  };
+  auto schedule = [] {
+#pragma unroll
+    for (int m = 0; m < 8 * TERMS; ++m) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                    // one product
+      __builtin_amdgcn_sched_group_barrier(0x002, TERMS == 1 ? 18 : 6, 0);  // vector instructions beside it
+    }
+  };
+  if constexpr (ROPE) {
+    // cur: where tile i's values go; prv: tile i - 1's; p: the registers of tile i (consumed), refilled with
+    // tile i + kApDepth; pn: those of tile i + 1
+    auto step = [&](int i, Pre& p, Pre& pn, ap_f16_t& cur, const ap_f16_t& prv) {
+      if (i > 1) finish(i - 2, slot_done);
+      load(p);
+      product(L.x[i & 1], cur);
+      quantize(i - 1, prv);  // of zeros in the first step, into a buffer that is rewritten before it is read
+      schedule();
+      slot_done = slot_prev;
+      slot_prev = slot;
+      slot = consume(i + 1, pn);
+      barrier();
+    };
+    static_assert(kApDepth % 2 == 0, "the register sets and the accumulators repeat together");
+    for (int i0 = 0; i0 < cnt; i0 += kApDepth) {
+#pragma unroll
+      for (int d = 0; d < kApDepth; ++d)
+        if (i0 + d < cnt) step(i0 + d, pre[d], pre[(d + 1) % kApDepth], acc[d & 1], acc[1 - (d & 1)]);
+    }
+  } else {
+    int stage = 0;  // of tile i
+    auto step = [&](int i, ap_f16_t& cur, const ap_f16_t& prv) {
+      // this wave's operations of tile i are done when at most those of the kApStages - 2 tiles after it are
+      // outstanding (stores among them only make the wait longer); the barrier extends that to every
+      // wave's, and says that tile i - 1's stage and the exchange buffers of tile i - 3 are free
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kDma * (kApStages - 2)) : "memory");
+      slot_done = slot_prev;
+      slot_prev = slot;
+      const int sl = L.slot[stage][tid];
+      slot = token(i) < n ? sl : -1;
+      if (i > 1) finish(i - 2, slot_done);
+      dma(stage == 0 ? kApStages - 1 : stage - 1);
+      product(L.x[stage], cur);
+      quantize(i - 1, prv);
+      schedule();
+      stage = stage + 1 == kApStages ? 0 : stage + 1;
+    };
+    for (int i0 = 0; i0 < cnt; i0 += 2) {
+      step(i0, acc[0], acc[1]);
+      if (i0 + 1 < cnt) step(i0 + 1, acc[1], acc[0]);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the tiles fetched past the end
+    slot_done = slot_prev;
+    slot_prev = slot;
+    barrier();
+  }
+  if (cnt > 1) finish(cnt - 2, slot_done);
+  if (cnt & 1)
+    quantize(cnt - 1, acc[0]);
+  else
+    quantize(cnt - 1, acc[1]);
+  barrier();
+  finish(cnt - 1, slot_prev);
+}
+
+// One append work-group with the rotation its options ask for.
+template <int NG, bool ERR = false, bool ROPE = false>
 __device__ __forceinline__ void append_block(const CacheView& cv, const uint16_t* __restrict__ k,
                                              const uint16_t* __restrict__ v, const int32_t* __restrict__ slots,
                                              int n, const float* __restrict__ R_k, const float* __restrict__ R_v,
                                              const float* __restrict__ mu_rk, float clip_k, float clip_v, int bx,
-                                             int nbx, int h, int kv, uint8_t* lds, float* __restrict__ err = nullptr,
+                                             int nbx, int h, int kv, ApLds& L, float* __restrict__ err = nullptr,
                                              const ApOpts& opt = ApOpts{}) {
-  uint16_t(*rt)[kHeadDim][kApRow] = reinterpret_cast<uint16_t(*)[kHeadDim][kApRow]>(lds);  // [term][c][i] = R[i][c]
-  float* recip_tab = reinterpret_cast<float*>(lds + 3 * kHeadDim * kApRow * 2);  // RN(1 / (1 + m / 1024))
-  const int H = cv.num_kv_heads, tid = threadIdx.x;
+  const uint16_t* X = kv == 0 ? k : v;
+  const float clip = kv == 0 ? clip_k : clip_v;
   const bool had = ((opt.had >> kv) & 1) != 0;
   const float* R = had ? nullptr : (kv == 0 ? R_k : R_v) + (size_t)h * kHeadDim * kHeadDim;
-  const bool rope = ROPE && kv == 0;
-  const int w = tid >> 6, l = tid & 63, lo = l & 15, hi = l >> 4;
-  const uint16_t* X = kv == 0 ? k : v;
-  constexpr int kStep = 16 * kApTiles;  // tokens per wave step
-  // the first step's operands and slots are fetched before R, so their latency overlaps R's
-  const int step0 = bx * kWaves + w;
-  ap_bf16x8_t X8[kApTiles][4];
-  int slot[kApTiles], pos[kApTiles];
-#pragma unroll
-  for (int u = 0; u < kApTiles; ++u) {
-    const int tok = step0 * kStep + 16 * u + lo, tc = min(tok, n - 1);
-    const uint16_t* xrow = X + ((size_t)tc * H + h) * kHeadDim + 8 * hi;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) X8[u][ks] = *reinterpret_cast<const ap_bf16x8_t*>(xrow + 32 * ks);
-    slot[u] = slots[tc];
-    if (tok >= n) slot[u] = -1;
-    pos[u] = rope ? opt.pos[tc] : 0;
-  }
-  if (had) {
-    // H^T = H: thread (c, i0) writes entries (i0 .. i0 + 7, c) = (-1)^popcount(i & c) as bf16 +-1
-    constexpr int kIb = kWaves / 2;
-    const int c = tid & 127, ib = tid >> 7;
-#pragma unroll
-    for (int u = 0; u < 16 / kIb; ++u) {
-      const int i0 = 8 * (ib + kIb * u);
-      uint32_t t16[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) t16[q] = (__builtin_popcount((i0 + q) & c) & 1) ? 0xBF80u : 0x3F80u;
-      *reinterpret_cast<uint4*>(&rt[0][c][i0]) =
-          make_uint4(t16[0] | (t16[1] << 16), t16[2] | (t16[3] << 16), t16[4] | (t16[5] << 16), t16[6] | (t16[7] << 16));
-    }
+  if (ROPE && kv == 0) {
+    if (had)
+      append_tiles<NG, ERR, ROPE, 1>(cv, X, slots, n, R, mu_rk, clip, bx, nbx, h, kv, L, err, opt);
+    else
+      append_tiles<NG, ERR, ROPE, 3>(cv, X, slots, n, R, mu_rk, clip, bx, nbx, h, kv, L, err, opt);
+  } else if (had) {
+    append_tiles<NG, ERR, false, 1>(cv, X, slots, n, R, mu_rk, clip, bx, nbx, h, kv, L, err, opt);
   } else {
-    // R^T as three bf16 terms: thread (c, i0) reads R[i0 .. i0 + 7][c] (coalesced over c) and
-    // splits each value by truncation: r = t0 + t1 + t2 exactly (t0 and t1 take the leading 8
-    // significant bits of r and of r - t0, the remainder has at most 8 left), then writes one
-    // 16-byte row piece per term (conflict-free)
-    constexpr int kIb = kWaves / 2;  // threads per channel c
-    const int c = tid & 127, ib = tid >> 7;
-#pragma unroll
-    for (int u = 0; u < 16 / kIb; ++u) {
-      const int i0 = 8 * (ib + kIb * u);
-      uint32_t t16[3][8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const float r = R[(i0 + q) * kHeadDim + c];
-        const uint32_t b0 = __float_as_uint(r) & 0xFFFF0000u;
-        const float r1 = r - __uint_as_float(b0);
-        const uint32_t b1 = __float_as_uint(r1) & 0xFFFF0000u;
-        const float r2 = r1 - __uint_as_float(b1);
-        t16[0][q] = b0 >> 16;
-        t16[1][q] = b1 >> 16;
-        t16[2][q] = __float_as_uint(r2) >> 16;
-      }
-#pragma unroll
-      for (int term = 0; term < 3; ++term)
-        *reinterpret_cast<uint4*>(&rt[term][c][i0]) =
-            make_uint4(t16[term][0] | (t16[term][1] << 16), t16[term][2] | (t16[term][3] << 16),
-                       t16[term][4] | (t16[term][5] << 16), t16[term][6] | (t16[term][7] << 16));
-    }
-  }
-  for (int m = tid; m < 1024; m += 64 * kWaves) recip_tab[m] = 1.0f / (1.0f + (float)m * 0x1p-10f);
-  __syncthreads();
-  // lane (token lo, hi) holds channels 16 p + 4 hi + j of its token in register j of tile p
-  ap_f4_t sub[8];
-#pragma unroll
-  for (int p = 0; p < 8; ++p)
-    sub[p] = kv == 0 ? -*reinterpret_cast<const ap_f4_t*>(mu_rk + (size_t)h * kHeadDim + 16 * p + 4 * hi)
-                     : ap_f4_t{0.f, 0.f, 0.f, 0.f};
-  const float clip = kv == 0 ? clip_k : clip_v;
-  const int nslots = cv.num_blocks * kBlock;
-  // software pipeline over the wave's steps: the next step's operands and slots are fetched while
-  // this one is computed (indexes clamped, so the fetch past the last step stays in bounds)
-  const int sstride = nbx * kWaves;
-  for (int st = step0; st * kStep < n; st += sstride) {
-    if (rope) {
-      // this step's keys become post-RoPE rows; a position outside the table skips the token
-#pragma unroll
-      for (int u = 0; u < kApTiles; ++u) {
-        const int tok = st * kStep + 16 * u + lo;
-        const bool ok = pos[u] >= 0 && pos[u] < opt.max_pos;
-        if (!ok) slot[u] = -1;
-        rope_lane(X8[u], opt.cos_sin + (size_t)(ok ? pos[u] : 0) * kHeadDim, hi);
-        if (opt.k_out && ok && tok < n) {
-          uint16_t* orow = opt.k_out + ((size_t)tok * H + h) * kHeadDim + 8 * hi;
-#pragma unroll
-          for (int ks = 0; ks < 4; ++ks) *reinterpret_cast<ap_bf16x8_t*>(orow + 32 * ks) = X8[u][ks];
-        }
-      }
-    }
-    ap_bf16x8_t Xn[kApTiles][4];
-    int slotn[kApTiles], posn[kApTiles];
-#pragma unroll
-    for (int u = 0; u < kApTiles; ++u) {
-      const int tok = (st + sstride) * kStep + 16 * u + lo, tc = min(tok, n - 1);
-      const uint16_t* xrow = X + ((size_t)tc * H + h) * kHeadDim + 8 * hi;
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) Xn[u][ks] = *reinterpret_cast<const ap_bf16x8_t*>(xrow + 32 * ks);
-      slotn[u] = slots[tc];
-      posn[u] = rope ? opt.pos[tc] : 0;
-    }
-    ap_f4_t acc[kApTiles][8];  // start at - mu R_K (keys) or 0 (values); 0 for the Hadamard product
-#pragma unroll
-    for (int u = 0; u < kApTiles; ++u)
-#pragma unroll
-      for (int p = 0; p < 8; ++p) acc[u][p] = had ? ap_f4_t{0.f, 0.f, 0.f, 0.f} : sub[p];
-    // the R^T fragments are the same for every step: an opaque offset keeps the compiler from
-    // hoisting all 96 of them into registers (which would cap occupancy at one wave per SIMD)
-    int boff = (lo * kApRow + 8 * hi) * 2;
-    asm volatile("" : "+v"(boff));
-    const uint8_t* rb = reinterpret_cast<const uint8_t*>(&rt[0][0][0]) + boff;
-    // fragment f = (term 2 - f / 32, k-step (f / 8) % 4, m-tile f % 8): smallest term first. The
-    // LDS reads run kApDepth fragments ahead of the matrix cores (the schedule is pinned below).
-    auto frag = [&](int f) {
-      const int term = 2 - f / 32, ks = (f / 8) % 4, p = f % 8;
-      return *reinterpret_cast<const ap_bf16x8_t*>(rb + ((term * kHeadDim + 16 * p) * kApRow + 32 * ks) * 2);
-    };
-    // fragments F0 .. 95: all three terms (F0 = 0) or the Hadamard's single +-1 term (F0 = 64)
-    auto mfma_pass = [&](auto f0_tag) {
-      constexpr int F0 = decltype(f0_tag)::value;
-      ap_bf16x8_t fr[kApDepth];
-#pragma unroll
-      for (int f = 0; f < kApDepth; ++f) fr[f] = frag(F0 + f);
-#pragma unroll
-      for (int f = F0; f < 96; ++f) {
-        const ap_bf16x8_t a = fr[(f - F0) % kApDepth];
-        const int ks = (f / 8) % 4, p = f % 8;
-#pragma unroll
-        for (int u = 0; u < kApTiles; ++u)
-          acc[u][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, X8[u][ks], acc[u][p], 0, 0, 0);
-        if (f + kApDepth < 96) fr[(f - F0) % kApDepth] = frag(f + kApDepth);
-      }
-#pragma unroll
-      for (int f = 0; f < kApDepth; ++f) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
-#pragma unroll
-      for (int f = F0; f < 96; ++f) {
-        __builtin_amdgcn_sched_group_barrier(0x008, kApTiles, 0);  // MFMA
-        if (f + kApDepth < 96) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
-    };
-    // a wave in its matrix-core phase is issued first: the other wave of the SIMD fills the gaps
-    // between its products with quantizer instructions
-    __builtin_amdgcn_s_setprio(1);
-    if (had) {
-      mfma_pass(std::integral_constant<int, 64>{});
-#pragma unroll
-      for (int u = 0; u < kApTiles; ++u)
-#pragma unroll
-        for (int p = 0; p < 8; ++p)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[u][p][j] = __builtin_fmaf(acc[u][p][j], kHadScale, sub[p][j]);
-    } else {
-      mfma_pass(std::integral_constant<int, 0>{});
-    }
-    __builtin_amdgcn_s_setprio(0);
-    ApOut out[kApTiles];
-#pragma unroll
-    for (int u = 0; u < kApTiles; ++u) out[u] = quantize_tile<NG, ERR>(acc[u], clip, recip_tab, lo, hi);
-    // the next step's loads are waited for here, before this step's stores: a wait placed after
-    // the (lane-conditional) stores would also wait for the stores to complete
-#pragma unroll
-    for (int u = 0; u < kApTiles; ++u) {
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) asm volatile("" : "+v"(Xn[u][ks])::"memory");
-      asm volatile("" : "+v"(slotn[u])::"memory");
-      if (rope) asm volatile("" : "+v"(posn[u])::"memory");
-    }
-#pragma unroll
-    for (int u = 0; u < kApTiles; ++u) store_tile<NG>(out[u], slot[u], cv, h, kv, nslots, hi);
-    if constexpr (ERR) {
-#pragma unroll
-      for (int u = 0; u < kApTiles; ++u) {
-        const int tok = st * kStep + 16 * u + lo;
-        if (hi == 0 && tok < n) err[((size_t)tok * H + h) * 2 + kv] = out[u].err;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kApTiles; ++u) {
-      const int tok = (st + sstride) * kStep + 16 * u + lo;
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) X8[u][ks] = Xn[u][ks];
-      slot[u] = tok < n ? slotn[u] : -1;
-      pos[u] = posn[u];
-    }
+    append_tiles<NG, ERR, false, 3>(cv, X, slots, n, R, mu_rk, clip, bx, nbx, h, kv, L, err, opt);
   }
 }
 

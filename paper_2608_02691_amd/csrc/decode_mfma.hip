@@ -94,7 +94,7 @@ __device__ __forceinline__ int seq_len_m(const DecodeArgs& a, int b) {
 // see the scan below). Constants: -sum_k A_k per row (accumulator start), sum_{k in g} q'_jk (for the
 // zero term) and 1/sigma. sigma comes from the row's norm, which bounds every |q'_c| (R_K orthogonal):
 // sigma |q'|_2 < 512, so every A value stays below 2^15 at the largest code factor 2^6.
-// One block serves KV head h of kQpSeqs sequences and 128 / SPLIT channels of q' (whole groups:
+// One block serves KV head h of kQpSeqs sequences and 128 / kQpSplit channels of q' (whole groups:
 // the operand block of group g and the group's constants only need its channels): those columns of
 // R_K[h] go into LDS as the B operand of a bf16 matrix-core product (split into two bf16 terms, as in
 // the cache write: error below 2^-17 |R|); the query rows are exact in bf16. Rows s * 8 + jj = query
@@ -103,17 +103,15 @@ constexpr int kQpSeqs = 8;
 constexpr int kQpRow = 136;   // bf16 per LDS row of R^T (128 + 8 pad: conflict-free 16-byte reads)
 typedef __bf16 qp_bf16x8_t __attribute__((ext_vector_type(8)));
 
-// LDS of the query-operand role with SPLIT blocks per (KV head, sequences): the block's columns of
-// R^T as bf16 hi / lo, its q' columns, the per-row scale (the largest size, SPLIT = 1).
-constexpr int qp_lds_bytes(int split) {
-  return 2 * (kHeadDim / split) * kQpRow * 2 + 8 * kQpSeqs * (kHeadDim / split + 4) * 4 + 8 * kQpSeqs * 4;
-}
-constexpr int kQpLdsBytes = qp_lds_bytes(1);
-static_assert(qp_lds_bytes(4) >= 512 * 4, "the page-prefix block's two 256-entry scans fit the query role's LDS");
+// The query role runs as four blocks per (KV head, 8 sequences), one per 32-channel group of q' (shorter chains
+// than one block of all groups). LDS: the block's columns of R^T as bf16 hi / lo, its q' columns, the row scales.
+constexpr int kQpSplit = 4;
+constexpr int kQpLdsBytes =
+    2 * (kHeadDim / kQpSplit) * kQpRow * 2 + 8 * kQpSeqs * (kHeadDim / kQpSplit + 4) * 4 + 8 * kQpSeqs * 4;
+static_assert(kQpLdsBytes >= 512 * 4, "the page-prefix block's two 256-entry scans fit the query role's LDS");
 
-template <int SPLIT>
 __device__ void qprep_block(const DecodeArgs& a, int blk, bool wide, uint8_t* lds) {
-  constexpr int kQpSplit = SPLIT, kQpCols = kHeadDim / SPLIT;
+  constexpr int kQpCols = kHeadDim / kQpSplit;
   uint16_t(*Rt)[kQpCols][kQpRow] = reinterpret_cast<uint16_t(*)[kQpCols][kQpRow]>(lds);  // [hi, lo][c][k] = R[k][32 g + c]
   float(*qb)[kQpCols + 4] = reinterpret_cast<float(*)[kQpCols + 4]>(lds + 2 * kQpCols * kQpRow * 2);  // q' rows
   float* sig = reinterpret_cast<float*>(lds + 2 * kQpCols * kQpRow * 2 + 8 * kQpSeqs * (kQpCols + 4) * 4);
@@ -818,31 +816,28 @@ __device__ void page_list_block(const DecodeArgs& a, int b, int p0, uint8_t* lds
 // per sequence). Lower block ids are dispatched first. The roles share one LDS buffer.
 constexpr int kPrepLdsBytes = kAppendLdsBytes > kQpLdsBytes ? kAppendLdsBytes : kQpLdsBytes;
 
-// AP: the launch carries append blocks (their LDS sets the block's size; without them the roles
-// below fit several blocks per CU).
-// The query role runs as one block per (KV head, 8 sequences) beside append blocks (whose LDS allows
-// one block per CU: fewer blocks keep the launch in one round) and as four (one per 32-channel group
-// of q', shorter chains) otherwise.
-constexpr int qp_split(bool ap) { return ap ? 1 : 4; }
+// AP: the launch carries append blocks.
 template <bool AP>
 __global__ __launch_bounds__(256) void qprep_kernel(DecodeArgs a, int wide, int nq, int nseg, AppendArgs ap, int nap) {
-  __shared__ __attribute__((aligned(16))) uint8_t lds[AP ? kPrepLdsBytes : qp_lds_bytes(qp_split(false))];
+  __shared__ __attribute__((aligned(16))) uint8_t lds[AP ? kPrepLdsBytes : kQpLdsBytes];
   int blk = blockIdx.x;
   if (AP && blk < nap) {
     const int bx = blk % ap.nbx, r = blk / ap.nbx;
     if (ap.cv.groups == 1)
-      append_block<1, 4, 1>(ap.cv, ap.k, ap.v, ap.slots, ap.n, ap.R_k, ap.R_v, ap.mu_rk, ap.clip_k, ap.clip_v, bx,
-                            ap.nbx, r % ap.cv.num_kv_heads, r / ap.cv.num_kv_heads, lds);
+      append_block<1>(ap.cv, ap.k, ap.v, ap.slots, ap.n, ap.R_k, ap.R_v, ap.mu_rk, ap.clip_k, ap.clip_v, bx,
+                            ap.nbx, r % ap.cv.num_kv_heads, r / ap.cv.num_kv_heads,
+                      *reinterpret_cast<ApLds*>(lds));
     else
-      append_block<1, 4, 4>(ap.cv, ap.k, ap.v, ap.slots, ap.n, ap.R_k, ap.R_v, ap.mu_rk, ap.clip_k, ap.clip_v, bx,
-                            ap.nbx, r % ap.cv.num_kv_heads, r / ap.cv.num_kv_heads, lds);
+      append_block<4>(ap.cv, ap.k, ap.v, ap.slots, ap.n, ap.R_k, ap.R_v, ap.mu_rk, ap.clip_k, ap.clip_v, bx,
+                            ap.nbx, r % ap.cv.num_kv_heads, r / ap.cv.num_kv_heads,
+                      *reinterpret_cast<ApLds*>(lds));
     return;
   }
   blk -= nap;
   if (blk == 0)
     page_prefix_block(a, lds);
   else if (blk <= nq)
-    qprep_block<qp_split(AP)>(a, blk - 1, wide != 0, lds);
+    qprep_block(a, blk - 1, wide != 0, lds);
   else
     page_list_block(a, (blk - 1 - nq) / nseg, ((blk - 1 - nq) % nseg) * kPlPages, lds);
 }
@@ -1455,10 +1450,10 @@ hipError_t launch_qprep(const DecodeArgs& a, const AppendArgs* ap, hipStream_t s
   int nap = 0;
   if (ap && ap->n > 0) {
     none = *ap;
-    none.nbx = (ap->n + 16 * 4 - 1) / (16 * 4);  // one 16-token tile per wave and step
+    none.nbx = (ap->n + kApTok - 1) / kApTok;  // one tile per block
     nap = none.nbx * ap->cv.num_kv_heads * 2;
   }
-  const int nq = a.H * ((a.B + kQpSeqs - 1) / kQpSeqs) * qp_split(nap > 0);
+  const int nq = a.H * ((a.B + kQpSeqs - 1) / kQpSeqs) * kQpSplit;
   const long long maxlen = min((long long)a.max_ctx, (long long)a.max_blocks * kBlock);
   const int maxp = (int)((maxlen + kBlock - 1) / kBlock);
   const int nseg = max(1, (maxp + kPlPages - 1) / kPlPages);
