@@ -1190,75 +1190,171 @@ __global__ __launch_bounds__(512, 1) void decode_scan_flat_kernel(DecodeArgs a) 
 // thread (c, s) finishing query heads s, s + kMergeSlots, ... The un-rotation has the 128 threads of slot 0 share one
 // pass over R_V (row c of R_V per thread) for all query heads.
 
-// First stage of the two-stage merge (few, long sequences): block (sequence b, KV head h, range z)
-// folds the work-group slots ga + z n .. ga + z n + n - 1 of the sequence (n = ceil(slots / s1)) into
-// one partial per query head, in slot order, and writes it to part2 (m = -inf for an empty range).
-// Thread (channel c, slot lane sl) takes every eighth slot; the lanes are combined in a fixed order.
-__global__ __launch_bounds__(1024) void merge_stage1_kernel(DecodeArgs a) {
-  __shared__ float ms[8][8], ls[8][8];
-  __shared__ float os[8][8][kHeadDim];
-  const int b = blockIdx.x, h = blockIdx.y, z = blockIdx.z, c = threadIdx.x & 127, sl = threadIdx.x >> 7;
-  const int gq = a.gq;
+// Merge for small batches: one block of 1,024 threads per (query head, sequence), so that the few heads of a
+// small batch spread over Hq x B compute units and a long sequence's slots stream through one block in
+// rounds of 64 (thread (channel c, lane sl) takes every eighth slot, eight loads in flight). Each round of up to
+// 512 slots first takes the slots' maxima and sums (one slot per thread) and turns them into weights, so the sums
+// over slots are plain products; the lanes are combined in a fixed order. When the output needs R_V, its 64 KiB
+// come into LDS by LDS-DMA beside the partials' loads (16-byte piece q of row r at q ^ (r % 32): conflict-free
+// by rows and by columns). Latency-bound. Us a decode,
+// against two stages (ranges of slots, then one block per KV head): one sequence of 131,072 tokens 46.1 -> 34.3; eight
+// ragged ones at 32/4 heads 46.6 -> 34.2; one head, 256 tokens 21.6 -> 17.5; one KV head, 65,536 tokens 34.0 -> 22.1.
+constexpr int kMhLanes = 8, kMhThreads = 128 * kMhLanes, kMhRound = 512;
+
+struct MergeHeadLds {
+  float f[kMhRound];                 // weights of the round's slots (0: no partial)
+  float red[16], redl[16];           // per wave: maxima, sums
+  float os[kMhLanes][kHeadDim];
+  float win[kMhLanes][kHeadDim];
+  __attribute__((aligned(16))) float v[kHeadDim];
+  float w[kHeadDim];
+};
+
+template <bool ROT>
+__global__ __launch_bounds__(kMhThreads) void merge_head_kernel(DecodeArgs a, int unrotate, float* __restrict__ out,
+                                                                uint16_t* __restrict__ ob, int fmt) {
+  __shared__ MergeHeadLds L;
+  __shared__ __attribute__((aligned(16))) float rl[ROT ? kHeadDim * kHeadDim : 4];
+  const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, c = tid & 127, sl = tid >> 7, w = tid >> 6, l = tid & 63;
   const int ga = a.seq_wg[2 * b], gb = a.seq_wg[2 * b + 1];
-  const int per = (gb - ga + a.s1) / a.s1;
-  const int lo = ga + z * per, hi = min(gb, lo + per - 1);
-  float M[8], lsum[8], osum[8];
+  if constexpr (ROT) {
+    const float* R = a.R_v + (size_t)(j / a.gq) * kHeadDim * kHeadDim;
+    const uint32_t base = (uint32_t)(uintptr_t)&rl[0] + 4096 * __builtin_amdgcn_readfirstlane(w);
 #pragma unroll
-  for (int jj = 0; jj < 8; ++jj) {
-    M[jj] = -INFINITY;
-    lsum[jj] = 0.0f;
-    osum[jj] = 0.0f;
-  }
-  for (int gg = lo + sl; gg <= hi; gg += 8) {
-    const int r0 = a.wg_info[4 * gg + 3], r1 = a.wg_info[4 * gg + 7];
-    const float* base = a.part + ((size_t)(gg + b) * a.Hq + h * gq) * kPartStride;
-    float mv[8], lv[8], ov[8];
-#pragma unroll
-    for (int jj = 0; jj < 8; ++jj) {
-      const float* pp = base + min(jj, gq - 1) * kPartStride;
-      mv[jj] = pp[0];
-      lv[jj] = pp[1];
-      ov[jj] = pp[4 + c];
-    }
-#pragma unroll
-    for (int jj = 0; jj < 8; ++jj) {
-      const bool valid = r0 < r1 && mv[jj] != -INFINITY;
-      const float Mn = valid ? fmaxf(M[jj], mv[jj]) : M[jj];
-      const float fa = valid ? __builtin_amdgcn_exp2f(M[jj] - Mn) : 1.0f;
-      const float fb = valid ? __builtin_amdgcn_exp2f(mv[jj] - Mn) : 0.0f;
-      lsum[jj] = fmaf(lsum[jj], fa, valid ? fb * lv[jj] : 0.0f);
-      osum[jj] = fmaf(osum[jj], fa, valid ? fb * ov[jj] : 0.0f);
-      M[jj] = Mn;
+    for (int k = 0; k < 4; ++k) {
+      const int piece = 256 * w + 64 * k + l, r = piece >> 5, q = (piece & 31) ^ (r & 31);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(base + 1024 * k),
+                   "v"(R + r * kHeadDim + 4 * q)
+                   : "memory", "m0");
     }
   }
-  if (c == 0) {
+  // the window's slices (model basis): lane sl takes slice sl
+  float wm[kWinMaxSlices], wl[kWinMaxSlices], wo = 0.0f;
+  const bool win = ROT && a.wpart != nullptr;
+  if (win) {
 #pragma unroll
-    for (int jj = 0; jj < 8; ++jj) {
-      ms[sl][jj] = M[jj];
-      ls[sl][jj] = lsum[jj];
+    for (int s = 0; s < kWinMaxSlices; ++s) {
+      const float* pp = a.wpart + (((size_t)(s < a.win_slices ? s : 0) * a.B + b) * a.Hq + j) * kPartStride;
+      wm[s] = s < a.win_slices ? pp[0] : -INFINITY;
+      wl[s] = pp[1];
     }
+    if (sl < a.win_slices) wo = a.wpart[(((size_t)sl * a.B + b) * a.Hq + j) * kPartStride + 4 + c];
   }
+  static_assert(kWinMaxSlices <= kMhLanes, "a lane per window slice");
+  const float* part = a.part + ((size_t)b * a.Hq + j) * kPartStride;  // slot of group g: g + b
+  const size_t hop = (size_t)a.Hq * kPartStride;
+  float M = -INFINITY, Ls = 0.0f, O = 0.0f;
+  if (win) {
 #pragma unroll
-  for (int jj = 0; jj < 8; ++jj) os[sl][jj][c] = osum[jj];
+    for (int s = 0; s < kWinMaxSlices; ++s) M = fmaxf(M, wm[s]);
+    float ws = 0.0f;  // of the lane's slice
+#pragma unroll
+    for (int s = 0; s < kWinMaxSlices; ++s) {
+      const float f = wm[s] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(wm[s] - M);
+      Ls = fmaf(f, wl[s], Ls);
+      ws = sl == s ? f : ws;
+    }
+    wo = ws != 0.0f ? ws * wo : 0.0f;
+  }
+  for (int base = ga; base <= gb; base += kMhRound) {
+    const int cnt = min(kMhRound, gb - base + 1);
+    // a partial with no cached token has m = -inf (or the scan's finite floor) and l = 0; an empty range wrote
+    // nothing and its slot holds stale values, never used
+    float m = -INFINITY, ls = 0.0f;
+    if (tid < cnt) {
+      const int g = base + tid, r0 = a.wg_info[4 * g + 3], r1 = a.wg_info[4 * g + 7];
+      const float* pp = part + (size_t)g * hop;
+      m = r0 < r1 ? pp[0] : -INFINITY;
+      ls = pp[1];
+    }
+    float mx = row_max16(m);
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    if (l == 0) L.red[w] = mx;
+    __syncthreads();
+    float Mn = M;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) Mn = fmaxf(Mn, L.red[i]);
+    const float f = m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - Mn);
+    if (tid < kMhRound) L.f[tid] = f;
+    float sum = row_sum16(f != 0.0f ? f * ls : 0.0f);
+    sum += __shfl_xor(sum, 16);
+    sum += __shfl_xor(sum, 32);
+    if (l == 0) L.redl[w] = sum;
+    __syncthreads();
+    const float sc = M == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(M - Mn);  // M <= Mn, finite together
+    float lt = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) lt += L.redl[i];
+    Ls = fmaf(Ls, sc, lt);
+    O *= sc;
+    wo *= sc;
+    M = Mn;
+    const float* po = part + (size_t)base * hop + 4 + c;
+    for (int s0 = sl; s0 < cnt; s0 += 8 * kMhLanes) {
+      float ov[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) ov[u] = po[(size_t)min(s0 + kMhLanes * u, cnt - 1) * hop];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int s = s0 + kMhLanes * u;
+        const float fs = s < cnt ? L.f[min(s, kMhRound - 1)] : 0.0f;
+        O = fs != 0.0f ? fmaf(fs, ov[u], O) : O;
+      }
+    }
+    __syncthreads();  // the weights and maxima are rewritten by the next round
+  }
+  L.os[sl][c] = O;
+  if (win) L.win[sl][c] = wo;
   __syncthreads();
-  const int jj = sl;  // thread (c, sl) finishes query head sl
-  if (jj >= gq) return;
-  float Mx = -INFINITY;
+  const size_t idx = ((size_t)b * a.Hq + j) * kHeadDim + c, total = (size_t)a.B * a.Hq * kHeadDim;
+  if (sl == 0) {
+    float o = 0.0f, ow = 0.0f;
 #pragma unroll
-  for (int t = 0; t < 8; ++t) Mx = fmaxf(Mx, ms[t][jj]);
-  float L = 0.0f, O = 0.0f;
+    for (int t = 0; t < kMhLanes; ++t) o += L.os[t][c];
+    if (win) {
 #pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    const float f = ms[t][jj] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(ms[t][jj] - Mx);
-    L = fmaf(f, ls[t][jj], L);
-    O = fmaf(f, os[t][jj][c], O);
+      for (int t = 0; t < kMhLanes; ++t) ow += L.win[t][c];
+    }
+    o = Ls > 0.0f ? o / Ls : 0.0f;
+    ow = Ls > 0.0f ? ow / Ls : 0.0f;
+    if constexpr (!ROT) store_head_out(o, out, ob, fmt, idx, total);
+    L.v[c] = unrotate ? o : ow;  // what R_V multiplies
+    L.w[c] = unrotate ? ow : o;  // what is added
   }
-  float* dst = a.part2 + ((size_t)(b * a.s1 + z) * a.Hq + h * gq + jj) * kPartStride;
-  if (c == 0) {
-    dst[0] = Mx;
-    dst[1] = L;
+  if constexpr (ROT) {
+    // o = o_int2 R_V^T (+ o_win), or o' = o_int2 + o_win R_V for a projection folded with R_V: thread (c, sl)
+    // sums the channels 16 sl .. + 15
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    float acc = 0.0f;
+#pragma unroll
+    for (int q = 4 * sl; q < 4 * sl + 4; ++q) {
+      const float4 v = *reinterpret_cast<const float4*>(&L.v[4 * q]);
+      if (unrotate) {
+        const float4 r = *reinterpret_cast<const float4*>(&rl[kHeadDim * c + 4 * (q ^ (c & 31))]);
+        acc = fmaf(v.x, r.x, acc);
+        acc = fmaf(v.y, r.y, acc);
+        acc = fmaf(v.z, r.z, acc);
+        acc = fmaf(v.w, r.w, acc);
+      } else {
+        const float vi[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row = 4 * q + i;
+          acc = fmaf(vi[i], rl[kHeadDim * row + 4 * ((c >> 2) ^ (row & 31)) + (c & 3)], acc);
+        }
+      }
+    }
+    L.os[sl][c] = acc;
+    __syncthreads();
+    if (sl == 0) {
+      float o = win || !unrotate ? L.w[c] : 0.0f;
+#pragma unroll
+      for (int t = 0; t < kMhLanes; ++t) o += L.os[t][c];
+      store_head_out(o, out, ob, fmt, idx, total);
+    }
   }
-  dst[4 + c] = O;
 }
 
 template <int kMergeSlots>
@@ -1287,14 +1383,9 @@ __global__ __launch_bounds__(128 * kMergeSlots) void merge_flat_kernel(DecodeArg
         wo[r][s] = pp[4 + c];
       }
   }
-  // groups whose ranges meet the sequence, from the page-prefix block; in the second stage of the
-  // two-stage merge, the sequence's folded slot ranges instead
-  const bool st2 = a.s1 > 0;
-  const int ga = st2 ? 0 : a.seq_wg[2 * b], gb = st2 ? a.s1 - 1 : a.seq_wg[2 * b + 1];
-  auto slot_base = [&](int gg) {
-    return st2 ? a.part2 + ((size_t)(b * a.s1 + gg) * a.Hq + h * gq) * kPartStride
-               : a.part + ((size_t)(gg + b) * a.Hq + h * gq) * kPartStride;
-  };
+  // groups whose ranges meet the sequence, from the page-prefix block
+  const int ga = a.seq_wg[2 * b], gb = a.seq_wg[2 * b + 1];
+  auto slot_base = [&](int gg) { return a.part + ((size_t)(gg + b) * a.Hq + h * gq) * kPartStride; };
   float M[8], lsum[8], osum[8];
 #pragma unroll
   for (int jj = 0; jj < 8; ++jj) {
@@ -1322,9 +1413,8 @@ __global__ __launch_bounds__(128 * kMergeSlots) void merge_flat_kernel(DecodeArg
     // dropped by selects below, never multiplied; a second slot past gb is loaded as slot gg and
     // dropped
     const int g2 = gg + kMergeSlots <= gb ? gg + kMergeSlots : gg;
-    // stage-2 ranges are never stale (an empty one was written with m = -inf)
-    const int r0 = st2 ? 0 : a.wg_info[4 * gg + 3], r1 = st2 ? 1 : a.wg_info[4 * gg + 7];
-    const int r2 = st2 ? 0 : a.wg_info[4 * g2 + 3], r3 = st2 ? 1 : a.wg_info[4 * g2 + 7];
+    const int r0 = a.wg_info[4 * gg + 3], r1 = a.wg_info[4 * gg + 7];
+    const int r2 = a.wg_info[4 * g2 + 3], r3 = a.wg_info[4 * g2 + 7];
     const float* base = slot_base(gg);
     const float* base2 = slot_base(g2);
     float mv[8], lv[8], ov[8], mv2[8], lv2[8], ov2[8];
@@ -1484,21 +1574,24 @@ hipError_t launch_decode_split_mfma(const DecodeArgs& a, hipStream_t s, hipEvent
 
 hipError_t launch_merge_flat(const DecodeArgs& a, bool unrotate, float* out, uint16_t* ob, int fmt, hipStream_t s) {
   if (a.gq > 8) return hipErrorNotSupported;
-  // four slots when many sequences share the work-groups (short spans; fewer idle waves to
-  // dispatch), eight for few, long sequences (fewer rounds of loads)
-  if (a.s1 > 0) {
-    // few, long sequences: every range of slots folded by its own block first, so that the
-    // partials stream through B x H x s1 blocks instead of B x H
-    DecodeArgs a1 = a;
-    hipLaunchKernelGGL(merge_stage1_kernel, dim3(a.B, a.H, a.s1), dim3(1024), 0, s, a1);
-    hipLaunchKernelGGL(merge_flat_kernel<8>, dim3(a.B, a.H), dim3(128 * 8), 0, s, a, unrotate ? 1 : 0, out,
-                       ob, fmt);
-  } else if (a.B >= 32)
-    hipLaunchKernelGGL(merge_flat_kernel<4>, dim3(a.B, a.H), dim3(128 * 4), 0, s, a, unrotate ? 1 : 0, out,
-                       ob, fmt);
-  else
-    hipLaunchKernelGGL(merge_flat_kernel<8>, dim3(a.B, a.H), dim3(128 * 8), 0, s, a, unrotate ? 1 : 0, out,
-                       ob, fmt);
+  // A block per query head for small batches, and at every size for the un-rotation alone (the block per KV head
+  // reads R_V in 64-byte pieces): us a call, per head / per KV head, 16 x 4,096 tokens un-rotated 26.9 / 33.9, 64 x
+  // 2,000 with a plain projection 54.6 / 55.5; but with the projection folded 39.8 / 39.0, with windows (32
+  // sequences, 40 heads) 91.5 / 82.3, where the blocks of one KV head share what they read.
+  const bool rot = unrotate || a.wpart;
+  if ((long long)a.B * a.H < kMergeHeadUnits || (unrotate && !a.wpart)) {
+    if (rot)
+      hipLaunchKernelGGL(merge_head_kernel<true>, dim3(a.Hq, a.B), dim3(kMhThreads), 0, s, a, unrotate ? 1 : 0, out, ob,
+                         fmt);
+    else
+      hipLaunchKernelGGL(merge_head_kernel<false>, dim3(a.Hq, a.B), dim3(kMhThreads), 0, s, a, 0, out, ob, fmt);
+  } else if (a.B >= 32) {
+    // four slots when many sequences share the work-groups (short spans; fewer idle waves to
+    // dispatch), eight for fewer, longer sequences (fewer rounds of loads)
+    hipLaunchKernelGGL(merge_flat_kernel<4>, dim3(a.B, a.H), dim3(128 * 4), 0, s, a, unrotate ? 1 : 0, out, ob, fmt);
+  } else {
+    hipLaunchKernelGGL(merge_flat_kernel<8>, dim3(a.B, a.H), dim3(128 * 8), 0, s, a, unrotate ? 1 : 0, out, ob, fmt);
+  }
   return hipGetLastError();
 }
 
