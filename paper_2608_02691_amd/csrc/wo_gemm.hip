@@ -18,6 +18,8 @@
 // in slice order (deterministic). With a single slice the GEMM writes y itself. (Letting the last
 // work-group of a tile sum the slices needs a device-scope release in every work-group, i.e. an L2
 // write-back per work-group, which measured slower than the second launch.)
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -156,6 +158,90 @@ __global__ __launch_bounds__(256) void wo_mfma_kernel(const uint16_t* __restrict
     }
 }
 
+// Few batch rows: block = 16 rows of W x all of K, eight waves taking every eighth 64-wide piece of K, so the
+// slices meet in LDS (summed in wave order) and there are no partials in memory and no second launch. A wave
+// issues all loads of kWoRowSteps pieces, weights and o, straight into operand registers before its products.
+// Bound by the weights' stream (33.5 MB at 4,096 x 4,096). In the row-major format a lane takes 16
+// consecutive k of a piece (8 for each of its two products), so a row's four lanes read whole 128-byte lines;
+// prepared tiles are read in their own order, 1 KiB at a time. Wider batches use the tiles above, whose 64 batch
+// rows share the o operand (here every block reads all of it). Us a step, against
+// tiles, partials and their sum: 32/8 heads, 1,011 tokens 27.5 -> 23.5; 16 x 4,096 tokens 39.1 -> 34.9; row-major weights,
+// eight ragged sequences 34.2 -> 30.7.
+constexpr int kWoRowBatch = 16, kWoRowWaves = 8;
+
+// NB: 16-row batch tiles
+template <bool PREP, int NB>
+__global__ __launch_bounds__(64 * kWoRowWaves) void wo_rows_kernel(const uint16_t* __restrict__ ob,
+                                                                   const uint16_t* __restrict__ W,
+                                                                   float* __restrict__ y, int B, int K, int N) {
+  constexpr int kTerms = PREP ? 1 : 2, kWoRowSteps = (PREP ? 8 : 4) / NB;
+  __shared__ float part[kWoRowWaves][16 * NB][17];
+  const int n0 = 16 * blockIdx.x, tid = threadIdx.x, w = tid >> 6, l = tid & 63, lo = l & 15, hi = l >> 4;
+  const int pieces = K / 64;
+  // element offsets of product u (0, 1) of piece p: wa + p * wstep + u * wu, oa + 64 p + u * ou
+  const size_t wa = PREP ? (size_t)(n0 / kWoTileN) * (K / kWoKStep) * kWoTileElems + 512 * ((n0 % kWoTileN) / 16) + 8 * l
+                         : (size_t)min(n0 + lo, N - 1) * K + 16 * hi;
+  constexpr int wstep = PREP ? 2 * kWoTileElems : 64, wu = PREP ? kWoTileElems : 8, ou = PREP ? 32 : 8;
+  size_t oa[NB];
+  const size_t term = (size_t)B * K;
+  wo_f4_t acc[NB];
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    oa[n] = (size_t)min(16 * n + lo, B - 1) * K + (PREP ? 8 : 16) * hi;
+    acc[n] = wo_f4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  // pieces p0, p0 + kWoRowWaves, .. (S of them): every load issued before the first product
+  auto chunk = [&](auto steps_tag, int p0) {
+    constexpr int S = decltype(steps_tag)::value;
+    bf16x8_t A[S][2], O[kTerms][NB][S][2];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int p = p0 + kWoRowWaves * s;
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        A[s][u] = *reinterpret_cast<const bf16x8_t*>(W + wa + (size_t)p * wstep + u * wu);
+#pragma unroll
+        for (int t = 0; t < kTerms; ++t)
+#pragma unroll
+          for (int n = 0; n < NB; ++n)
+            O[t][n][s][u] = *reinterpret_cast<const bf16x8_t*>(ob + t * term + oa[n] + 64 * p + u * ou);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+          if constexpr (PREP) {
+            acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, A[s][u]),
+                                                            __builtin_bit_cast(f16x8_t, O[0][n][s][u]), acc[n], 0, 0, 0);
+          } else {
+            acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[s][u], O[0][n][s][u], acc[n], 0, 0, 0);
+            acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[s][u], O[kTerms - 1][n][s][u], acc[n], 0, 0, 0);
+          }
+        }
+  };
+  int p0 = w;
+  for (; p0 + kWoRowWaves * (kWoRowSteps - 1) < pieces; p0 += kWoRowWaves * kWoRowSteps)
+    chunk(std::integral_constant<int, kWoRowSteps>{}, p0);
+  for (; p0 < pieces; p0 += kWoRowWaves) chunk(std::integral_constant<int, 1>{}, p0);
+  // D[m][n]: W row m = 4 hi + r, batch row n = lo of the tile
+#pragma unroll
+  for (int n = 0; n < NB; ++n)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[w][16 * n + lo][4 * hi + r] = acc[n][r];
+  __syncthreads();
+  const int m = tid & 15;
+  for (int b = tid >> 4; b < B && n0 + m < N; b += 4 * kWoRowWaves) {
+    float s = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kWoRowWaves; ++i) s += part[i][b][m];
+    y[(size_t)b * N + n0 + m] = s;
+  }
+}
+
 // y = sum over slices, in slice order, of partial[s] (B x N, fp32). Four consecutive elements per
 // thread; the loads of all slices are issued before the sums (no load waits behind an add).
 constexpr int kWoMaxUnroll = 8;
@@ -195,6 +281,19 @@ hipError_t launch_wo_gemm(const uint16_t* ob, const uint16_t* W, bool prepared, 
   if (K % kWoKStep != 0 || B <= 0 || N <= 0 || ksplit != wo_ksplit(K, N, B) ||
       (!prepared && (size_t)N * K * 2 >= (1ull << 32)) || (size_t)2 * B * K * 2 >= (1ull << 32))
     return hipErrorInvalidValue;
+  // One launch of 16-row blocks for up to 16 batch rows, and for up to 32 with prepared weights while every block
+  // has a CU of its own (us a step there, 16-row blocks / tiles and sum: 20 rows 29.5 / 32.7, 32 rows 32.7 / 34.5 at
+  // 4,096 x 4,096; but 92.4 / 82.8 at 5,120 x 5,120, 42.1 / 37.1 row-major, and worse from 48 rows on)
+  const dim3 rows((N + 15) / 16), block(64 * kWoRowWaves);
+  if (B <= kWoRowBatch || (prepared && B <= 2 * kWoRowBatch && (int)rows.x <= num_cus())) {
+    if (!prepared)
+      hipLaunchKernelGGL((wo_rows_kernel<false, 1>), rows, block, 0, s, ob, W, y, B, K, N);
+    else if (B <= kWoRowBatch)
+      hipLaunchKernelGGL((wo_rows_kernel<true, 1>), rows, block, 0, s, ob, W, y, B, K, N);
+    else
+      hipLaunchKernelGGL((wo_rows_kernel<true, 2>), rows, block, 0, s, ob, W, y, B, K, N);
+    return hipGetLastError();
+  }
   dim3 grid((N + kWoTileN - 1) / kWoTileN, ksplit, (B + kWoBatch - 1) / kWoBatch);
   if (prepared)
     hipLaunchKernelGGL(wo_mfma_kernel<true>, grid, dim3(256), 0, s, ob, W, partial, y, B, K, N, wo_slice(K, N, B),
@@ -219,6 +318,7 @@ int wo_slice(int K, int N, int B) {
   return kWoKStep * ((steps + want - 1) / want);
 }
 int wo_ksplit(int K, int N, int B) {
+  if (B <= kWoRowBatch) return 1;
   const int sl = wo_slice(K, N, B);
   return (K + sl - 1) / sl;
 }
