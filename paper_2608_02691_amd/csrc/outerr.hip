@@ -33,32 +33,10 @@ __device__ __forceinline__ int oe_seq_len(const OutErrArgs& e, int b) {
   return max(L, 0);
 }
 
-// sum over the 4 lanes of a DPP quad (quad_perm [1, 0, 3, 2] then [2, 3, 0, 1]); every lane gets it
-__device__ __forceinline__ float quad_sum4(float x) {
-  x += dppf<0xB1>(x);
-  return x + dppf<0x4E>(x);
-}
-// max over the four tokens of a DPP row (lanes 4 tq + gk; rotations by 4 and 8 lanes)
-__device__ __forceinline__ float row_max_tokens(float x) {
-  x = fmaxf(x, dppf<0x124>(x));
-  return fmaxf(x, dppf<0x128>(x));
-}
-// max over the four DPP rows of values that are already uniform within each row (lanes 0, 16, 32
-// and 48 read out as scalars)
-__device__ __forceinline__ float rows_max4(float x) {
-  const float a = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 0));
-  const float b = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 16));
-  const float c = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 32));
-  const float d = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 48));
-  return fmaxf(fmaxf(a, b), fmaxf(c, d));
-}
-__device__ __forceinline__ float rows_sum4(float x) {
-  const float a = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 0));
-  const float b = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 16));
-  const float c = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 32));
-  const float d = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 48));
-  return (a + b) + (c + d);
-}
+typedef _Float16 oe_f16x8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 oe_bf8_t __attribute__((ext_vector_type(8)));
+typedef float oe_f4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t oe_u4_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ void oe_wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -68,23 +46,31 @@ __device__ __forceinline__ void oe_wave_sync() {
 
 }  // namespace
 
-// Block (chunk, KV head h, sequence b). Lane roles as in the vector-ALU decode scan: for the scores,
-// token tq = l / 4 of the page and 32-channel quarter gk = l % 4; for the values, channels 2l, 2l+1.
+// Block (chunk, KV head h, sequence b). Scores on the matrix cores, with fp32's precision: lane (token lo = l % 16,
+// hi = l / 16) ends with the scores of token lo for query head 4 Q + hi of each quad Q of heads.
+//  * full precision: q . k as bf16 products (exact), fp32 sums; query head j of the quad in row 4 j;
+//  * INT2: a code's two bits, shifted to the bottom of a 16-bit half, are the fp16 number code 2^-24; times 2^15 it is
+//    a normal number (the matrix cores align a product by its exponents, so that subnormal factors cost the sum
+//    their leading zeros: statistics to 2e-5 of fp64's instead of 1e-6). q' = q R_K, scaled by a power of two, enters
+//    as three fp16 terms whose sum it is, in rows 4 j .. 4 j + 2: one product per 32-channel group gives
+//    sum_{c in g} q'_c code_c in the lane's first three registers.
+// Softmaxes run on one (token, head) per lane, with maxima and sums over the 16 lanes of a DPP row. For the
+// values lane l owns channels 2 l, 2 l + 1 on the vector ALU. Near the rows' stream: 16 x 4,096 tokens, 32/8 heads
+// 121 us with the scores on the vector ALU (their products and LDS broadcasts of q) -> 83 us for 318 MB. Statistics
+// differ from fp64's by 3e-7 to 8e-7 (on the vector ALU 4e-7 to 9e-7).
 template <int MAXG, int NG>
 __global__ __launch_bounds__(256, MAXG <= 4 ? 4 : 1) void outerr_scan_kernel(OutErrArgs e) {
   using Lay = Rec<NG>;
+  constexpr int kQuads = (MAXG + 3) / 4;
   const DecodeArgs& a = e.a;
-  __shared__ float qf[MAXG][kHeadDim];       // q (model basis), base-2 logit units
-  __shared__ float qr[MAXG][kHeadDim];       // q R_K, base-2 logit units
-  __shared__ float qsum[MAXG][kGroups];      // sums of q R_K over each 32-channel quarter
-  __shared__ float pb[kOeWaves][2][kBlock][MAXG];   // p of both softmaxes for the page (token-major)
-  __shared__ float wst[kOeWaves][MAXG][4];
+  __shared__ float pb[kOeWaves][2][kBlock][4 * kQuads];  // p of both softmaxes for the page (token-major)
+  __shared__ float wst[kOeWaves][4 * kQuads][4];
   __shared__ float wout[kOeWaves][3][MAXG][kHeadDim];
 
   const int chunk = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   const int L = oe_seq_len(e, b);
   const int t0 = chunk * a.chunk_tokens;
-  const int gq = a.gq, tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+  const int gq = a.gq, tid = threadIdx.x, w = tid >> 6, l = tid & 63, lo = l & 15, hi = l >> 4;
   if (t0 >= L) {
     // a chunk past the context: an empty partial (m = -inf) that the merge drops
     for (int i = tid; i < gq; i += blockDim.x) {
@@ -95,31 +81,73 @@ __global__ __launch_bounds__(256, MAXG <= 4 ? 4 : 1) void outerr_scan_kernel(Out
     return;
   }
   const int t1 = min(L, t0 + a.chunk_tokens);
-  for (int i = tid; i < gq * kHeadDim; i += blockDim.x) {
-    const int jj = i / kHeadDim, c = i % kHeadDim;
-    const size_t q = ((size_t)b * a.Hq + h * gq + jj) * kHeadDim + c;
-    qr[jj][c] = a.qrot[q] * kOeLogit2;
-    qf[jj][c] = bf16_bits_to_f32(a.q[q]) * kOeLogit2;
+
+  // query operands of each quad, the group sums of q' of head hi and the factor back to base-2 logits
+  __shared__ oe_bf8_t A1[kQuads][4][64];  // in LDS: 16 vector registers less a quad, which would spill
+  oe_f16x8_t A2[kQuads][4];
+  float qsum[kQuads][kGroups], unscale[kQuads];
+#pragma unroll
+  for (int Q = 0; Q < kQuads; ++Q) {
+    // row lo = 4 j + term of head j: the lane's channels of group g are 32 g + 4 hi + 0..3, 32 g + 16 + 4 hi + 0..3
+    const int jr = 4 * Q + (lo >> 2), term = lo & 3;
+    const size_t qrow = ((size_t)b * a.Hq + h * gq + min(jr, gq - 1)) * kHeadDim;
+    const bool on = jr < gq;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const oe_u4_t x = *reinterpret_cast<const oe_u4_t*>(a.q + qrow + 32 * ks + 8 * hi);
+      const uint32_t keep = on && term == 0 ? ~0u : 0u;
+      const oe_bf8_t y = __builtin_bit_cast(oe_bf8_t, x & oe_u4_t{keep, keep, keep, keep});
+      if (ks == w) A1[Q][ks][l] = y;
+    }
+    float x[4][8], mx = 0.0f;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 u = *reinterpret_cast<const float4*>(a.qrot + qrow + 32 * g + 4 * hi);
+      const float4 v = *reinterpret_cast<const float4*>(a.qrot + qrow + 32 * g + 16 + 4 * hi);
+      const float y[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        x[g][i] = on ? y[i] : 0.0f;
+        mx = fmaxf(mx, fabsf(x[g][i]));
+      }
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    int ex = 0;
+    frexpf(mx, &ex);
+    ex = mx > 0.0f && mx < INFINITY ? max(-80, ex) : 14;  // |q'| 2^(14 - ex) < 2^14
+    const float sg = ldexpf(1.0f, 14 - ex);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      float s = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        s += x[g][i];
+        const float y = x[g][i] * sg;
+        const _Float16 f0 = (_Float16)y, f1 = (_Float16)(y - (float)f0);
+        const _Float16 f2 = (_Float16)((y - (float)f0) - (float)f1);
+        A2[Q][g][i] = term == 0 ? f0 : term == 1 ? f1 : term == 2 ? f2 : (_Float16)0.0f;
+      }
+      s += __shfl_xor(s, 16);
+      s += __shfl_xor(s, 32);
+      qsum[Q][g] = __shfl(s, 4 * hi) * kOeLogit2;  // lane 4 hi holds row 4 hi: head hi of the quad
+    }
+    unscale[Q] = ldexpf(kOeLogit2, 24 - 15 - 14 + __shfl(ex, 4 * hi));
   }
-  __syncthreads();
-  if (tid < gq * kGroups) {
-    const int jj = tid / kGroups, g = tid % kGroups;
-    float acc = 0.0f;
-    for (int c = 0; c < kGroup; ++c) acc += qr[jj][g * kGroup + c];
-    qsum[jj][g] = acc;
-  }
+
   __syncthreads();
 
-  // running states: (m, l) of both softmaxes, and the three value sums of channels 2l, 2l+1
-  float m1[MAXG], l1[MAXG], m2[MAXG], l2[MAXG], o[3][MAXG][2];
+  // running states: (m, l) of both softmaxes for head hi of each quad; the three value sums of channels 2l, 2l + 1
+  float m1[kQuads], l1[kQuads], m2[kQuads], l2[kQuads], o[3][MAXG][2];
 #pragma unroll
-  for (int j = 0; j < MAXG; ++j) {
-    m1[j] = m2[j] = -INFINITY;
-    l1[j] = l2[j] = 0.0f;
+  for (int Q = 0; Q < kQuads; ++Q) {
+    m1[Q] = m2[Q] = -INFINITY;
+    l1[Q] = l2[Q] = 0.0f;
+  }
+#pragma unroll
+  for (int j = 0; j < MAXG; ++j)
 #pragma unroll
     for (int r = 0; r < 3; ++r) o[r][j][0] = o[r][j][1] = 0.0f;
-  }
-  const int tq = l >> 2, gk = l & 3;
   const int c0 = 2 * l, m0 = c0 & 15, pv = c0 >> 4, gv = c0 >> 5;
   const size_t row_stride = (size_t)a.H * kHeadDim;
   const uint16_t* krow0 = e.k_rows + ((size_t)b * e.row_cap * a.H + h) * kHeadDim;
@@ -130,106 +158,83 @@ __global__ __launch_bounds__(256, MAXG <= 4 ? 4 : 1) void outerr_scan_kernel(Out
     const int blk = a.block_table[(size_t)b * a.max_blocks + pg];
     if (blk < 0 || blk >= a.num_blocks) continue;  // uniform per wave
     const uint8_t* rec = a.pool + ((size_t)blk * a.H + h) * Lay::kBytes;
-    const int pos = pg * kBlock + tq;
+    const int pos = pg * kBlock + lo;
     const bool valid = pos >= t0 && pos < t1;
     const int posc = min(max(pos, t0), t1 - 1);  // a row inside the caller's store
 
-    // ---- INT2 and full-precision scores of token tq over the lane's channel quarter gk: half mm of the
-    // token's code words holds channels 32 gk + mm (bits 4 gk) and 32 gk + 16 + mm (bits 4 gk + 2); the
-    // codes and the raw key values are unpacked four halves at a time, each chunk feeding every head
-    const uint4* kc = reinterpret_cast<const uint4*>(rec + kOffKCodes + 32 * tq);
-    const uint4 k0 = kc[0], k1 = kc[1];
-    const uint32_t kw[8] = {k0.x, k0.y, k0.z, k0.w, k1.x, k1.y, k1.z, k1.w};
-    const uint32_t meta =
-        *reinterpret_cast<const uint32_t*>(rec + Lay::kOffKMeta + 4 * NG * tq + 4 * (NG == 4 ? gk : 0));
-    const float ks = f16_bits_to_f32(meta & 0xFFFF), kz = f16_bits_to_f32(meta >> 16);
-    uint32_t kraw[16];  // the token's raw key row, channels 32 gk .. 32 gk + 31 (two per word)
-    {
-      const uint4* kp = reinterpret_cast<const uint4*>(krow0 + (size_t)posc * row_stride + 32 * gk);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const uint4 x = kp[u];
-        kraw[4 * u] = x.x;
-        kraw[4 * u + 1] = x.y;
-        kraw[4 * u + 2] = x.z;
-        kraw[4 * u + 3] = x.w;
-      }
+    // ---- operands of token lo: its codes (halves 4 hi .. + 3), metadata and raw key channels 32 ks + 8 hi ..
+    const uint2 kc = *reinterpret_cast<const uint2*>(rec + kOffKCodes + 32 * lo + 8 * hi);
+    uint32_t km[NG];
+    if constexpr (NG == 4) {
+      const uint4 x = *reinterpret_cast<const uint4*>(rec + Lay::kOffKMeta + 16 * lo);
+      km[0] = x.x, km[1] = x.y, km[2] = x.z, km[3] = x.w;
+    } else {
+      km[0] = *reinterpret_cast<const uint32_t*>(rec + Lay::kOffKMeta + 4 * lo);
     }
-    auto kf = [&](int c) {  // raw key value of channel 32 gk + c
-      return __uint_as_float((c & 1) ? (kraw[c >> 1] & 0xFFFF0000u) : (kraw[c >> 1] << 16));
-    };
-    float d1[MAXG], d2[MAXG];
+    oe_bf8_t kr[4];
 #pragma unroll
-    for (int j = 0; j < MAXG; ++j) d1[j] = d2[j] = 0.0f;
+    for (int ks = 0; ks < 4; ++ks)
+      kr[ks] = *reinterpret_cast<const oe_bf8_t*>(krow0 + (size_t)posc * row_stride + 32 * ks + 8 * hi);
+    oe_f16x8_t kq[4];
 #pragma unroll
-    for (int mc = 0; mc < 16; mc += 4) {
-      float cl[4], chi[4], fl[4], fh[4];
+    for (int g = 0; g < 4; ++g)
+      kq[g] = __builtin_bit_cast(oe_f16x8_t, oe_u4_t{(kc.x >> (4 * g)) & 0x00030003u, (kc.y >> (4 * g)) & 0x00030003u,
+                                                     (kc.x >> (4 * g + 2)) & 0x00030003u,
+                                                     (kc.y >> (4 * g + 2)) & 0x00030003u}) *
+              (_Float16)32768.0f;
+    bool moved = false;
+    float al1[kQuads], al2[kQuads];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int mm = mc + i;
-        const uint32_t half = (kw[mm >> 1] >> (16 * (mm & 1))) & 0xFFFF;
-        cl[i] = static_cast<float>((half >> (4 * gk)) & 3);       // channel 32 gk + mm
-        chi[i] = static_cast<float>((half >> (4 * gk + 2)) & 3);  // channel 32 gk + 16 + mm
-        fl[i] = kf(mm);
-        fh[i] = kf(16 + mm);
+    for (int Q = 0; Q < kQuads; ++Q) {
+      oe_f4_t d1 = {0.f, 0.f, 0.f, 0.f}, d2[NG];
+#pragma unroll
+      for (int g = 0; g < NG; ++g) d2[g] = oe_f4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        d1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A1[Q][g][l], kr[g], d1, 0, 0, 0);
+        d2[g % NG] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A2[Q][g], kq[g], d2[g % NG], 0, 0, 0);
       }
+      float s1 = d1[0] * kOeLogit2, s2 = 0.0f;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        const float qs = NG == 4 ? qsum[Q][g] : (qsum[Q][0] + qsum[Q][1]) + (qsum[Q][2] + qsum[Q][3]);
+        const float dot = ((d2[g][2] + d2[g][1]) + d2[g][0]) * unscale[Q];
+        s2 += f16_bits_to_f32(km[g] & 0xFFFF) * dot + f16_bits_to_f32(km[g] >> 16) * qs;
+      }
+      s1 = valid ? s1 : -INFINITY;
+      s2 = valid ? s2 : -INFINITY;
+      const float n1 = fmaxf(m1[Q], row_max16(s1)), n2 = fmaxf(m2[Q], row_max16(s2));
+      al1[Q] = n1 == -INFINITY ? 1.0f : exp2f(m1[Q] - n1);
+      al2[Q] = n2 == -INFINITY ? 1.0f : exp2f(m2[Q] - n2);
+      moved |= n1 != m1[Q] || n2 != m2[Q];
+      const float p1 = valid ? exp2f(s1 - n1) : 0.0f, p2 = valid ? exp2f(s2 - n2) : 0.0f;
+      l1[Q] = l1[Q] * al1[Q] + row_sum16(p1);
+      l2[Q] = l2[Q] * al2[Q] + row_sum16(p2);
+      m1[Q] = n1;
+      m2[Q] = n2;
+      pb[w][0][lo][4 * Q + hi] = p1;
+      pb[w][1][lo][4 * Q + hi] = p2;
+    }
+    oe_wave_sync();
+    if (__any(moved)) {
 #pragma unroll
       for (int j = 0; j < MAXG; ++j) {
-        if (j >= gq) continue;
+        const float f1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, al1[j >> 2]), 16 * (j & 3)));
+        const float f2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, al2[j >> 2]), 16 * (j & 3)));
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int mm = mc + i;
-          d2[j] = fmaf(qr[j][32 * gk + mm], cl[i], d2[j]);
-          d2[j] = fmaf(qr[j][32 * gk + 16 + mm], chi[i], d2[j]);
-          d1[j] = fmaf(qf[j][32 * gk + mm], fl[i], d1[j]);
-          d1[j] = fmaf(qf[j][32 * gk + 16 + mm], fh[i], d1[j]);
+        for (int cc = 0; cc < 2; ++cc) {
+          o[0][j][cc] *= f1;
+          o[1][j][cc] *= f2;
+          o[2][j][cc] *= f2;
         }
       }
     }
-    float al1[MAXG], al2[MAXG];
-#pragma unroll
-    for (int j = 0; j < MAXG; ++j) {
-      al1[j] = al2[j] = 1.0f;
-      if (j >= gq) continue;
-      // the token's scores: sums over its four quarter lanes (a DPP quad)
-      float s2 = quad_sum4(ks * d2[j] + kz * qsum[j][gk]);
-      float s1 = quad_sum4(d1[j]);
-      s1 = valid ? s1 : -INFINITY;
-      s2 = valid ? s2 : -INFINITY;
-      // page maxima: over the four tokens of each DPP row, then the rows
-      const float x1 = rows_max4(row_max_tokens(s1)), x2 = rows_max4(row_max_tokens(s2));
-      const float n1 = fmaxf(m1[j], x1), n2 = fmaxf(m2[j], x2);
-      al1[j] = n1 == -INFINITY ? 1.0f : exp2f(m1[j] - n1);
-      al2[j] = n2 == -INFINITY ? 1.0f : exp2f(m2[j] - n2);
-      const float p1 = valid ? exp2f(s1 - n1) : 0.0f, p2 = valid ? exp2f(s2 - n2) : 0.0f;
-      // page sums of p: one lane per token (gk = 0), over each DPP row, then the rows
-      const float ps1 = rows_sum4(row_sum16(gk == 0 ? p1 : 0.0f));
-      const float ps2 = rows_sum4(row_sum16(gk == 0 ? p2 : 0.0f));
-      l1[j] = l1[j] * al1[j] + ps1;
-      l2[j] = l2[j] * al2[j] + ps2;
-      m1[j] = n1;
-      m2[j] = n2;
-      if (gk == 0) {
-        pb[w][0][tq][j] = p1;
-        pb[w][1][tq][j] = p2;
-      }
-    }
-    oe_wave_sync();
 
     // ---- values of channels c0, c0 + 1: INT2 (R_V basis) and full precision (model basis), in two
     // halves of eight tokens (the loads of a half, then its arithmetic)
     const uint4* vc = reinterpret_cast<const uint4*>(rec + kOffVCodes + 32 * m0);  // halves m0, m0 + 1
     const uint4* vsp = reinterpret_cast<const uint4*>(rec + Lay::kOffVScale + 32 * (NG == 4 ? gv : 0));
     const uint4* vzp = reinterpret_cast<const uint4*>(rec + Lay::kOffVZero + 32 * (NG == 4 ? gv : 0));
-#pragma unroll
-    for (int j = 0; j < MAXG; ++j) {
-#pragma unroll
-      for (int cc = 0; cc < 2; ++cc) {
-        o[0][j][cc] *= al1[j];
-        o[1][j][cc] *= al2[j];
-        o[2][j][cc] *= al2[j];
-      }
-    }
 #pragma unroll
     for (int H = 0; H < 2; ++H) {
       const uint4 ca = vc[H], cb = vc[2 + H], s4 = vsp[H], z4 = vzp[H];  // tokens 8 H .. 8 H + 7
@@ -267,15 +272,18 @@ __global__ __launch_bounds__(256, MAXG <= 4 ? 4 : 1) void outerr_scan_kernel(Out
   }
 
   // ---- merge the four wave states into the chunk's partial
+  if (lo == 0)
+#pragma unroll
+    for (int Q = 0; Q < kQuads; ++Q) {
+      const int j = 4 * Q + hi;
+      wst[w][j][0] = m1[Q];
+      wst[w][j][1] = l1[Q];
+      wst[w][j][2] = m2[Q];
+      wst[w][j][3] = l2[Q];
+    }
 #pragma unroll
   for (int j = 0; j < MAXG; ++j) {
     if (j < gq) {
-      if (l == 0) {
-        wst[w][j][0] = m1[j];
-        wst[w][j][1] = l1[j];
-        wst[w][j][2] = m2[j];
-        wst[w][j][3] = l2[j];
-      }
 #pragma unroll
       for (int r = 0; r < 3; ++r) {
         wout[w][r][j][c0] = o[r][j][0];
@@ -373,8 +381,6 @@ __global__ __launch_bounds__(128) void outerr_merge_kernel(OutErrArgs e) {
   }
 }
 
-typedef float oe_f4_t __attribute__((ext_vector_type(4)));
-
 // Block (query head j, tile of kOeRowTile rows of W_O), four waves: dy[b][j][{K, V}][row] =
 // do[b][j][{K, V}] . W_O[row][j * 128 ..] for every sequence, and the tile's partial statistics, on
 // the bf16 matrix cores with do as three exact bf16 terms (fp32 products and accumulation, as an
@@ -384,7 +390,6 @@ typedef float oe_f4_t __attribute__((ext_vector_type(4)));
 // the head's 128 channels in four blocks of 32 (lane: channels 32 i + 8 (l / 16) .. + 7 of its do
 // and W_O rows).
 constexpr int kOeNT = kOeRowTile / 64;  // 16-row N tiles per wave
-typedef __bf16 oe_bf16x8_t __attribute__((ext_vector_type(8)));
 __global__ __launch_bounds__(256) void outerr_proj_kernel(OutErrArgs e, const uint16_t* __restrict__ W_o,
                                                           int d_model, float* __restrict__ dy,
                                                           float* __restrict__ spart, int ntiles) {
@@ -394,7 +399,7 @@ __global__ __launch_bounds__(256) void outerr_proj_kernel(OutErrArgs e, const ui
   const int w = tid >> 6, l = tid & 63, li = l & 15, lk = l >> 4;
   int n[kOeNT];
   bool have[kOeNT];
-  oe_bf16x8_t wb[kOeNT][4];
+  oe_bf8_t wb[kOeNT][4];
 #pragma unroll
   for (int nt = 0; nt < kOeNT; ++nt) {
     n[nt] = tile * kOeRowTile + 16 * (kOeNT * w + nt) + li;  // this lane's W_O row of N tile nt
@@ -403,13 +408,13 @@ __global__ __launch_bounds__(256) void outerr_proj_kernel(OutErrArgs e, const ui
                                                      (size_t)j * kHeadDim + 8 * lk);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      wb[nt][i] = __builtin_bit_cast(oe_bf16x8_t, have[nt] ? wp[4 * i] : make_uint4(0, 0, 0, 0));
+      wb[nt][i] = __builtin_bit_cast(oe_bf8_t, have[nt] ? wp[4 * i] : make_uint4(0, 0, 0, 0));
   }
   const int M = 2 * a.B;
   const size_t plane = (size_t)a.B * a.Hq * 2 * kHeadDim;
   for (int m0 = 0; m0 < M; m0 += 16) {
     const int m = m0 + li, mc = m < M ? m : 0;
-    oe_bf16x8_t da[3][4];
+    oe_bf8_t da[3][4];
     {
       const uint16_t* dp = e.dov + (((size_t)(mc >> 1) * a.Hq + j) * 2 + (mc & 1)) * kHeadDim + 8 * lk;
 #pragma unroll
@@ -417,7 +422,7 @@ __global__ __launch_bounds__(256) void outerr_proj_kernel(OutErrArgs e, const ui
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           da[t][i] = __builtin_bit_cast(
-              oe_bf16x8_t, m < M ? *reinterpret_cast<const uint4*>(dp + t * plane + 32 * i) : make_uint4(0, 0, 0, 0));
+              oe_bf8_t, m < M ? *reinterpret_cast<const uint4*>(dp + t * plane + 32 * i) : make_uint4(0, 0, 0, 0));
     }
     oe_f4_t acc[kOeNT];
 #pragma unroll
