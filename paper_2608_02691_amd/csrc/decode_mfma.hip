@@ -1579,7 +1579,8 @@ hipError_t launch_merge_flat(const DecodeArgs& a, bool unrotate, float* out, uin
   // 2,000 with a plain projection 54.6 / 55.5; but with the projection folded 39.8 / 39.0, with windows (32
   // sequences, 40 heads) 91.5 / 82.3, where the blocks of one KV head share what they read.
   const bool rot = unrotate || a.wpart;
-  if ((long long)a.B * a.H < kMergeHeadUnits || (unrotate && !a.wpart)) {
+  // (the sequences are the second grid dimension there, which ends at 65,535)
+  if ((long long)a.B * a.H < kMergeHeadUnits || (unrotate && !a.wpart && a.B <= 65535)) {
     if (rot)
       hipLaunchKernelGGL(merge_head_kernel<true>, dim3(a.Hq, a.B), dim3(kMhThreads), 0, s, a, unrotate ? 1 : 0, out, ob,
                          fmt);
