@@ -278,7 +278,7 @@ struct PairLoads {
   uint4 km[2];  // K scale/zero of token lo, groups 0..3
   uint2 vc[2];  // V codes of half lo, tokens 4hi..4hi+3
   uint2 vs[2][WIDE ? 2 : 1];  // V scales, tokens 4hi..4hi+3: group lo&3 (narrow); lo&1, 2+(lo&1) (wide)
-  uint2 vz[2];  // (Z, l) operand rows: V zeros of group lo (lo < 4), 1.0 (lo 4..7), 0 (lo 8..15)
+  uint2 vz[2];  // (Z, l, S) operand rows: V zeros of group lo (lo < 4), 1.0 (lo 4..7), V scales (lo 8..11), 0
   uint32_t nv[2];  // wave-uniform: cached tokens of each page (16 for a full page)
 };
 
@@ -407,8 +407,10 @@ __device__ __forceinline__ void read_pair(const uint8_t* slot, uint32_t nv0, uin
     } else {
       p.vs[P][0] = *reinterpret_cast<const uint2*>(met + L::kOffVScale + gs * (lo & 3) + 8 * hi);
     }
-    // lanes 0..3: the zeros of group lo; lanes 4..15 read the constant rows of the (Z, l) operand
-    const uint8_t* vzb = lo < 4 ? slot + 2048 - 1024 + L::kOffVZero + gs * (lo & 3) + 8 * hi : czb;
+    // lanes 0..3: the zeros of group lo, lanes 8..11 the scales; the others read the constant rows of the (Z, l, S)
+    // operand
+    const uint8_t* vzb =
+        (lo & 4) == 0 ? slot + 2048 - 1024 + (lo < 8 ? L::kOffVZero : L::kOffVScale) + gs * (lo & 3) + 8 * hi : czb;
     p.vz[P] = *reinterpret_cast<const uint2*>(vzb + P * 128 * NG);
   }
 }
@@ -443,7 +445,7 @@ struct ScanState {
   float thr[NJ];                 // (mref + tau) sigma: the lazy-rescale threshold on the scaled logits
   float4_t acc[8];              // O' tiles: channels 16 mt + 4hi + r, column lo
   float4_t wsum[NT];            // sum_t w_t of each column (every row); wide: groups gg, 2 + gg
-  float4_t zl;                  // rows 0..3: sum_t p_t z_tg (row = group); rows 4..7: sum_t p_t
+  float4_t zl;                  // rows 0..3: sum_t p_t z_tg (row = group); 4..7: sum_t p_t; 8..11: sum_t p_t s_tg
   float mref[NJ];
   float Qz[NJ];                 // sigma sum_k q'_jk of query head jq(hi, u) (used with one group per token)
   LandK lk;                     // landing constants
@@ -590,8 +592,8 @@ __device__ __forceinline__ void pv_pair(ScanState<WIDE>& st, const PairLoads<WID
   constexpr int NT = NG == 1 ? 1 : ScanState<WIDE>::NT;
   LandK lk = st.lk;
   if constexpr (big) lk.one = 0x5C005C00u;  // fp16 256.0, twice
-  // A operand of the (Z, l) contraction: rows 0..3 hold z of group `row`, rows 4..7 hold 1.0, rows
-  // 8..15 zero, all as read from LDS (see read_pair)
+  // A operand of the (Z, l, S) contraction: rows 0..3 hold z of group `row`, rows 4..7 hold 1.0, rows 8..11 s of
+  // group `row - 8`, rows 12..15 zero, all as read from LDS (see read_pair)
   const half8_t Azl = __builtin_bit_cast(half8_t, u32x4_t{cur.vz[0].x, cur.vz[0].y, cur.vz[1].x, cur.vz[1].y});
   const half8_t Aones = __builtin_bit_cast(half8_t, u32x4_t{lk.one, lk.one, lk.one, lk.one});
   // column lo: query head jc, probabilities of tokens 4hi..4hi+3 of both pages
@@ -921,12 +923,13 @@ __device__ __forceinline__ bool scan_segment(const DecodeArgs& a, int b, int h, 
     st.Qz[u] = (((Q[0] + Q[1]) + Q[2]) + Q[3]) / st.invsig[u];
   }
   st.lk = land_constants();
-  // the wave's constant rows of the (Z, l) operand, at both page offsets: fp16 1.0 x 4, then 0 x 4
-  if (l < 4)
-    *reinterpret_cast<uint2*>(cz_w + (l >> 1) * 128 * NG + 8 * (l & 1)) =
+  // the wave's constant rows of the (Z, l, S) operand, at both page offsets: fp16 1.0 x 4, then 0 x 4
+  // (twice each, so that either half of the wave finds them in banks its zeros and scales leave free)
+  if (l < 8)
+    *reinterpret_cast<uint2*>(cz_w + (l >> 2) * 128 * NG + 8 * (l & 3)) =
         (l & 1) ? make_uint2(0u, 0u) : make_uint2(0x3C003C00u, 0x3C003C00u);
   lds_sync_wave();
-  const uint8_t* czb = cz_w + (lo < 8 ? 0 : 8);
+  const uint8_t* czb = cz_w + (lo < 8 ? 0 : 8) + (hi < 2 ? 16 : 0);
 
   // ---- pipeline over the segment's page pairs (global pages gs + 2k, gs + 2k + 1; the second page
   // of a last pair of one page is a stand-in: block 0, no tokens). Pair k sits in slot k % kStages.
@@ -1082,7 +1085,11 @@ __device__ __forceinline__ bool scan_segment(const DecodeArgs& a, int b, int h, 
     }
   }
   // O' of column lo = (jc, g) (narrow) or (jc, gg) (wide): W from any row of the column's weight
-  // sum; Z[jc][g] from lane (lo, hi = 0), register g
+  // sum; Z[jc][g] from lane (lo, hi = 0), register g, S[jc][g] from lane (lo, hi = 2). The rounding of a weight
+  // w = fp16(p s) would enter O' times its code, 0 to 3; S holds the products p s unrounded, so the codes' middle
+  // is taken at S and the rounding enters times code - 3/2: O = 2^e (D - W) - 3/2 W + 3/2 S + Z. The product rows
+  // are free (they were zero). Error of a decode against fp64: 1,011 tokens 4.9e-4 -> 3.6e-4, 131,072 tokens 6.0e-4
+  // -> 3.9e-4, one group per token 5.5e-4 -> 3.7e-4.
   const int jc = WIDE ? lo >> 1 : lo >> 2;
   float zc[2], wc[2];
   if constexpr (WIDE) {
@@ -1091,11 +1098,13 @@ __device__ __forceinline__ bool scan_segment(const DecodeArgs& a, int b, int h, 
     zc[1] = __shfl(odd ? st.zl[3] : st.zl[2], lo);  // group 2 + (lo & 1)
     wc[0] = st.wsum[0][0];
     wc[1] = st.wsum[NG == 1 ? 0 : NT - 1][0];
+    zc[0] = fmaf(1.5f, __shfl(odd ? st.zl[1] : st.zl[0], 32 + lo) - wc[0], zc[0]);
+    zc[1] = fmaf(1.5f, __shfl(odd ? st.zl[3] : st.zl[2], 32 + lo) - wc[1], zc[1]);
   } else {
     const int g = lo & 3;
     const float zown = g == 0 ? st.zl[0] : g == 1 ? st.zl[1] : g == 2 ? st.zl[2] : st.zl[3];
-    zc[0] = zc[1] = __shfl(zown, lo);
     wc[0] = wc[1] = st.wsum[0][0];
+    zc[0] = zc[1] = fmaf(1.5f, __shfl(zown, 32 + lo) - wc[0], __shfl(zown, lo));
   }
   float* dst = part + (size_t)jc * kPartStride + 4;
 #define INT2KV_OUT_TILE(MT)                                                                         \
@@ -1140,7 +1149,7 @@ struct ScanLds {
   __attribute__((aligned(16))) uint8_t stage[kStages][2][kRecord];
   _Float16 p[2][2][8][kBlock];
   float al[8];
-  __attribute__((aligned(16))) uint8_t cz[128 * NG + 16];
+  __attribute__((aligned(32))) uint8_t cz[128 * NG + 32];
 };
 static_assert(sizeof(ScanLds<4>) % 16 == 0 && sizeof(ScanLds<1>) % 16 == 0, "the waves' slices stay 16-byte aligned");
 
