@@ -16,6 +16,8 @@ CASES = [
     ([1], 8, 8), ([16 * 8], 4, 1), ([16 * 8 + 1], 1, 1), ([16 * 29], 32, 8), ([16 * 32 + 5], 8, 2),
     ([1] * 9, 4, 1), ([0, 3, 0, 640, 17, 0], 8, 2), ([16] * 20 + [300], 4, 4), ([64, 65, 63, 1, 0, 129, 40, 31], 8, 1),
     ([5, 700], 20, 10), ([2100], 4, 1),
+    # up to 256 sequences a thread of the split serves a group, beyond it serves sequences
+    ([16, 0, 1, 40] * 64, 4, 1), ([5, 0, 33] * 100, 4, 1),
 ]
 
 
