@@ -25,6 +25,8 @@ ROW_RTOL = 2e-5
 @pytest.mark.parametrize("gq,H,lens,G,scale", [
     (1, 3, [17, 515], 32, 1.0), (2, 2, [16, 129], 128, 2.0 ** -6), (3, 2, [300, 511], 32, 1.0), (4, 2, [1025, 64], 128, 4.0),
     (6, 1, [513, 15], 32, 2.0 ** -6), (8, 1, [255, 700], 128, 1.0), (12, 1, [128, 1], 32, 1.0), (16, 1, [530, 31], 32, 4.0),
+    # more chunks than the merge holds in flight, and more sequences than one 16-row tile of the projection
+    (2, 1, [4700, 2100, 513], 32, 1.0), (1, 1, [40, 7, 520, 16, 33, 90, 1, 64, 17], 128, 1.0),
 ])
 def test_output_error_scores_hold_fp32(gq, H, lens, G, scale):
     print(f"\n[output_error scores] gq={gq} H={H} lens={lens} G={G} scale={scale}", flush=True)
