@@ -958,13 +958,20 @@ __global__ __launch_bounds__(512) void cal_dr_kernel(CalSet S, CalCfg c, int val
 // 16 w .. + 15: the left operand's rows stay in registers (64 per lane), the column block goes through
 // LDS, and a product is 32 fp64 matrix-core steps per wave (1.7 us at the CU's fp64 rate). Bound by that
 // chain of products: per call at 8 heads, exponential 369 -> 40 us and gradient 1,011 -> 90 us (medians
-// over a 20-step calibration) against one work-group of 1,024 threads per head (8 of 256 CUs).
+// over a 20-step calibration, before the squarings below) against one work-group of 1,024 threads per head (8 of 256 CUs).
+// The last kExpSquares of the j doublings are squarings of the finished blocks, a launch each: a column block is one
+// product of the exponential (three of the gradient) there, against 3 + nb - 1 (three times that) for every further
+// application. At 8 heads, means over a 20-step calibration: exponential 49 -> 20 us and 15 for its squarings, gradient
+// 108 -> 43 and 17; one layer's calibration 22.9 -> 18.3 ms.
+// Error against a long-double exponential, 1-norms of S^4 to the power 1/4 from 4 to 27: 3e-16 to 2.3e-15
+// (2e-16 to 2.4e-15 with applications alone).
 // Beyond kExpMaxReps halvings one work-group per head forms all column blocks and squares j times.
 constexpr int kExpCols = 16;      // columns per work-group
 constexpr int kExpThreads = 512;  // eight waves of 16 rows
 constexpr double kExpTheta = 3.5;
 constexpr int kExpMaxBlocks = 9;  // nb at most (theta^32 / 32! < 2^-55)
-constexpr int kExpMaxReps = 5;    // up to 2^5 applications per column block
+constexpr int kExpSquares = 2;    // doublings done by squaring launches
+constexpr int kExpMaxReps = 5;    // halvings (and so up to 2^3 applications) per column block
 // scratch matrices of a head (c.ex): powers of S, then of [[X, G], [0, X]] with X = S^T = -S (upper right
 // blocks: X D_k + G X^k), the exponential's blocks, the column-block bounds on ||S^4||_1
 enum { kExS = 0, kExS2, kExS3, kExS4, kExG, kExD2, kExD3, kExD4, kExP2, kExP1, kExBound };
@@ -1058,6 +1065,9 @@ __device__ __forceinline__ void exp_plan(const double* ex, int& j, int& nb) {
   nb = __builtin_amdgcn_readfirstlane(nb);
 }
 
+// Squaring launches a head needs (none where one work-group forms all of its column blocks).
+__device__ __forceinline__ int exp_squares(int j) { return j > kExpMaxReps ? 0 : min(j, kExpSquares); }
+
 // S, S^2, S^3, S^4 and each column block's largest absolute column sum of S^4.
 __global__ __launch_bounds__(kExpThreads) void cal_exp_powers_kernel(CalCfg c, const double* __restrict__ Aall) {
   __shared__ ExpBuf sm;
@@ -1097,7 +1107,27 @@ __global__ __launch_bounds__(kExpThreads) void cal_exp_powers_kernel(CalCfg c, c
   }
 }
 
-// R = R0 exp(S) and Rt = R^T (fp64).
+// R[:, block] = R0 y and the rows of Rt (fp64), y in LDS.
+__device__ __forceinline__ void exp_finish(const CalCfg& c, int value, int h, int cb, const double* Y, double (&a)[32]) {
+  const float* R0f = (value ? c.R0v : c.R0k) + (size_t)h * kMat;
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const float4* r = reinterpret_cast<const float4*>(R0f + (16 * w + (l & 15)) * kD + 32 * (l >> 4));
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float4 x = r[i];
+    a[4 * i] = x.x;
+    a[4 * i + 1] = x.y;
+    a[4 * i + 2] = x.z;
+    a[4 * i + 3] = x.w;
+  }
+  const f64x4 f = exp_prod(a, Y, f64x4{0.0, 0.0, 0.0, 0.0});
+  exp_store(c.R + (size_t)h * kMat, cb, f);
+  double* Rt = c.Rt + (size_t)h * kMat + (kExpCols * cb + (l & 15)) * kD;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) Rt[exp_row(v)] = f[v];
+}
+
+// R = R0 exp(S) and Rt = R^T, or, where squarings follow, the column blocks of exp(S 2^-squares) into scratch kExP1.
 __global__ __launch_bounds__(kExpThreads) void cal_exp_apply_kernel(CalCfg c, int value) {
   __shared__ ExpBuf sm;
   const int h = blockIdx.y;
@@ -1106,7 +1136,6 @@ __global__ __launch_bounds__(kExpThreads) void cal_exp_apply_kernel(CalCfg c, in
   exp_plan(ex, j, nb);
   const bool alone = j > kExpMaxReps;  // uniform over the head's work-groups
   if (alone && blockIdx.x != 0) return;
-  const float* R0f = (value ? c.R0v : c.R0k) + (size_t)h * kMat;
   double a[32];
   int yb = 0;  // LDS buffer the next column block goes to
   auto put = [&](f64x4 f) {
@@ -1141,29 +1170,15 @@ __global__ __launch_bounds__(kExpThreads) void cal_exp_apply_kernel(CalCfg c, in
     for (int i = nb - 2; i >= 0; --i) p = exp_prod(a, put(p), blk(i));
     return p;
   };
-  auto finish = [&](int cb, f64x4 y) {  // R[:, block] = R0 y
-    const double* Y = put(y);
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const float4* r = reinterpret_cast<const float4*>(R0f + (16 * w + (l & 15)) * kD + 32 * (l >> 4));
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float4 x = r[i];
-      a[4 * i] = x.x;
-      a[4 * i + 1] = x.y;
-      a[4 * i + 2] = x.z;
-      a[4 * i + 3] = x.w;
-    }
-    const f64x4 f = exp_prod(a, Y, zero);
-    exp_store(c.R + (size_t)h * kMat, cb, f);
-    double* Rt = c.Rt + (size_t)h * kMat + (kExpCols * cb + (l & 15)) * kD;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) Rt[exp_row(v)] = f[v];
-  };
   if (!alone) {
     const int cb = blockIdx.x;
+    const int sq = exp_squares(j);
     f64x4 y = poly(cb, true, zero);
-    for (int r = 1; r < (1 << j); ++r) y = poly(cb, false, y);
-    finish(cb, y);
+    for (int r = 1; r < (1 << (j - sq)); ++r) y = poly(cb, false, y);
+    if (sq > 0)
+      exp_store(ex + kExP1 * kMat, cb, y);
+    else
+      exp_finish(c, value, h, cb, put(y), a);
     return;
   }
   double *P = ex + kExP1 * kMat, *Q = ex + kExP2 * kMat;
@@ -1176,7 +1191,32 @@ __global__ __launch_bounds__(kExpThreads) void cal_exp_apply_kernel(CalCfg c, in
     P = Q;
     Q = t;
   }
-  for (int cb = 0; cb < kD / kExpCols; ++cb) finish(cb, exp_load(P, cb, 1.0));
+  for (int cb = 0; cb < kD / kExpCols; ++cb) exp_finish(c, value, h, cb, put(exp_load(P, cb, 1.0)), a);
+}
+
+// Squaring i of the exponential (kExP1 -> kExP2 -> ..); the head's last one goes on to R.
+static_assert(kExpSquares == 2, "the scratch matrices of the squarings alternate between two");
+__global__ __launch_bounds__(kExpThreads) void cal_exp_square_kernel(CalCfg c, int value, int i) {
+  __shared__ ExpBuf sm;
+  const int cb = blockIdx.x, h = blockIdx.y;
+  double* ex = c.ex + (size_t)h * kCalScratch * kMat;
+  int j, nb;
+  exp_plan(ex, j, nb);
+  const int sq = exp_squares(j);
+  if (i >= sq) return;  // uniform
+  const double* P = ex + (i == 0 ? kExP1 : kExP2) * kMat;
+  double a[32];
+  exp_left(P, 1.0, a);
+  exp_block(P, cb, 1.0, sm.y[0]);
+  __syncthreads();
+  const f64x4 f = exp_prod(a, sm.y[0], f64x4{0.0, 0.0, 0.0, 0.0});
+  if (i + 1 < sq) {
+    exp_store(ex + kExP2 * kMat, cb, f);
+    return;
+  }
+  exp_put(sm.y[1], f);
+  __syncthreads();
+  exp_finish(c, value, h, cb, sm.y[1], a);
 }
 
 // Gradient: dL/dA = dS - dS^T with dS = L_exp(S^T, G), G = R0^T dL/dR: the upper right block of
@@ -1225,7 +1265,8 @@ __global__ __launch_bounds__(kExpThreads) void cal_grad_powers_kernel(CalCfg c) 
   }
 }
 
-// The upper right block of the exponential, [128][128] per head, into scratch kExP2.
+// The upper right block of the exponential, [128][128] per head, into scratch kExP2; where squarings follow, that of
+// exp(.. 2^-squares) there and its diagonal block in kExP1.
 __global__ __launch_bounds__(kExpThreads) void cal_grad_apply_kernel(CalCfg c) {
   __shared__ ExpBuf su, sv;
   const int h = blockIdx.y;
@@ -1296,9 +1337,11 @@ __global__ __launch_bounds__(kExpThreads) void cal_grad_apply_kernel(CalCfg c) {
   f64x4 u, v;
   if (!alone) {
     const int cb = blockIdx.x;
+    const int sq = exp_squares(j);
     poly(cb, true, u, v);
-    for (int r = 1; r < (1 << j); ++r) poly(cb, false, u, v);
+    for (int r = 1; r < (1 << (j - sq)); ++r) poly(cb, false, u, v);
     exp_store(ex + kExP2 * kMat, cb, u);
+    if (sq > 0) exp_store(ex + kExP1 * kMat, cb, v);
     return;
   }
   for (int cb = 0; cb < kD / kExpCols; ++cb) {
@@ -1330,10 +1373,34 @@ __global__ __launch_bounds__(kExpThreads) void cal_grad_apply_kernel(CalCfg c) {
     for (int cb = 0; cb < kD / kExpCols; ++cb) exp_store(ex + kExP2 * kMat, cb, exp_load(ex + p2 * kMat, cb, 1.0));
 }
 
+// Squaring i of the gradient's blocks: (P_1, P_2) <- (P_1 P_1, P_1 P_2 + P_2 P_1), from (kExP1, kExP2) to (kExD2,
+// kExD3) and back; the last one needs no P_1.
+__global__ __launch_bounds__(kExpThreads) void cal_grad_square_kernel(CalCfg c, int i) {
+  __shared__ ExpBuf su, sv;
+  const int cb = blockIdx.x;
+  double* ex = c.ex + (size_t)blockIdx.y * kCalScratch * kMat;
+  int j, nb;
+  exp_plan(ex, j, nb);
+  const int sq = exp_squares(j);
+  if (i >= sq) return;  // uniform
+  const double *P1 = ex + (i == 0 ? kExP1 : kExD2) * kMat, *P2 = ex + (i == 0 ? kExP2 : kExD3) * kMat;
+  double a[32], b[32];
+  exp_left(P1, 1.0, a);
+  exp_left(P2, 1.0, b);
+  exp_block(P2, cb, 1.0, su.y[0]);
+  exp_block(P1, cb, 1.0, sv.y[0]);
+  __syncthreads();
+  const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
+  exp_store(ex + (i == 0 ? kExD3 : kExP2) * kMat, cb, exp_prod(a, su.y[0], zero) + exp_prod(b, sv.y[0], zero));
+  if (i + 1 < sq) exp_store(ex + (i == 0 ? kExD2 : kExP1) * kMat, cb, exp_prod(a, sv.y[0], zero));
+}
+
 // grad = dS - dS^T
 __global__ __launch_bounds__(256) void cal_grad_skew_kernel(CalCfg c, double* __restrict__ grad) {
   const int h = blockIdx.y, e = blockIdx.x * 256 + threadIdx.x, r = e / kD, col = e % kD;
-  const double* P = c.ex + ((size_t)h * kCalScratch + kExP2) * kMat;
+  int j, nb;
+  exp_plan(c.ex + (size_t)h * kCalScratch * kMat, j, nb);
+  const double* P = c.ex + ((size_t)h * kCalScratch + (exp_squares(j) == 1 ? kExD3 : kExP2)) * kMat;
   grad[(size_t)h * kMat + e] = P[e] - P[col * kD + r];
 }
 
@@ -1586,6 +1653,7 @@ static void rotation(const CalCfg& c, const double* A, int value, hipStream_t s)
   const dim3 grid(kD / kExpCols, c.H), block(kExpThreads);
   hipLaunchKernelGGL(cal_exp_powers_kernel, grid, block, 0, s, c, A);
   hipLaunchKernelGGL(cal_exp_apply_kernel, grid, block, 0, s, c, value);
+  for (int i = 0; i < kExpSquares; ++i) hipLaunchKernelGGL(cal_exp_square_kernel, grid, block, 0, s, c, value, i);
 }
 
 static void rot_and_quant(const CalCfg& c, CalSet& set, const double* A, int value, hipStream_t s) {
@@ -1603,6 +1671,7 @@ static void backward(const CalCfg& c, CalSet& set, int value, double* grad, hipS
   hipLaunchKernelGGL(cal_grad_g_kernel, grid, block, 0, s, c, value);
   hipLaunchKernelGGL(cal_grad_powers_kernel, grid, block, 0, s, c);
   hipLaunchKernelGGL(cal_grad_apply_kernel, grid, block, 0, s, c);
+  for (int i = 0; i < kExpSquares; ++i) hipLaunchKernelGGL(cal_grad_square_kernel, grid, block, 0, s, c, i);
   hipLaunchKernelGGL(cal_grad_skew_kernel, dim3(kMat / 256, c.H), dim3(256), 0, s, c, grad);
 }
 

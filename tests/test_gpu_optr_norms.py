@@ -1,5 +1,5 @@
 """The matrix exponential of the calibration and its gradient over the norms that change its form: fewer and more
-polynomial blocks, one to thirty-two applications per column block, and the squarings beyond that. Both sides compute
+polynomial blocks, one to eight applications per column block with up to two squarings, and squarings alone beyond that. Both sides compute
 in fp64; exp(S) carries a relative error of about ||S|| eps (1e-13 at the largest norm here, against the library's own
 1e-15), so the bounds of the other calibration tests hold at every norm."""
 import numpy as np
