@@ -43,7 +43,7 @@ KERNEL_SOURCES = {
     "decode_scan": ("decode_mfma.hip", "append_core.h") + _COMMON,
     "qprep": ("decode_mfma.hip", "append_core.h") + _COMMON,
     "merge": ("decode_mfma.hip", "append_core.h") + _COMMON,
-    "append": ("append.hip", "append_core.h") + _COMMON,
+    "append": ("append.hip", "append_core.h", "append_wide.h") + _COMMON,
     "wo": ("wo_gemm.hip",) + _COMMON,
     "wo_reduce": ("wo_gemm.hip",) + _COMMON,
     "outerr_scan": ("outerr.hip",) + _COMMON,
