@@ -165,8 +165,9 @@ __global__ __launch_bounds__(kApThreads, 2) void append_mfma_kernel(CacheView cv
                                                                     const float* __restrict__ mu_rk, float clip_k,
                                                                     float clip_v, float* __restrict__ err, ApOpts opt) {
   __shared__ ApLds lds;
+  __shared__ __attribute__((aligned(16))) int pos[ROPE ? kApPos : 4];
   append_block<NG, ERR, ROPE>(cv, k, v, slots, n, R_k, R_v, mu_rk, clip_k, clip_v, (int)blockIdx.x, (int)gridDim.x,
-                              (int)blockIdx.y, (int)blockIdx.z, lds, err, opt);
+                              (int)blockIdx.y, (int)blockIdx.z, lds, pos, err, opt);
 }
 
 // Long dense appends: grid as above, eight waves.

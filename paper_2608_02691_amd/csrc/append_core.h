@@ -59,6 +59,7 @@ struct ApLds {
   __attribute__((aligned(16))) float sub[kHeadDim];              // - mu R_K (keys), 0 (values)
   float recip[1024];                                             // RN(1 / (1 + m / 1024))
 };
+constexpr int kApPos = kApStages * kApThreads;  // ints of the staged positions, laid out as ApLds::slot
 constexpr int kAppendLdsBytes = sizeof(ApLds);
 
 // x / 3 correctly rounded, as a product with RN(1/3) and one FMA correction: checked against the
@@ -266,12 +267,14 @@ __device__ __forceinline__ void ap_dma4(const void* p, uint32_t lds) {
 // One append work-group (kApThreads threads): KV head h, K (kv = 0) or V (kv = 1), block bx of nbx striding over
 // the 32-token tiles. Every thread of the block must call it (it synchronizes). TERMS: 3 (dense R) or 1
 // (Hadamard). With ERR, err[(token * H + h) * 2 + kv] receives each token's squared reconstruction error. With
-// ROPE (keys only), opt carries the positions and table.
-template <int NG, bool ERR, bool ROPE, int TERMS>
+// ROPE (keys), opt carries the positions and table; with POS (values of such a write) the positions only, so that a
+// token skipped for its position keeps both halves of its row: pos_lds then
+// holds kApPos ints.
+template <int NG, bool ERR, bool ROPE, bool POS, int TERMS>
 __device__ __forceinline__ void append_tiles(const CacheView& cv, const uint16_t* __restrict__ X,
                                              const int32_t* __restrict__ slots, int n, const float* __restrict__ R,
                                              const float* __restrict__ mu_rk, float clip, int bx, int nbx, int h, int kv,
-                                             ApLds& L, float* __restrict__ err, const ApOpts& opt) {
+                                             ApLds& L, int* pos_lds, float* __restrict__ err, const ApOpts& opt) {
   using Lay = Rec<NG>;
   const int H = cv.num_kv_heads, tid = threadIdx.x, l = tid & 63;
   const int g = __builtin_amdgcn_readfirstlane(tid >> 6);  // the wave's group
@@ -294,7 +297,7 @@ __device__ __forceinline__ void append_tiles(const CacheView& cv, const uint16_t
   int tok_ld = token(0);
   const uint16_t* row_ld = X + ((size_t)min(tok_ld, n - 1) * H + h) * kHeadDim + 8 * j;
   const int32_t* slot_ld = slots + min(tok_ld, n - 1);
-  const int32_t* pos_ld = ROPE ? opt.pos + min(tok_ld, n - 1) : nullptr;
+  const int32_t* pos_ld = ROPE || POS ? opt.pos + min(tok_ld, n - 1) : nullptr;
   auto load = [&](Pre& p) {
     const bool more = tok_ld + hop < n;
     if constexpr (ROPE) {
@@ -386,7 +389,8 @@ __device__ __forceinline__ void append_tiles(const CacheView& cv, const uint16_t
     }
   }
   const uint32_t x_lds = (uint32_t)(uintptr_t)&L.x[0][0] + 2048 * g, slot_lds = (uint32_t)(uintptr_t)&L.slot[0][0] + 256 * g;
-  constexpr int kDma = 3;  // operations per tile and wave
+  const uint32_t pos_dst = POS ? (uint32_t)(uintptr_t)pos_lds + 256 * g : 0u;
+  constexpr int kDma = POS ? 4 : 3;  // operations per tile and wave
   auto dma = [&](int stage) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -395,6 +399,10 @@ __device__ __forceinline__ void append_tiles(const CacheView& cv, const uint16_t
       tok_dma[u] += hop;
     }
     ap_dma4(slot_ld, slot_lds + (uint32_t)(stage * kApThreads * 4));
+    if constexpr (POS) {
+      ap_dma4(pos_ld, pos_dst + (uint32_t)(stage * kApThreads * 4));
+      pos_ld += tok_ld + hop < n ? hop : 0;
+    }
     slot_ld += tok_ld + hop < n ? hop : 0;
     tok_ld += hop;
   };
@@ -530,6 +538,10 @@ __device__ __forceinline__ void append_tiles(const CacheView& cv, const uint16_t
       slot_prev = slot;
       const int sl = L.slot[stage][tid];
       slot = token(i) < n ? sl : -1;
+      if constexpr (POS) {
+        const int pos = pos_lds[stage * kApThreads + tid];
+        if (pos < 0 || pos >= opt.max_pos) slot = -1;
+      }
       if (i > 1) finish(i - 2, slot_done);
       dma(stage == 0 ? kApStages - 1 : stage - 1);
       product(L.x[stage], cur);
@@ -561,21 +573,21 @@ __device__ __forceinline__ void append_block(const CacheView& cv, const uint16_t
                                              const uint16_t* __restrict__ v, const int32_t* __restrict__ slots,
                                              int n, const float* __restrict__ R_k, const float* __restrict__ R_v,
                                              const float* __restrict__ mu_rk, float clip_k, float clip_v, int bx,
-                                             int nbx, int h, int kv, ApLds& L, float* __restrict__ err = nullptr,
-                                             const ApOpts& opt = ApOpts{}) {
+                                             int nbx, int h, int kv, ApLds& L, int* pos_lds = nullptr,
+                                             float* __restrict__ err = nullptr, const ApOpts& opt = ApOpts{}) {
   const uint16_t* X = kv == 0 ? k : v;
   const float clip = kv == 0 ? clip_k : clip_v;
   const bool had = ((opt.had >> kv) & 1) != 0;
   const float* R = had ? nullptr : (kv == 0 ? R_k : R_v) + (size_t)h * kHeadDim * kHeadDim;
   if (ROPE && kv == 0) {
     if (had)
-      append_tiles<NG, ERR, ROPE, 1>(cv, X, slots, n, R, mu_rk, clip, bx, nbx, h, kv, L, err, opt);
+      append_tiles<NG, ERR, ROPE, false, 1>(cv, X, slots, n, R, mu_rk, clip, bx, nbx, h, kv, L, pos_lds, err, opt);
     else
-      append_tiles<NG, ERR, ROPE, 3>(cv, X, slots, n, R, mu_rk, clip, bx, nbx, h, kv, L, err, opt);
+      append_tiles<NG, ERR, ROPE, false, 3>(cv, X, slots, n, R, mu_rk, clip, bx, nbx, h, kv, L, pos_lds, err, opt);
   } else if (had) {
-    append_tiles<NG, ERR, false, 1>(cv, X, slots, n, R, mu_rk, clip, bx, nbx, h, kv, L, err, opt);
+    append_tiles<NG, ERR, false, ROPE, 1>(cv, X, slots, n, R, mu_rk, clip, bx, nbx, h, kv, L, pos_lds, err, opt);
   } else {
-    append_tiles<NG, ERR, false, 3>(cv, X, slots, n, R, mu_rk, clip, bx, nbx, h, kv, L, err, opt);
+    append_tiles<NG, ERR, false, ROPE, 3>(cv, X, slots, n, R, mu_rk, clip, bx, nbx, h, kv, L, pos_lds, err, opt);
   }
 }
 

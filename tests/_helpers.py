@@ -69,6 +69,17 @@ def unpack_slots(pool: np.ndarray, slots: np.ndarray):
     return [np.stack(x, axis=1) for x in out]
 
 
+def slot_bytes(pool: np.ndarray) -> np.ndarray:
+    """Every byte of each slot's row, [num_blocks * 16, H, 64 + 8 groups]: K codes, V codes, K (s, z), V (s, z)."""
+    nb, H, rec = pool.shape
+    ng = {1536: 4, 1152: 1}[rec]
+    tok = lambda a: a.transpose(0, 1, 3, 2, 4).reshape(nb, H, 16, -1)  # token-minor runs of 2 bytes
+    kc, km = pool[..., :512].reshape(nb, H, 16, 32), pool[..., 1024:1024 + 64 * ng].reshape(nb, H, 16, 4 * ng)
+    vc, vm = pool[..., 512:1024].reshape(nb, H, 16, 16, 2), pool[..., 1024 + 64 * ng:].reshape(nb, H, 2 * ng, 16, 2)
+    rows = np.concatenate([kc, tok(vc), km, tok(vm)], axis=-1)
+    return rows.transpose(0, 2, 1, 3).reshape(nb * 16, H, -1)
+
+
 def compare_cache_writes(pool_gpu, pool_ref, slots, k_rot, v_rot):
     """End-to-end cache-write parity. Codes may differ from the oracle's only at rounding ties:
     either the group's fp16 scale or zero is one ulp away (its fp32 value sat at an fp16 rounding

@@ -9,7 +9,7 @@ from oracle import int2kv_oracle as O
 from paper_2608_02691_amd import int2kv as K
 from paper_2608_02691_amd import workloads as W
 
-from _helpers import dev
+from _helpers import dev, slot_bytes
 
 pytestmark = pytest.mark.gpu
 
@@ -58,3 +58,37 @@ def test_rope_rounding_edges(kind, n):
     with np.errstate(over="ignore"):
         ref = O.rope(k, pos, cs)
     assert np.array_equal(got, ref), (kind, np.argwhere(got != ref)[:3])
+
+
+# 40 tokens: one tile and a part; 3,100 at 8 heads: several tiles of 32 per work-group on any count of CUs up to 384
+@pytest.mark.parametrize("G", [32, 128])
+@pytest.mark.parametrize("had", [0, 1, 2, 3])
+@pytest.mark.parametrize("n,H", [(40, 2), (3100, 8)])
+def test_skipped_positions_leave_their_rows(n, H, had, G):
+    """A token whose position lies outside the table writes nothing, key or value: the call stores what it would store
+    with that token's slot at -1, over a cache that held other bytes."""
+    print(f"\n[rope skip] n={n} H={H} hadamard={had} G={G}", flush=True)
+    rng = np.random.default_rng([n, had, G])
+    bits = lambda *s: W.f32_to_bf16_bits(rng.standard_normal(s).astype(np.float32))
+    k, v, P = bits(n, H, 128), bits(n, H, 128), 512
+    blocks = (n + 15) // 16 + 1
+    slots = rng.permutation(blocks * 16)[:n].astype(np.int32)
+    pos = rng.integers(0, P, n).astype(np.int32)
+    bad = rng.random(n) < 0.2
+    bad[[0, n - 1]] = True
+    pos[bad] = rng.choice([-1, -2**31, P, P + 7, 2**31 - 1], int(bad.sum()))
+    R = K.hadamard_rotation(H)
+    mu_rk = torch.zeros((H, 128), dtype=torch.float32, device="cuda")
+    before = rng.integers(0, 256, (blocks, H, K.RECORD_BYTES_BY_GROUP[G]), dtype=np.uint8)
+    pools = []
+    for sl, ps in ((slots, pos), (np.where(bad, -1, slots).astype(np.int32), np.where(bad, 0, pos).astype(np.int32))):
+        cache = K.Int2KVCache(blocks, H, pool=torch.from_numpy(before.copy()).cuda(), group_size=G)
+        K.int2kv_quantize_append_rope(cache, dev(k), dev(v), dev(sl), dev(ps), dev(W.rope_cos_sin(P)), R, R, mu_rk,
+                                      flags=had)
+        pools.append(cache.pool.cpu().numpy())
+    same = slot_bytes(pools[0]) == slot_bytes(before)
+    unnamed = np.ones(blocks * 16, bool)
+    unnamed[slots[~bad]] = False
+    assert same[unnamed].all(), "rows of skipped tokens and of no token stay as they were"
+    assert not same[~unnamed].all(axis=-1).any(), "every other row is written"
+    assert np.array_equal(pools[0], pools[1])
