@@ -75,6 +75,15 @@ __device__ __forceinline__ void bf16x8_to_f64(uint4 u, double (&d)[8]) {
   }
 }
 
+// 16 bytes of an input that has no alignment beyond its type's (q, R^0, A and W_O; one 16-byte load all the same).
+template <class V, class T>
+__device__ __forceinline__ V load16(const T* p) {
+  static_assert(sizeof(V) == 16, "one 16-byte piece");
+  V v;
+  __builtin_memcpy(&v, p, sizeof(v));
+  return v;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Rows times a 128 x 128 matrix on the fp64 matrix cores, as out^T = Bm^T y^T: M = the 128 output
 // channels (eight 16-row tiles), N = the wave's 16 rows y (lane l holds row l % 16), K = the 128
@@ -240,7 +249,7 @@ __device__ __forceinline__ void rows_operand_bf16(const uint16_t* row, bool ok, 
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
     double d[8];
-    bf16x8_to_f64(ok ? *reinterpret_cast<const uint4*>(row + 32 * lk + 8 * g) : make_uint4(0, 0, 0, 0), d);
+    bf16x8_to_f64(ok ? load16<uint4>(row + 32 * lk + 8 * g) : make_uint4(0, 0, 0, 0), d);
 #pragma unroll
     for (int i = 0; i < 8; ++i) x[8 * g + i] = d[i];
   }
@@ -817,7 +826,7 @@ __global__ __launch_bounds__(128) void cal_gxz_kernel(CalSet S, CalCfg c, int va
     for (int r0 = r_lo; r0 < r_hi; r0 += 4) {
       const int r = min(r0 + lk, nr - 1), pos = r / c.gq;
       double y[8];
-      bf16x8_to_f64(*reinterpret_cast<const uint4*>(qr + (size_t)pos * step + (size_t)(r - pos * c.gq) * kD), y);
+      bf16x8_to_f64(load16<uint4>(qr + (size_t)pos * step + (size_t)(r - pos * c.gq) * kD), y);
       const double x = pd[(size_t)r * sq.len], p = ok && r0 + lk < r_hi ? x * kInvSqrtD : 0.0;
 #pragma unroll
       for (int t = 0; t < 8; ++t) acc[t] = mfma64(y[t], p, acc[t]);
@@ -995,10 +1004,10 @@ struct ExpBuf {
 // Rows 16 w + li of M (row-major, times sign) as the left operand: lane (li, lk) holds M[16 w + li][32 lk + s].
 __device__ __forceinline__ void exp_left(const double* M, double sign, double (&a)[32]) {
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const double2* r = reinterpret_cast<const double2*>(M + (16 * w + (l & 15)) * kD + 32 * (l >> 4));
+  const double* r = M + (16 * w + (l & 15)) * kD + 32 * (l >> 4);  // of the scratch, or the caller's A
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
-    const double2 x = r[i];
+    const double2 x = load16<double2>(r + 2 * i);
     a[2 * i] = sign * x.x;
     a[2 * i + 1] = sign * x.y;
   }
@@ -1111,10 +1120,10 @@ __global__ __launch_bounds__(kExpThreads) void cal_exp_powers_kernel(CalCfg c, c
 __device__ __forceinline__ void exp_finish(const CalCfg& c, int value, int h, int cb, const double* Y, double (&a)[32]) {
   const float* R0f = (value ? c.R0v : c.R0k) + (size_t)h * kMat;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const float4* r = reinterpret_cast<const float4*>(R0f + (16 * w + (l & 15)) * kD + 32 * (l >> 4));
+  const float* r = R0f + (16 * w + (l & 15)) * kD + 32 * (l >> 4);
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const float4 x = r[i];
+    const float4 x = load16<float4>(r + 4 * i);
     a[4 * i] = x.x;
     a[4 * i + 1] = x.y;
     a[4 * i + 2] = x.z;
@@ -1480,8 +1489,7 @@ __global__ __launch_bounds__(512) void cal_gram_kernel(const uint16_t* __restric
   bool okr = false;
   auto fetch = [&](int r0) {
     okr = r0 + rr < n_hi;
-    // W_O has no alignment beyond its type's
-    __builtin_memcpy(&xr, W + (size_t)(okr ? r0 + rr : n_lo) * ld + (size_t)j * kD + c8, 16);
+    xr = load16<uint4>(W + (size_t)(okr ? r0 + rr : n_lo) * ld + (size_t)j * kD + c8);
   };
   if (n_lo < n_hi) fetch(n_lo);
   for (int r0 = n_lo; r0 < n_hi; r0 += kGramRows) {

@@ -76,3 +76,33 @@ def test_few_or_no_int2_tokens(lens, sink, recent):
             # absolute terms: with no INT2 token both are zero up to the rounding of the softmaxes' sums
             assert abs(float(got_l[h]) - float(ref.detach())) <= 1e-9 * abs(float(ref.detach())) + 1e-14
             assert np.linalg.norm(got_g[h].cpu().numpy() - g) <= 1e-7 * np.linalg.norm(g) + 1e-13
+
+
+def test_inputs_of_any_alignment():
+    """q, R^0, A, mu and W_O need no alignment beyond their types': one element past an aligned address, the losses and
+    gradients are the same bits."""
+    H, Hq, lens = 2, 4, [50, 41]
+    w = W.make_workload(1, batch=1, ctx=16, num_q_heads=Hq, num_kv_heads=H, d_model=64)
+    rng = np.random.default_rng(7)
+    T = sum(lens)
+    bits = lambda *s: W.f32_to_bf16_bits(rng.standard_normal(s).astype(np.float32))
+    k, v, q, st = bits(T, H, 128), bits(T, H, 128), bits(T, Hq, 128), np.cumsum([0] + lens).astype(np.int32)
+    mu = P.key_mean(k)
+    cfg = K.optr_config(H, Hq, 64, group_size=32, n_last=12, sink=4, recent=9)
+    A, Av = rng.standard_normal((2, H, 128, 128)) * 0.02
+
+    def run(put):
+        tr = K.OptrTraces(dev(k), dev(v), put(q), st)
+        key = K.int2kv_optr_key_loss(cfg, tr, put(w.R_k), put(mu), put(w.W_o), put(A))
+        value = K.int2kv_optr_value_loss(cfg, tr, put(w.R_k), put(A), put(mu), put(w.R_v), put(w.W_o), put(Av))
+        return [x.cpu() for x in key + value]
+
+    def shifted(a):
+        x = dev(a)
+        at = torch.empty(x.numel() + 1, dtype=x.dtype, device="cuda")[1:].view(x.shape)
+        at.copy_(x)
+        assert at.data_ptr() % 16 == x.element_size()
+        return at
+
+    for aligned, odd in zip(run(dev), run(shifted)):
+        assert torch.equal(aligned, odd)
