@@ -15,6 +15,8 @@
 // are folded into the query operand (scaled by 2^e per channel, with sum_k A_k subtracted through
 // the accumulator's initial value); for the values they are removed from the accumulator at the
 // end (O = 2^e (D - sum_t w_t)), using the exact fp16 weights the matrix core multiplied.
+#include <type_traits>
+
 #include "append_core.h"
 #include "common.h"
 #include "kernels.h"
@@ -1371,7 +1373,13 @@ __global__ __launch_bounds__(kMhThreads) void merge_head_kernel(DecodeArgs a, in
   }
 }
 
-template <int kMergeSlots>
+// Merge with a block per (sequence, KV head); WIN: with the BF16-window partials. A wave's slot is uniform, so the range
+// bounds, the partials' addresses and their (m, l) live in scalar registers: 62 to 91 vector registers at four and
+// eight slots, without and with windows, against 127 and the cap of 128 with four spilled when the slot was per lane and
+// the windows a branch. Us a call, that form / this one: 28 x 3,000 tokens, 40/8 heads, projection folded 44.7 / 43.9; 24 x
+// 100..1,000, 32/8 heads 28.5 / 27.6; 28 x 3,000 with windows 66.7 / 65.0; 64 x 500..2,000 48.0 / 47.5; eight query heads
+// per KV head 0.3 to 0.5 us slower (68.5 / 69.0 with windows).
+template <int kMergeSlots, bool WIN>
 __global__ __launch_bounds__(128 * kMergeSlots) void merge_flat_kernel(DecodeArgs a, int unrotate,
                                                                        float* __restrict__ out,
                                                                        uint16_t* __restrict__ ob, int fmt) {
@@ -1379,12 +1387,13 @@ __global__ __launch_bounds__(128 * kMergeSlots) void merge_flat_kernel(DecodeArg
   __shared__ float os[kMergeSlots][8][kHeadDim];
   __shared__ float vs[8][kHeadDim];
   __shared__ float wsh[8][kHeadDim];  // BF16-window part of each head output (model basis)
-  const int b = blockIdx.x, h = blockIdx.y, c = threadIdx.x & 127, sl = threadIdx.x >> 7, gq = a.gq;
+  const int b = blockIdx.x, h = blockIdx.y, c = threadIdx.x & 127, gq = a.gq;
+  const int sl = __builtin_amdgcn_readfirstlane(threadIdx.x >> 7);  // a wave lies in one slot
   // the BF16-window partials of this thread's query heads (model basis, one per window slice), all
   // loaded first (slices past win_slices read slice 0 and are dropped), folded in below
   constexpr int kR = 8 / kMergeSlots;
   float wm[kR][kWinMaxSlices], wl[kR][kWinMaxSlices], wo[kR][kWinMaxSlices];
-  if (a.wpart) {
+  if constexpr (WIN) {
 #pragma unroll
     for (int r = 0; r < kR; ++r)
 #pragma unroll
@@ -1464,7 +1473,7 @@ __global__ __launch_bounds__(128 * kMergeSlots) void merge_flat_kernel(DecodeArg
     float Mx = -INFINITY;
 #pragma unroll
     for (int t = 0; t < kMergeSlots; ++t) Mx = fmaxf(Mx, ms[t][jj]);
-    if (a.wpart) {
+    if constexpr (WIN) {
 #pragma unroll
       for (int s = 0; s < kWinMaxSlices; ++s) Mx = fmaxf(Mx, wm[r][s]);
     }
@@ -1476,7 +1485,7 @@ __global__ __launch_bounds__(128 * kMergeSlots) void merge_flat_kernel(DecodeArg
       L = fmaf(f, ls[t][jj], L);
       O = fmaf(f, os[t][jj][c], O);
     }
-    if (a.wpart) {
+    if constexpr (WIN) {
 #pragma unroll
       for (int s = 0; s < kWinMaxSlices; ++s) {
         const float f = wm[r][s] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(wm[r][s] - Mx);
@@ -1487,7 +1496,7 @@ __global__ __launch_bounds__(128 * kMergeSlots) void merge_flat_kernel(DecodeArg
     val[r] = L > 0.0f ? O / L : 0.0f;
     wval[r] = L > 0.0f ? Ow / L : 0.0f;
   }
-  if (!a.wpart && !unrotate) {
+  if (!WIN && !unrotate) {
 #pragma unroll
     for (int r = 0; r < 8 / kMergeSlots; ++r) {
       const int jj = sl + kMergeSlots * r;
@@ -1539,7 +1548,7 @@ __global__ __launch_bounds__(128 * kMergeSlots) void merge_flat_kernel(DecodeArg
 #pragma unroll
   for (int r = 0; r < 8 / kMergeSlots; ++r) {
     const int jj = sl + kMergeSlots * r;
-    float o = a.wpart ? add[jj][c] : 0.0f;
+    float o = WIN ? add[jj][c] : 0.0f;
 #pragma unroll
     for (int t = 0; t < kMergeSlots; ++t) o += os[t][jj][c];
     if (jj < gq)
@@ -1600,12 +1609,18 @@ hipError_t launch_merge_flat(const DecodeArgs& a, bool unrotate, float* out, uin
                          fmt);
     else
       hipLaunchKernelGGL(merge_head_kernel<false>, dim3(a.Hq, a.B), dim3(kMhThreads), 0, s, a, 0, out, ob, fmt);
-  } else if (a.B >= 32) {
+  } else {
     // four slots when many sequences share the work-groups (short spans; fewer idle waves to
     // dispatch), eight for fewer, longer sequences (fewer rounds of loads)
-    hipLaunchKernelGGL(merge_flat_kernel<4>, dim3(a.B, a.H), dim3(128 * 4), 0, s, a, unrotate ? 1 : 0, out, ob, fmt);
-  } else {
-    hipLaunchKernelGGL(merge_flat_kernel<8>, dim3(a.B, a.H), dim3(128 * 8), 0, s, a, unrotate ? 1 : 0, out, ob, fmt);
+    auto go = [&](auto slots_tag, auto win_tag) {
+      constexpr int kSlots = decltype(slots_tag)::value;
+      hipLaunchKernelGGL((merge_flat_kernel<kSlots, decltype(win_tag)::value>), dim3(a.B, a.H), dim3(128 * kSlots), 0, s,
+                         a, unrotate ? 1 : 0, out, ob, fmt);
+    };
+    auto slots = [&](auto win_tag) {
+      a.B >= 32 ? go(std::integral_constant<int, 4>{}, win_tag) : go(std::integral_constant<int, 8>{}, win_tag);
+    };
+    a.wpart ? slots(std::true_type{}) : slots(std::false_type{});
   }
   return hipGetLastError();
 }
