@@ -1597,13 +1597,20 @@ hipError_t launch_decode_split_mfma(const DecodeArgs& a, hipStream_t s, hipEvent
 
 hipError_t launch_merge_flat(const DecodeArgs& a, bool unrotate, float* out, uint16_t* ob, int fmt, hipStream_t s) {
   if (a.gq > 8) return hipErrorNotSupported;
-  // A block per query head for small batches, and at every size for the un-rotation alone (the block per KV head
-  // reads R_V in 64-byte pieces): us a call, per head / per KV head, 16 x 4,096 tokens un-rotated 26.9 / 33.9, 64 x
-  // 2,000 with a plain projection 54.6 / 55.5; but with the projection folded 39.8 / 39.0, with windows (32
-  // sequences, 40 heads) 91.5 / 82.3, where the blocks of one KV head share what they read.
+  // A block per query head while the blocks fill the chip once: with R_V in LDS two fit on a CU; without it the block per
+  // KV head, which shares the slots' loads, already wins from one and a half per CU. Beyond, every further block
+  // brings its 64 KiB of R_V once more, so it stays only for the un-rotation at one query head per KV head, where the
+  // other form computes eight. Us a call, per query head / per KV head (256 CUs). Un-rotated: 16 x 4,000 tokens at 8 KV
+  // heads and 24, 32, 40 query heads (384, 512, 640 blocks) 25.3 / 26.4, 25.9 / 27.6, 29.9 / 28.6; 64 x 500..2,000 at 1/8
+  // heads (512) 21.3 / 25.5; 256 x 64..200 at 1/4 heads (1,024) 20.8 / 17.4; 1,024 x 64..200 at 8/32 heads 280 / 139, at 4/32
+  // heads 263 / 85, at 8/8 heads 118 / 137. Folded: 12 x 3,000 at 8/32 heads (384) 30.5 / 30.8, 28 x 2,000 at 8/16 heads (448)
+  // 31.9 / 29.8, 28 x 3,000 at 4/32 heads (896) 40.6 / 35.2. Windows, folded: 8 x 4,000 at 8/64 heads (512) 60.4 / 62.5, 28 x
+  // 3,000 at 4/32 heads (896) 56.9 / 51.3.
   const bool rot = unrotate || a.wpart;
+  const long long blocks = (long long)a.B * a.Hq;
+  const int cus = num_cus();
   // (the sequences are the second grid dimension there, which ends at 65,535)
-  if ((long long)a.B * a.H < kMergeHeadUnits || (unrotate && !a.wpart && a.B <= 65535)) {
+  if (blocks <= (rot ? 2 * cus : cus + cus / 2) || (unrotate && a.gq == 1 && a.B <= 65535)) {
     if (rot)
       hipLaunchKernelGGL(merge_head_kernel<true>, dim3(a.Hq, a.B), dim3(kMhThreads), 0, s, a, unrotate ? 1 : 0, out, ob,
                          fmt);

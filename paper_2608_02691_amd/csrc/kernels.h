@@ -84,7 +84,6 @@ struct WindowArgs {
 constexpr int kWinMaxGq = 16;
 constexpr int kWinMaxCap = 512;
 constexpr int kWinSliceTokens = 96;                            // window tokens per partial
-constexpr int kMergeHeadUnits = 128;   // a merge block per query head when batch x KV heads is below this
 // window partials per (sequence, query head)
 constexpr int kWinMaxSlices = (kWinMaxCap + kWinSliceTokens - 1) / kWinSliceTokens;
 hipError_t launch_window_write(const uint16_t* k, const uint16_t* v, const int32_t* rows, int n, int H, const float* mu,

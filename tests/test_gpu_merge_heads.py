@@ -55,3 +55,34 @@ def test_merge_per_query_head(case, window, wo):
         ref = O.decode(pool, w.q, w.block_table, w.ctx_lens, w.R_k, w.R_v, ref_wo)
     torch.cuda.synchronize()
     assert_rows_close(out.cpu().numpy(), ref, what=f"{case} {window} {wo}")
+
+
+# (sequences, query heads, KV heads) on both sides of two and of one and a half blocks per CU at 256 CUs, at under and
+# over 32 sequences (eight and four slots); one query head per KV head at any size
+@pytest.mark.parametrize("B,Hq,H", [(128, 4, 1), (129, 4, 1), (16, 32, 8), (17, 32, 8), (12, 32, 4), (13, 32, 4), (31, 24, 3),
+                                    (600, 1, 1), (70, 9, 9)])
+@pytest.mark.parametrize("window", [0, 100])
+@pytest.mark.parametrize("wo", ["none", "folded"])
+def test_merge_block_counts(B, Hq, H, window, wo):
+    rng = np.random.default_rng([B, Hq, window])
+    lens = rng.integers(0, 60, B)
+    lens[:2] = 0, 700
+    dm = 0 if wo == "none" else 32
+    w = W.make_workload(1, batch=B, ctx_lens=lens, num_q_heads=Hq, num_kv_heads=H, d_model=dm or None)
+    cache, pool = _random_cache(w, rng, 128)
+    args = (dev(w.q), dev(w.block_table), dev(w.ctx_lens), int(lens.max()), dev(w.R_k), dev(w.R_v))
+    kw = {}
+    if dm:
+        kw = dict(W_o=K.int2kv_prepare_wo(dev(w.W_o), dev(w.R_v), Hq), wo_format=K.INT2KV_WO_PREPARED_FOLDED, d_model=dm)
+    ref_wo = w.W_o if dm else None
+    if window:
+        wk, wv = (W.f32_to_bf16_bits(rng.standard_normal((B, window, H, 128)).astype(np.float32)) for _ in range(2))
+        wl = rng.integers(0, window + 1, B).astype(np.int32)
+        out = K.int2kv_decode_window(cache, *args, dev(wk.reshape(-1, H, 128)), dev(wv.reshape(-1, H, 128)), dev(wl),
+                                     window, **kw)
+        ref = O.decode_window(pool, w.q, w.block_table, w.ctx_lens, w.R_k, w.R_v, wk, wv, wl, ref_wo)
+    else:
+        out = K.int2kv_decode(cache, *args, **kw)
+        ref = O.decode(pool, w.q, w.block_table, w.ctx_lens, w.R_k, w.R_v, ref_wo)
+    torch.cuda.synchronize()
+    assert_rows_close(out.cpu().numpy(), ref, what=f"{B} {Hq}/{H} {window} {wo}")
