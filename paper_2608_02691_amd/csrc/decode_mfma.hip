@@ -825,9 +825,11 @@ __device__ void page_list_block(const DecodeArgs& a, int b, int p0, uint8_t* lds
 // per sequence). Lower block ids are dispatched first. The roles share one LDS buffer.
 constexpr int kPrepLdsBytes = kAppendLdsBytes > kQpLdsBytes ? kAppendLdsBytes : kQpLdsBytes;
 
-// AP: the launch carries append blocks.
+// AP: the launch carries append blocks, whose registers set the work-groups per CU: capped so that two fit (260 vector and
+// accumulation registers without the cap, one work-group per CU; 254 with it). Us a step at 32/8 heads, one / two: 64 x
+// 64..200 tokens 35.2 / 33.6, 128 x 46.3 / 43.3, 256 x 70.0 / 62.7, 256 x 2,000 125.7 / 119.1; 1,011 tokens 23.5 / 23.1.
 template <bool AP>
-__global__ __launch_bounds__(256) void qprep_kernel(DecodeArgs a, int wide, int nq, int nseg, AppendArgs ap, int nap) {
+__global__ __launch_bounds__(256, AP ? 2 : 1) void qprep_kernel(DecodeArgs a, int wide, int nq, int nseg, AppendArgs ap, int nap) {
   __shared__ __attribute__((aligned(16))) uint8_t lds[AP ? kPrepLdsBytes : kQpLdsBytes];
   int blk = blockIdx.x;
   if (AP && blk < nap) {
