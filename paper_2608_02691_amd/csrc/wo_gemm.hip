@@ -162,7 +162,8 @@ __global__ __launch_bounds__(256) void wo_mfma_kernel(const uint16_t* __restrict
 // slices meet in LDS (summed in wave order) and there are no partials in memory and no second launch. A wave
 // issues all loads of kWoRowSteps pieces, weights and o, straight into operand registers before its products.
 // Bound by the weights' stream (33.5 MB at 4,096 x 4,096). In the row-major format a lane takes 16
-// consecutive k of a piece (8 for each of its two products), so a row's four lanes read whole 128-byte lines;
+// consecutive k of a piece (8 for each of its two products): each of its two loads takes every other 16 bytes of a row's
+// 128-byte line, so the lines are fetched whole but in halves;
 // prepared tiles are read in their own order, 1 KiB at a time. Wider batches use the tiles above, whose 64 batch
 // rows share the o operand (here every block reads all of it). Us a step, against
 // tiles, partials and their sum: 32/8 heads, 1,011 tokens 27.5 -> 23.5; 16 x 4,096 tokens 39.1 -> 34.9; row-major weights,
@@ -242,6 +243,33 @@ __global__ __launch_bounds__(64 * kWoRowWaves) void wo_rows_kernel(const uint16_
   }
 }
 
+// Whether a projection runs as one launch of 16-row blocks rather than tiles, partials and their sum. Every block reads
+// all of o, so B x K bounds it, less where the blocks are a quarter to a half more than the CUs (the last round leaves most
+// of them idle). With prepared weights o is half as large and W is read by whole KiBs; only where K is a multiple of 8,192,
+// so that the 128-row blocks lie whole 2 MiB apart, do the blocks of a round stream more slowly than tiles (at 8,192 and
+// 16,384, not at 7,168 and 12,288). Both sides were measured with the decode of a 64-token context, K and N of 1,024 to
+// 16,384, us a call, blocks / tiles:
+//  * row-major: 4,096 x 4,096 (N x K) 16 rows 29.9 / 31.2; 5,120 x 5,120 one row 30.4 / 32.6, four 34.4 / 33.9, 16 48.1 / 37.9;
+//    8,192 x 8,192 four rows 45.3 / 48.0, eight 51.8 / 49.9, 16 65.4 / 53.8; 5,120 x 8,192 one row 39.9 / 38.5; 2,048 x 8,192
+//    four 31.3 / 31.2, 16 44.4 / 36.7; 8,192 x 4,096 eight 33.8 / 36.0, 16 39.9 / 37.3; 16,384 x 2,048 eight
+//    33.8 / 35.5, 16 38.8 / 36.0;
+//  * prepared: 4,096 x 4,096 16 rows 24.2 / 28.2, 32 31.1 / 33.0; 5,120 x 5,120 12 rows 31.1 / 31.7, 16 34.8 / 33.7, 32 45.4 /
+//    38.1; 8,192 x 7,168 16 rows 41.1 / 43.1; 12,288 x 12,288 eight 121 / 129, 16 135 / 130; 8,192 x 8,192 one row 45.2 / 38.5,
+//    16 53.9 / 45.9; 5,120 x 8,192 one 35.3 / 32.9; 2,048 x 8,192 16 rows 32.9 / 33.7, 20 37.8 / 36.5; 4,096 x 6,144 32 rows
+//    39.0 / 39.6.
+static bool wo_by_rows(int K, int N, int B, bool prepared) {
+  const int blocks = (N + 15) / 16, cus = num_cus();
+  const bool one_round = blocks <= cus, part_round = !one_round && 2 * blocks < 3 * cus;
+  const long long bk = (long long)B * K;
+  if (prepared) {
+    if (K % 8192 == 0 && N > 2048) return false;
+    if (B <= kWoRowBatch) return bk <= (part_round ? 65536 : 131072);
+    return B <= 2 * kWoRowBatch && one_round && K < 8192;
+  }
+  if (one_round) return B <= kWoRowBatch && bk <= (2 * blocks > cus ? 65536 : 32768);
+  return B <= kWoRowBatch / 2 && bk <= (part_round ? 6144 : 32768);
+}
+
 // y = sum over slices, in slice order, of partial[s] (B x N, fp32). Four consecutive elements per
 // thread; the loads of all slices are issued before the sums (no load waits behind an add).
 constexpr int kWoMaxUnroll = 8;
@@ -281,11 +309,8 @@ hipError_t launch_wo_gemm(const uint16_t* ob, const uint16_t* W, bool prepared, 
   if (K % kWoKStep != 0 || B <= 0 || N <= 0 || ksplit != wo_ksplit(K, N, B) ||
       (!prepared && (size_t)N * K * 2 >= (1ull << 32)) || (size_t)2 * B * K * 2 >= (1ull << 32))
     return hipErrorInvalidValue;
-  // One launch of 16-row blocks for up to 16 batch rows, and for up to 32 with prepared weights while every block
-  // has a CU of its own (us a step there, 16-row blocks / tiles and sum: 20 rows 29.5 / 32.7, 32 rows 32.7 / 34.5 at
-  // 4,096 x 4,096; but 92.4 / 82.8 at 5,120 x 5,120, 42.1 / 37.1 row-major, and worse from 48 rows on)
   const dim3 rows((N + 15) / 16), block(64 * kWoRowWaves);
-  if (B <= kWoRowBatch || (prepared && B <= 2 * kWoRowBatch && (int)rows.x <= num_cus())) {
+  if (wo_by_rows(K, N, B, prepared)) {
     if (!prepared)
       hipLaunchKernelGGL((wo_rows_kernel<false, 1>), rows, block, 0, s, ob, W, y, B, K, N);
     else if (B <= kWoRowBatch)
@@ -318,7 +343,7 @@ int wo_slice(int K, int N, int B) {
   return kWoKStep * ((steps + want - 1) / want);
 }
 int wo_ksplit(int K, int N, int B) {
-  if (B <= kWoRowBatch) return 1;
+  if (wo_by_rows(K, N, B, false) && wo_by_rows(K, N, B, true)) return 1;  // no tiles in either weight format
   const int sl = wo_slice(K, N, B);
   return (K + sl - 1) / sl;
 }

@@ -17,6 +17,18 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("B", [1, 16, 17, 32, 33])
 @pytest.mark.parametrize("Hq,H,dm", [(1, 1, 8), (3, 1, 130), (8, 2, 257), (20, 4, 4100)])
 def test_projection_of_few_rows(B, Hq, H, dm, fmt):
+    _check(B, Hq, H, dm, fmt)
+
+
+# both sides of the bounds on rows x K (at 256 CUs): blocks just over the CUs, K of 8,192 with more than 2,048 rows of W
+@pytest.mark.parametrize("fmt", ["plain", "prepared"])
+@pytest.mark.parametrize("B,Hq,H,dm", [(1, 40, 8, 4100), (2, 40, 8, 4100), (12, 40, 8, 4100), (13, 40, 8, 4100), (8, 64, 8, 2056),
+                                       (9, 64, 8, 2056), (4, 64, 8, 2048), (5, 64, 8, 2048)])
+def test_projection_by_rows_or_tiles(B, Hq, H, dm, fmt):
+    _check(B, Hq, H, dm, fmt)
+
+
+def _check(B, Hq, H, dm, fmt):
     w = W.make_workload(1, batch=B, ctx_lens=np.arange(B) % 3 * 7 + 1, num_q_heads=Hq, num_kv_heads=H, d_model=dm)
     pool = oracle_pool(w)
     Wo, f = dev(w.W_o), {"plain": K.INT2KV_WO_PLAIN, "folded": K.INT2KV_WO_FOLDED, "prepared": K.INT2KV_WO_PREPARED,
