@@ -155,7 +155,23 @@ hipError_t launch_pack_rotated(CacheView c, const float* k_rot, const float* v_r
   return hipGetLastError();
 }
 
-// Standalone append kernel: grid (blocks per (h, K|V), KV heads, K|V): a CU holds a key and a value work-group.
+// Place of a work-group of the standalone kernels: KV head, K or V and its block among those of that pair. Work-groups go
+// round-robin to the 8 XCDs, so with the blocks of a pair first in the grid every XCD's L2 reads every R (2 H x 64 KiB). From
+// 16 heads on the heads come first instead, and the blocks of one head share an XCD (H a multiple of 8): 32 heads, RoPE,
+// 256 and 512 tokens 9.8 -> 7.8 and 12.8 -> 10.0 us, dense, 256 tokens 9.2 -> 6.6; 16 heads, RoPE, 2,048 tokens 16.1 -> 15.3; at 8
+// heads nothing (RoPE, 4,096 tokens 15.1 / 15.8). Keys and values stay the last dimension: a CU holds a work-group of each.
+struct ApPlace {
+  int bx, nbx, h, kv;
+};
+__device__ __forceinline__ ApPlace ap_place(int heads_first) {
+  return heads_first ? ApPlace{(int)blockIdx.y, (int)gridDim.y, (int)blockIdx.x, (int)blockIdx.z}
+                     : ApPlace{(int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y, (int)blockIdx.z};
+}
+inline dim3 ap_grid(int blocks, int heads, int heads_first) {
+  return heads_first ? dim3(heads, blocks, 2) : dim3(blocks, heads, 2);
+}
+
+// Standalone append kernel.
 template <int NG, bool ERR, bool ROPE>
 __global__ __launch_bounds__(kApThreads, 2) void append_mfma_kernel(CacheView cv, const uint16_t* __restrict__ k,
                                                                     const uint16_t* __restrict__ v,
@@ -163,11 +179,13 @@ __global__ __launch_bounds__(kApThreads, 2) void append_mfma_kernel(CacheView cv
                                                                     const float* __restrict__ R_k,
                                                                     const float* __restrict__ R_v,
                                                                     const float* __restrict__ mu_rk, float clip_k,
-                                                                    float clip_v, float* __restrict__ err, ApOpts opt) {
+                                                                    float clip_v, float* __restrict__ err, ApOpts opt,
+                                                                    int heads_first) {
   __shared__ ApLds lds;
   __shared__ __attribute__((aligned(16))) int pos[ROPE ? kApPos : 4];
-  append_block<NG, ERR, ROPE>(cv, k, v, slots, n, R_k, R_v, mu_rk, clip_k, clip_v, (int)blockIdx.x, (int)gridDim.x,
-                              (int)blockIdx.y, (int)blockIdx.z, lds, pos, err, opt);
+  const ApPlace p = ap_place(heads_first);
+  append_block<NG, ERR, ROPE>(cv, k, v, slots, n, R_k, R_v, mu_rk, clip_k, clip_v, p.bx, p.nbx, p.h, p.kv, lds, pos,
+                              err, opt);
 }
 
 // Long dense appends: grid as above, eight waves.
@@ -178,10 +196,10 @@ __global__ __launch_bounds__(64 * kWdWaves) void append_wide_kernel(CacheView cv
                                                                     const float* __restrict__ R_k,
                                                                     const float* __restrict__ R_v,
                                                                     const float* __restrict__ mu_rk, float clip_k,
-                                                                    float clip_v, float* __restrict__ err, int had) {
+                                                                    float clip_v, float* __restrict__ err, int had, int heads_first) {
   __shared__ __attribute__((aligned(16))) uint8_t lds[kWideLdsBytes];
-  append_wide_block<NG, ERR>(cv, k, v, slots, n, R_k, R_v, mu_rk, clip_k, clip_v, (int)blockIdx.x, (int)gridDim.x,
-                             (int)blockIdx.y, (int)blockIdx.z, lds, err, had);
+  const ApPlace p = ap_place(heads_first);
+  append_wide_block<NG, ERR>(cv, k, v, slots, n, R_k, R_v, mu_rk, clip_k, clip_v, p.bx, p.nbx, p.h, p.kv, lds, err, had);
 }
 
 hipError_t launch_append_mfma(CacheView c, const uint16_t* k, const uint16_t* v, const int32_t* slots, int n,
@@ -199,19 +217,20 @@ hipError_t launch_append_mfma(CacheView c, const uint16_t* k, const uint16_t* v,
   if (n <= 0) return hipSuccess;
   // two work-groups per CU over the (KV head, K|V) pairs, each converting its R once for all its tiles
   const int tiles = (n + kApTok - 1) / kApTok, per_head = max(1, num_cus() / c.num_kv_heads);
-  const dim3 grid(min(tiles, per_head), c.num_kv_heads, 2), block(kApThreads);
+  const int heads_first = c.num_kv_heads >= 16;
+  const dim3 grid = ap_grid(min(tiles, per_head), c.num_kv_heads, heads_first), block(kApThreads);
   // the instantiation: 4 or 1 groups per token, plain, with the reconstruction error or with RoPE
   auto go = [&](auto ng_tag) {
     constexpr int NG = decltype(ng_tag)::value;
     if (opt.pos)
       hipExtLaunchKernelGGL((append_mfma_kernel<NG, false, true>), grid, block, 0, s, ev0, ev1, 0, c, k, v, slots, n,
-                            R_k, R_v, mu_rk, clip_k, clip_v, err, opt);
+                            R_k, R_v, mu_rk, clip_k, clip_v, err, opt, heads_first);
     else if (err)
       hipExtLaunchKernelGGL((append_mfma_kernel<NG, true, false>), grid, block, 0, s, ev0, ev1, 0, c, k, v, slots, n,
-                            R_k, R_v, mu_rk, clip_k, clip_v, err, opt);
+                            R_k, R_v, mu_rk, clip_k, clip_v, err, opt, heads_first);
     else
       hipExtLaunchKernelGGL((append_mfma_kernel<NG, false, false>), grid, block, 0, s, ev0, ev1, 0, c, k, v, slots, n,
-                            R_k, R_v, mu_rk, clip_k, clip_v, err, opt);
+                            R_k, R_v, mu_rk, clip_k, clip_v, err, opt, heads_first);
   };
   // the wide arrangement (append_wide.h): one work-group per CU, once every wave of the chip has a step (there it
   // takes 11.9 us against 13.0 at 8 heads; with half as many tokens 10.7 against 8.9)
@@ -219,9 +238,9 @@ hipError_t launch_append_mfma(CacheView c, const uint16_t* k, const uint16_t* v,
   auto go_wide = [&](auto ng_tag, auto err_tag) {
     constexpr int NG = decltype(ng_tag)::value;
     constexpr bool ERR = decltype(err_tag)::value;
-    const dim3 wide(min((tiles + kWdWaves - 1) / kWdWaves, per_wide), c.num_kv_heads, 2);
+    const dim3 wide = ap_grid(min((tiles + kWdWaves - 1) / kWdWaves, per_wide), c.num_kv_heads, heads_first);
     hipExtLaunchKernelGGL((append_wide_kernel<NG, ERR>), wide, dim3(64 * kWdWaves), 0, s, ev0, ev1, 0, c, k, v, slots,
-                          n, R_k, R_v, mu_rk, clip_k, clip_v, err, opt.had);
+                          n, R_k, R_v, mu_rk, clip_k, clip_v, err, opt.had, heads_first);
   };
   using One = std::integral_constant<int, 1>;
   using Four = std::integral_constant<int, 4>;
