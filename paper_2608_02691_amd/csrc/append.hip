@@ -188,8 +188,8 @@ __global__ __launch_bounds__(kApThreads, 2) void append_mfma_kernel(CacheView cv
                               err, opt);
 }
 
-// Long dense appends: grid as above, eight waves.
-template <int NG, bool ERR>
+// The wide arrangement: grid as above, eight waves.
+template <int NG, bool ERR, int kTiles>
 __global__ __launch_bounds__(64 * kWdWaves) void append_wide_kernel(CacheView cv, const uint16_t* __restrict__ k,
                                                                     const uint16_t* __restrict__ v,
                                                                     const int32_t* __restrict__ slots, int n,
@@ -199,7 +199,8 @@ __global__ __launch_bounds__(64 * kWdWaves) void append_wide_kernel(CacheView cv
                                                                     float clip_v, float* __restrict__ err, int had, int heads_first) {
   __shared__ __attribute__((aligned(16))) uint8_t lds[kWideLdsBytes];
   const ApPlace p = ap_place(heads_first);
-  append_wide_block<NG, ERR>(cv, k, v, slots, n, R_k, R_v, mu_rk, clip_k, clip_v, p.bx, p.nbx, p.h, p.kv, lds, err, had);
+  append_wide_block<NG, ERR, kTiles>(cv, k, v, slots, n, R_k, R_v, mu_rk, clip_k, clip_v, p.bx, p.nbx, p.h, p.kv, lds, err,
+                                     had);
 }
 
 hipError_t launch_append_mfma(CacheView c, const uint16_t* k, const uint16_t* v, const int32_t* slots, int n,
@@ -232,19 +233,33 @@ hipError_t launch_append_mfma(CacheView c, const uint16_t* k, const uint16_t* v,
       hipExtLaunchKernelGGL((append_mfma_kernel<NG, false, false>), grid, block, 0, s, ev0, ev1, 0, c, k, v, slots, n,
                             R_k, R_v, mu_rk, clip_k, clip_v, err, opt, heads_first);
   };
-  // the wide arrangement (append_wide.h): one work-group per CU, once every wave of the chip has a step (there it
-  // takes 11.9 us against 13.0 at 8 heads; with half as many tokens 10.7 against 8.9)
-  const int per_wide = max(1, num_cus() / (2 * c.num_kv_heads));
+  // The wide arrangement (append_wide.h), one work-group per CU, for keys that are already post-RoPE. With one 16-token
+  // tile per wave, while that takes one step, it beats two tiles in turn of the blocks above; beyond, its steps of two
+  // tiles beat four. With one group per token the blocks above exchange extremes at a barrier more, and Hadamard rotations
+  // need no R, so there two work-groups on a CU already lose to it. Kernel time in us, blocks above / wide, at x = tiles per
+  // block above. G = 32, 8 heads: 512 tokens (x = 1/2) 5.2 / 6.6, 1,024 (1) 6.8 / 6.9, 1,500 8.2 / 7.2, 2,048 (2) 8.5 / 7.6, 2,500
+  // 10.1 / 10.3, 3,072 (3) 10.6 / 10.7, 3,300 11.7 / 10.8; 32 heads: 256 (1) 6.6 / 6.9, 300 7.9 / 7.0, 520 9.6 / 10.2, 768 (3) 10.2 /
+  // 10.7. G = 128, 8 heads: 512 5.1 / 6.5, 700 6.7 / 6.6, 1,024 7.0 / 6.8, 2,048 8.7 / 7.4, 2,500 10.3 / 10.1; 12 heads, 1,300 (just
+  // under 2, but two steps) 9.6 / 10.5. Hadamard, 8 heads: 512 4.2 / 4.6, 1,500 6.8 / 5.0, 2,100 7.7 / 7.2; 32 heads, 256 5.6 / 4.9.
+  const int H = c.num_kv_heads, per_wide = max(1, num_cus() / (2 * H)), tiles16 = (n + 15) / 16;
+  const bool one_step = tiles16 <= kWdWaves * per_wide;
+  const bool wide = one_step ? (c.groups == 1 || opt.had == 3 ? 2LL * tiles > per_head : tiles > per_head)
+                             : tiles > (opt.had == 3 ? 1LL : c.groups == 1 ? 2LL : 3LL) * per_head;
   auto go_wide = [&](auto ng_tag, auto err_tag) {
     constexpr int NG = decltype(ng_tag)::value;
     constexpr bool ERR = decltype(err_tag)::value;
-    const dim3 wide = ap_grid(min((tiles + kWdWaves - 1) / kWdWaves, per_wide), c.num_kv_heads, heads_first);
-    hipExtLaunchKernelGGL((append_wide_kernel<NG, ERR>), wide, dim3(64 * kWdWaves), 0, s, ev0, ev1, 0, c, k, v, slots,
-                          n, R_k, R_v, mu_rk, clip_k, clip_v, err, opt.had, heads_first);
+    auto launch = [&](auto tiles_tag) {
+      constexpr int kTiles = decltype(tiles_tag)::value;
+      const int steps = (tiles16 + kTiles - 1) / kTiles;
+      const dim3 wgrid = ap_grid(min((steps + kWdWaves - 1) / kWdWaves, per_wide), H, heads_first);
+      hipExtLaunchKernelGGL((append_wide_kernel<NG, ERR, kTiles>), wgrid, dim3(64 * kWdWaves), 0, s, ev0, ev1, 0, c, k, v,
+                            slots, n, R_k, R_v, mu_rk, clip_k, clip_v, err, opt.had, heads_first);
+    };
+    one_step ? launch(std::integral_constant<int, 1>{}) : launch(std::integral_constant<int, 2>{});
   };
   using One = std::integral_constant<int, 1>;
   using Four = std::integral_constant<int, 4>;
-  if (!opt.pos && tiles >= kWdWaves * per_wide) {
+  if (!opt.pos && wide) {
     if (c.groups == 1)
       err ? go_wide(One{}, std::true_type{}) : go_wide(One{}, std::false_type{});
     else

@@ -1,12 +1,13 @@
 // The cache write of long dense prompts: the same products, quantizer and stores as append_core.h in another
-// arrangement, for appends whose tiles fill the chip and whose keys are already post-RoPE. A work-group of eight waves holds R^T as three bf16 terms in LDS (rows padded to 288 B,
-// conflict-free 16-byte reads) and each wave takes two 16-token tiles of all 128 channels per step, so a token's
-// four groups stay in one wave (no exchange through LDS and no barrier in the loop): 96 fragments of R^T, each
-// read from LDS for two products. LDS, matrix cores and vector ALU each need about 20 us of the 32,768-token
-// prefill's time and share it badly; the arrangement with R^T in registers needs less LDS but a barrier per
-// tile: us at 8 KV heads, this one / that one: dense, G = 32:
-// 32,768 tokens 54.0 / 61.5, 8,192 17.8 / 20.0, 4,096 11.9 / 13.0, 2,048 10.7 / 8.9; G = 128, 32,768 tokens 52.0 / 64.8;
-// Hadamard, 32,768 tokens 39.9 / 46.0.
+// arrangement, for keys that are already post-RoPE. A work-group of eight waves holds R^T as three bf16 terms in LDS
+// (rows padded to 288 B, conflict-free 16-byte reads) and each wave takes two 16-token tiles of all 128 channels per
+// step, so a token's four groups stay in one wave (no exchange through LDS and no barrier in the loop): 96 fragments of
+// R^T, each read from LDS for two products. With one tile per step (kTiles = 1) it serves short prompts of many heads,
+// whose blocks take one step: there a block of the other arrangement would take a second tile. LDS, matrix cores and
+// vector ALU each need about 20 us of the 32,768-token prefill's time and share it badly; the arrangement with R^T in
+// registers needs less LDS but a barrier per tile: us at 8 KV heads, this one / that one: dense, G = 32: 32,768 tokens
+// 54.0 / 61.5, 8,192 17.8 / 20.0, 4,096 10.7 / 12.9, 2,048 9.9 / 8.6; G = 128, 32,768 tokens 52.0 / 64.8; Hadamard,
+// 32,768 tokens 39.9 / 46.0.
 //
 // The product is formed transposed, D^T = R^T x^T: D^T[channel][token] of m-tile p (channels 16p .. 16p + 15) sits
 // in lane token + 16 ((channel % 16) / 4), register channel % 4: lane (token, hi) holds channels
@@ -198,18 +199,18 @@ __device__ __forceinline__ void store_tile(const WdOut& o, int slot, const Cache
   }
 }
 
-// One work-group of kWdWaves waves: KV head h, K (kv = 0) or V (kv = 1), block bx of nbx striding over the 32-token
-// steps; lds holds kWideLdsBytes (16-byte aligned). Every thread of the block must call it (it synchronizes
+// One work-group of kWdWaves waves: KV head h, K (kv = 0) or V (kv = 1), block bx of nbx striding over the steps of
+// kTiles 16-token tiles; lds holds kWideLdsBytes (16-byte aligned). Every thread of the block must call it (it synchronizes
 // once). With ERR, err[(token * H + h) * 2 + kv] receives each token's squared reconstruction error.
 // Bit kv of had_flags: the Hadamard rotation in place of R.
-template <int NG, bool ERR>
+template <int NG, bool ERR, int kTiles>
 __device__ __forceinline__ void append_wide_block(const CacheView& cv, const uint16_t* __restrict__ k,
                                                   const uint16_t* __restrict__ v, const int32_t* __restrict__ slots,
                                                   int n, const float* __restrict__ R_k, const float* __restrict__ R_v,
                                                   const float* __restrict__ mu_rk, float clip_k, float clip_v, int bx,
                                                   int nbx, int h, int kv, uint8_t* lds, float* __restrict__ err,
                                                   int had_flags) {
-  constexpr int kTiles = 2, kWaves = kWdWaves;
+  constexpr int kWaves = kWdWaves;
   uint16_t(*rt)[kHeadDim][kWdRow] = reinterpret_cast<uint16_t(*)[kHeadDim][kWdRow]>(lds);  // [term][c][i] = R[i][c]
   float* recip_tab = reinterpret_cast<float*>(lds + 3 * kHeadDim * kWdRow * 2);  // RN(1 / (1 + m / 1024))
   const int H = cv.num_kv_heads, tid = threadIdx.x;
