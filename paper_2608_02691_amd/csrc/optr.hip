@@ -15,7 +15,8 @@
 // G R masked, dL/dR = X^T (mask . G R) + G^T Zhat, dL/dE = R0^T dL/dR for E = exp(S), dL/dS as the
 // Frechet derivative of exp at S^T applied to dL/dE (the upper-right block of the exponential of
 // [[S^T, dL/dE], [0, S^T]]), and dL/dA = dL/dS - dL/dS^T.
-// exp: a Taylor polynomial of S 2^-j applied 2^j times, by column blocks (see the matrix functions below).
+// exp: a Taylor polynomial of S 2^-j by column blocks, the last of the j doublings as squarings (see the matrix functions
+// below).
 #include <vector>
 
 #include "common.h"
@@ -978,7 +979,7 @@ __global__ __launch_bounds__(512) void cal_dr_kernel(CalSet S, CalCfg c, int val
 constexpr int kExpCols = 16;      // columns per work-group
 constexpr int kExpThreads = 512;  // eight waves of 16 rows
 constexpr double kExpTheta = 3.5;
-constexpr int kExpMaxBlocks = 9;  // nb at most (theta^32 / 32! < 2^-55)
+constexpr int kExpMaxBlocks = 8;  // nb at most (theta^32 / 32! < 2^-55)
 constexpr int kExpSquares = 2;    // doublings done by squaring launches
 constexpr int kExpMaxReps = 5;    // halvings (and so up to 2^3 applications) per column block
 // scratch matrices of a head (c.ex): powers of S, then of [[X, G], [0, X]] with X = S^T = -S (upper right
@@ -994,8 +995,7 @@ __device__ constexpr double kInvFact[4 * kExpMaxBlocks] = {
     0x1.952c77030ad4ap-49, 0x1.6827863b97d97p-53, 0x1.2f49b46814157p-57, 0x1.e542ba4020225p-62,
     0x1.71b8ef6dcf572p-66, 0x1.0ce396db7f853p-70, 0x1.761b41316381ap-75, 0x1.f2cf01972f578p-80,
     0x1.3f3ccdd165fa9p-84, 0x1.88e85fc6a4e5ap-89, 0x1.d1ab1c2dccea3p-94, 0x1.0a18a2635085dp-98,
-    0x1.259f98b4358adp-103, 0x1.3932c5047d60ep-108, 0x1.434d2e783f5bcp-113, 0x1.434d2e783f5bcp-118,
-    0x1.3981254dd0d52p-123, 0x1.2710231c0fd7ap-128, 0x1.0dc59c716d91fp-133};
+    0x1.259f98b4358adp-103, 0x1.3932c5047d60ep-108, 0x1.434d2e783f5bcp-113};
 
 struct ExpBuf {
   double y[2][kD * kExpCols];  // column block, two buffers
