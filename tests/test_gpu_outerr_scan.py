@@ -1,4 +1,4 @@
-"""The output-error scan's scores against the CPU oracle at fp32 precision: query heads that fill and part-fill the
+"""The output-error scan's scores and statistics against the CPU oracle at fp32 precision: query heads that fill and part-fill the
 quads of the score tiles, queries far from unit scale (the scan rescales them by powers of two) and one of zeros,
 page and chunk edges."""
 import numpy as np
@@ -19,6 +19,10 @@ pytestmark = pytest.mark.gpu
 # p, 1e-6 of ||o|| with the fp32 sums; dy is a difference of two of them, 10% of ||o|| or more for INT2. Factor 2 for
 # the norm over W_O's rows.
 ROW_RTOL = 2e-5
+# A statistic is a square or product of two rows, summed: its error is that of the rows along each other, and over many
+# (sequence, head) pairs it is typical and not worst: 2^-24 of |q| |k| / sqrt(128) a logit, 1e-6 of dy, once for each row.
+# Scores with subnormal fp16 operands, whose products lose their leading zeros, give 2e-5.
+STATS_RMS = 2e-6
 
 
 # heads of one KV head, KV heads, context lengths, group, scale of the queries
@@ -38,8 +42,8 @@ def test_output_error_scores_hold_fp32(gq, H, lens, G, scale):
     row_cap = int(lens.max())
     pool = oracle_pool(w, group=G)
     kr, vr, ks, vs = _rows(w, row_cap)
-    dyK, dyV, _ = O.output_error(pool, ks, vs, q, lens, w.block_table, w.R_k, w.R_v, w.mu, w.W_o)
-    _, dy = K.int2kv_output_error(gpu_cache(pool), dev(q), dev(w.block_table), dev(lens.astype(np.int32)), row_cap,
+    dyK, dyV, ref_stats = O.output_error(pool, ks, vs, q, lens, w.block_table, w.R_k, w.R_v, w.mu, w.W_o)
+    stats, dy = K.int2kv_output_error(gpu_cache(pool), dev(q), dev(w.block_table), dev(lens.astype(np.int32)), row_cap,
                                   dev(w.R_k), dev(w.R_v), dev(kr), dev(vr), row_cap, dev(w.W_o), want_dy=True)
     dy = dy.cpu().numpy().astype(np.float64)
     # against the larger of the two: a key error of nearly equal keys can vanish, its rounding does not
@@ -47,3 +51,7 @@ def test_output_error_scores_hold_fp32(gq, H, lens, G, scale):
     worst = max(float((np.linalg.norm(dy[:, :, i] - ref, axis=-1) / norm).max()) for i, ref in enumerate((dyK, dyV)))
     print(f"worst row error {worst:.2e}", flush=True)
     assert worst <= ROW_RTOL * max(1.0, scale)
+    rel = np.abs(stats.cpu().numpy() - ref_stats) / (norm ** 2)[..., None]
+    rms = float(np.sqrt((rel ** 2).mean()))
+    print(f"statistics: rms error {rms:.2e}", flush=True)
+    assert rms <= STATS_RMS * max(1.0, scale)
