@@ -86,3 +86,40 @@ def test_merge_block_counts(B, Hq, H, window, wo):
         ref = O.decode(pool, w.q, w.block_table, w.ctx_lens, w.R_k, w.R_v, ref_wo)
     torch.cuda.synchronize()
     assert_rows_close(out.cpu().numpy(), ref, what=f"{B} {Hq}/{H} {window} {wo}")
+
+
+@pytest.mark.parametrize("B,Hq,H", [(3, 8, 4), (40, 32, 8)])  # a block per query head, per KV head
+@pytest.mark.parametrize("window", [0, 40])
+@pytest.mark.parametrize("what", ["v_zero_nan", "v_scale_inf", "q_nan", "q_inf"])
+def test_merge_keeps_non_finite_values_to_their_heads(B, Hq, H, window, what):
+    """A NaN or an infinity in one head's cached values reaches that head's outputs and no other's bits; one in a query
+    changes no other query's output (beyond the rounding of the heads scanned together with it)."""
+    rng = np.random.default_rng([B, window])
+    w = W.make_workload(1, batch=B, ctx_lens=np.full(B, 300), num_q_heads=Hq, num_kv_heads=H, d_model=None)
+    cache, _ = _random_cache(w, rng, 32)
+    q = dev(w.q)
+    win = [dev(W.f32_to_bf16_bits(rng.standard_normal((B * window, H, 128)).astype(np.float32))) for _ in range(2)]
+    wl = torch.full((B,), window, dtype=torch.int32, device="cuda")
+
+    def run():
+        args = (cache, q, dev(w.block_table), dev(w.ctx_lens), 300, dev(w.R_k), dev(w.R_v))
+        out = K.int2kv_decode_window(*args, *win, wl, window) if window else K.int2kv_decode(*args)
+        return out.cpu().numpy().reshape(B, H, Hq // H, 128)
+
+    clean = run()
+    halves = cache.pool.view(torch.int16)[int(w.block_table[1, 2]), 0]  # KV head 0 of sequence 1, token 0 of a page
+    if what == "v_zero_nan":
+        halves[1408 // 2] = 0x7E00
+    elif what == "v_scale_inf":
+        halves[1280 // 2] = 0x7C00
+    else:
+        q.view(torch.bfloat16)[1, 0, 5] = float("nan" if what == "q_nan" else "inf")
+    got = run()
+    assert np.isfinite(clean).all()
+    others = np.ones((B, H), bool)
+    others[1, 0] = False
+    assert np.array_equal(got[others], clean[others])
+    if what[0] == "v":
+        assert not np.isfinite(got[1, 0]).all(axis=-1).any()
+    else:
+        assert_rows_close(got[1, 0, 1:], clean[1, 0, 1:], what="the other queries of the KV head")

@@ -55,3 +55,32 @@ def test_output_error_scores_hold_fp32(gq, H, lens, G, scale):
     rms = float(np.sqrt((rel ** 2).mean()))
     print(f"statistics: rms error {rms:.2e}", flush=True)
     assert rms <= STATS_RMS * max(1.0, scale)
+
+
+@pytest.mark.parametrize("gq,H", [(2, 2), (6, 2), (12, 1)])
+@pytest.mark.parametrize("what", ["k_nan", "v_nan", "v_inf", "q_nan"])
+def test_non_finite_rows_stay_with_their_heads(gq, H, what):
+    """A NaN or an infinity in one sequence's rows of a KV head, or in a query, changes no other sequence's, KV head's or
+    query's statistics; in the values it reaches every statistic of its own."""
+    w = W.make_workload(1, batch=3, ctx_lens=np.array([300, 200, 40]), num_q_heads=gq * H, num_kv_heads=H, d_model=64)
+    kr, vr, _, _ = _rows(w, 300)
+    q, kr, vr = dev(w.q), dev(kr), dev(vr)
+    cache = gpu_cache(oracle_pool(w))
+
+    def run():
+        stats, dy = K.int2kv_output_error(cache, q, dev(w.block_table), dev(w.ctx_lens), 300, dev(w.R_k), dev(w.R_v), kr,
+                                          vr, 300, dev(w.W_o), want_dy=True)
+        return stats.cpu().numpy().reshape(3, H, gq, 4), dy.cpu().numpy().reshape(3, H, gq, -1)
+
+    clean = run()
+    bad = float("inf" if what == "v_inf" else "nan")
+    if what == "q_nan":
+        q.view(torch.bfloat16)[1, 0, 5] = bad
+    else:
+        (kr if what == "k_nan" else vr).view(torch.bfloat16).reshape(3, 300, H, 128)[1, 77, 0, 5] = bad
+    others = np.ones((3, H, gq), bool)
+    others[1, 0, 0 if what == "q_nan" else slice(None)] = False
+    for x, y in zip(run(), clean):
+        assert np.isfinite(y).all() and np.array_equal(x[others], y[others])
+        if what[0] == "v":
+            assert not np.isfinite(x[1, 0]).all(axis=-1).any()
