@@ -487,7 +487,9 @@ def main():
                 with_events(lambda: K.int2kv_quantize_append(cache, k_all, v_all, slots_all, Rk, Rv, mu_rk, clip_k,
                                                              clip_v))
 
-        dom_name = "cache write (append_mfma_kernel)"
+        # keys before RoPE, and up to three 32-token tiles per work-group, go to append_mfma_kernel
+        short = n_tok <= 96 * max(1, torch.cuda.get_device_properties(0).multi_processor_count // H)
+        dom_name = f"cache write ({'append_mfma_kernel' if args.rope or short else 'append_wide_kernel'})"
         dom_bytes = (n_tok * H * (512 + tok_bytes) + 4 * n_tok + (0 if args.hadamard else R_bytes) + H * 128 * 4
                      + (4 * n_tok + int(lens.max()) * 512 if args.rope else 0))
         step_bytes = dom_bytes

@@ -31,7 +31,7 @@ namespace int2kv {
 // prompts therefore use the arrangement of append_wide.h.
 //
 // Us a call at 8 KV heads, against sixteen 16-token tiles per eight-wave work-group with R^T in LDS: RoPE,
-// 32,768 tokens 91 -> 75; RoPE and Hadamard, 16,384 tokens 44.5 -> 31.8; RoPE, G = 128, 2,011 tokens 11.3 ->
+// 32,768 tokens 91 -> 75; RoPE and Hadamard, 16,384 tokens 44.4 -> 33; RoPE, G = 128, 2,011 tokens 11.3 ->
 // 10.6; one decode step (32/8 heads, 1,011 tokens), whose first launch carries the write, 30.5 -> 28.8.
 typedef __bf16 ap_bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float ap_f16_t __attribute__((ext_vector_type(16)));
@@ -96,9 +96,7 @@ __device__ __forceinline__ void int2_group_params_fast(float mn, float mx, float
 
 // Cross-lane exchanges of the group reductions on the vector ALU (no LDS round trip).
 // lane_swap32(a, b): lanes 32-63 of a trade places with lanes 0-31 of b, so afterwards lane l < 32
-// holds (a[l], a[l + 32]) and lane l >= 32 holds (b[l - 32], b[l]). lane_swap16: the same between
-// the odd 16-lane rows of a and the even rows of b, so a lane of an even row holds (a[l], a[l + 16])
-// and a lane of an odd row (b[l - 16], b[l]).
+// holds (a[l], a[l + 32]) and lane l >= 32 holds (b[l - 32], b[l]).
 struct LanePair {
   float a, b;
 };
@@ -191,9 +189,11 @@ __device__ __forceinline__ uint32_t f64_to_bf16_rne(double d) {
 // E a little above that bound (and above 2^-120, which covers underflow) the exact value lies in [y - E, y + E];
 // when both ends round to the same bf16 value, so does the exact value (and its fp64 rounding, which lies between
 // them too). Otherwise, and for infinities and NaN (E is not below 2^100 then), `unsure` is set and the caller
-// takes fp64. About one word in twenty of a wave is unsure on N(0, 1) keys. Per pair 20 vector instructions
-// instead of about 50, with fp64 at half rate; the write is bound by the rows and the table it moves (without the
-// output rows 44 -> 30 us), so this shows only once those move well.
+// takes fp64. On N(0, 1) keys one word in 3,000 is unsure, so a wave takes fp64 for 2 % of its words; words of zeros
+// always are (an interval around zero has two signs: 16,384 tokens of zero keys 39 us against 33 to 35 of N(0, 1)
+// keys, and 39.7 with fp64 throughout). Per pair 20 vector instructions instead of about 50, with fp64 at half
+// rate; the write is bound by the rows and the table it moves (without the output rows 44 -> 30 us), so this shows
+// only once those move well.
 struct RopeWord {
   uint32_t a, b;
   bool unsure;

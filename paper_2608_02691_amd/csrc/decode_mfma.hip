@@ -669,9 +669,10 @@ typedef __attribute__((address_space(4))) const int32_t* cint_ptr;  // read thro
 // Work split of the scan. Every sequence a work-group starts costs a prologue and a pipeline
 // refill (measured: about 4 us per extra segment, the time of ~6 pages; 8 units measured best in a
 // sweep of 3 to 10 on the ragged 64-sequence batch), so the pages are split
-// evenly along a cost axis on which each non-empty sequence b occupies [c0(b), c1(b)): kSegCost
-// units of lead-in, then one unit per page (c1 - c0 = kSegCost + pages; empty sequences take no
-// room). Group g of G starts at cost x(g) = floor(g W / G), W = P + kSegCost * (non-empty
+// evenly along a cost axis on which each non-empty sequence b occupies [c0(b), c1(b)): `seg`
+// units of lead-in, then one unit per page (c1 - c0 = seg + pages; empty sequences take no
+// room). seg is kSegCost, half of it among groups of the smallest size, and 0 for a lone sequence
+// (page_prefix_block). Group g of G starts at cost x(g) = floor(g W / G), W = P + seg * (non-empty
 // sequences); a start inside a lead-in maps to the sequence's first page. Ranges that take on
 // extra sequence starts thus get fewer pages.
 #ifndef INT2KV_SCAN_SEG_COST
@@ -683,9 +684,9 @@ constexpr int kSegCost = INT2KV_SCAN_SEG_COST;
 // scan work-group g the sequence b holding the first page of its range with that sequence's page
 // range: wg_info[g] = {b, prefix[b], prefix[b + 1], lo(g)}, wg_info[G].w = P, and for every sequence
 // the first and last group whose range meets it (seq_wg[b] = {ga, gb}, {0, -1} when empty), so that
-// that no later wave divides or searches. With x(g) <= T  <=>  g <= ceil((T + 1) G / W) - 1, the groups
+// no later wave divides or searches. With x(g) <= T  <=>  g <= ceil((T + 1) G / W) - 1, the groups
 // starting in b's span are ceil(c0 G / W) .. ceil(c1 G / W) - 1, the group holding b's first page
-// is the last one with x(g) <= c0 + kSegCost, the one holding its last page the last with
+// is the last one with x(g) <= c0 + seg, the one holding its last page the last with
 // x(g) <= c1 - 1. Every group below G starts in exactly one span (the spans tile [0, W)). One block of 256
 // threads. Up to 256 sequences, a thread takes a group and finds its span by bisection of the spans' ends in
 // LDS; beyond, a thread walks the groups of its sequences. One latency chain, so loops over sequences or groups

@@ -52,8 +52,8 @@ __device__ __forceinline__ void oe_wave_sync() {
 //  * INT2: a code's two bits, shifted to the bottom of a 16-bit half, are the fp16 number code 2^-24; times 2^15 it is
 //    a normal number (the matrix cores align a product by its exponents, so that subnormal factors cost the sum
 //    their leading zeros: statistics to 2e-5 of fp64's instead of 1e-6). q' = q R_K, scaled by a power of two, enters
-//    as three fp16 terms whose sum it is, in rows 4 j .. 4 j + 2: one product per 32-channel group gives
-//    sum_{c in g} q'_c code_c in the lane's first three registers.
+//    as three fp16 terms, whose sum it is to 2^-38 of the row's largest value, in rows 4 j .. 4 j + 2: one product per
+//    32-channel group gives sum_{c in g} q'_c code_c in the lane's first three registers.
 // Softmaxes run on one (token, head) per lane, with maxima and sums over the 16 lanes of a DPP row. For the
 // values lane l owns channels 2 l, 2 l + 1 on the vector ALU. Near the rows' stream: 16 x 4,096 tokens, 32/8 heads
 // 121 us with the scores on the vector ALU (their products and LDS broadcasts of q) -> 83 us for 318 MB. Statistics
