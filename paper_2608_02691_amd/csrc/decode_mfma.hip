@@ -1377,11 +1377,11 @@ __global__ __launch_bounds__(kMhThreads) void merge_head_kernel(DecodeArgs a, in
 }
 
 // Merge with a block per (sequence, KV head); WIN: with the BF16-window partials. A wave's slot is uniform, so the range
-// bounds, the partials' addresses and their (m, l) live in scalar registers: 62 to 91 vector registers at four and
-// eight slots, without and with windows, against 127 and the cap of 128 with four spilled when the slot was per lane and
+// bounds, the partials' addresses and their (m, l) live in scalar registers: 62, 66 and 75 vector registers at four and
+// eight slots and at eight with windows, against 127 and the cap of 128 with four spilled when the slot was per lane and
 // the windows a branch. Us a call, that form / this one: 28 x 3,000 tokens, 40/8 heads, projection folded 44.7 / 43.9; 24 x
-// 100..1,000, 32/8 heads 28.5 / 27.6; 28 x 3,000 with windows 66.7 / 65.0; 64 x 500..2,000 48.0 / 47.5; eight query heads
-// per KV head 0.3 to 0.5 us slower (68.5 / 69.0 with windows).
+// 100..1,000, 32/8 heads 28.5 / 27.6; 28 x 3,000 with windows 66.7 / 65.0; 64 x 500..2,000 48.0 / 47.5. Four slots with windows
+// keep the slot per lane (128 registers, none spilled): 32 ragged sequences, 40/8 heads 82.2 / 83.0 with it uniform.
 template <int kMergeSlots, bool WIN>
 __global__ __launch_bounds__(128 * kMergeSlots) void merge_flat_kernel(DecodeArgs a, int unrotate,
                                                                        float* __restrict__ out,
@@ -1391,7 +1391,8 @@ __global__ __launch_bounds__(128 * kMergeSlots) void merge_flat_kernel(DecodeArg
   __shared__ float vs[8][kHeadDim];
   __shared__ float wsh[8][kHeadDim];  // BF16-window part of each head output (model basis)
   const int b = blockIdx.x, h = blockIdx.y, c = threadIdx.x & 127, gq = a.gq;
-  const int sl = __builtin_amdgcn_readfirstlane(threadIdx.x >> 7);  // a wave lies in one slot
+  // a wave lies in one slot
+  const int sl = WIN && kMergeSlots == 4 ? threadIdx.x >> 7 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 7);
   // the BF16-window partials of this thread's query heads (model basis, one per window slice), all
   // loaded first (slices past win_slices read slice 0 and are dropped), folded in below
   constexpr int kR = 8 / kMergeSlots;
